@@ -114,15 +114,13 @@ struct hgs_ctx {
     uint8_t *qbits = nullptr;  // forward quarter records, kMaxBlocks planes of pair_cap bytes
     uint32_t *dup_first = nullptr;  // first splat of every pair-emission block
     uint32_t *k2 = nullptr, *v2 = nullptr;
-    uint32_t *hist = nullptr, *hist_scan = nullptr, *partial = nullptr, *scan_total = nullptr;
-    SortBlock *sort_plan = nullptr;  // work of every block of a per-view (segmented) sort
-    uint32_t *vis_bounds = nullptr, *pair_bounds = nullptr, *seg_tile_base = nullptr;  // per view
+    uint32_t *hist = nullptr, *sort_tot = nullptr, *partial = nullptr;
+    SortPlan sort_plan{};            // segments (one per view) of the sort under way
+    uint32_t *vis_bounds = nullptr;  // per view: its first visible splat
     uint2 *ranges = nullptr;
-    uint32_t *tile_keys = nullptr, *tile_order = nullptr, *tile_k2 = nullptr, *tile_v2 = nullptr;
-    uint32_t *tile_n = nullptr;
+    uint32_t *tile_order = nullptr, *tile_hist = nullptr;  // longest tile lists first
     uint4 *wstats = nullptr;  // per-wave work counts of the blend kernels
     size_t wstats_cap = 0;
-    const uint32_t *tile_sorted = nullptr;  // the longest-first order (one of tile_order / tile_v2)
     float *T_final = nullptr;
     uint32_t *n_last = nullptr, *n_blend = nullptr;
     double *sgrad = nullptr;     // [visible rank][12] screen-space gradients
@@ -409,11 +407,7 @@ hgs_status ensure_fixed(hgs_ctx *ctx, int nv, uint32_t n_tiles, size_t n_pix)
     }
     if (n_tiles > ctx->tile_cap) {
         if ((s = realloc_buf(ctx, ctx->ranges, n_tiles))) return s;
-        if ((s = realloc_buf(ctx, ctx->tile_keys, n_tiles))) return s;
         if ((s = realloc_buf(ctx, ctx->tile_order, n_tiles))) return s;
-        if ((s = realloc_buf(ctx, ctx->tile_k2, n_tiles))) return s;
-        if ((s = realloc_buf(ctx, ctx->tile_v2, n_tiles))) return s;
-        if (!ctx->tile_n && (s = realloc_buf(ctx, ctx->tile_n, 4))) return s;
         ctx->tile_cap = n_tiles;
         ctx->layout_gen++;
     }
@@ -493,7 +487,7 @@ int bits_for(uint32_t n)
 void enqueue_blend(hgs_ctx *ctx, int nv, uint32_t n_tiles, hipStream_t st)
 {
     const uint32_t *vals = ctx->pairs_in_scratch ? ctx->v2 : ctx->pvals;
-    launch_blend(ctx->views_dev, nv, n_tiles, ctx->tile_sorted, ctx->ranges, vals, ctx->recs, ctx->axes, ctx->T_final,
+    launch_blend(ctx->views_dev, nv, n_tiles, ctx->tile_order, ctx->ranges, vals, ctx->recs, ctx->axes, ctx->T_final,
                  ctx->n_last, ctx->n_blend, ctx->qbits, ctx->pair_cap, ctx->wstats, ctx->ctr, ctx->tile_w,
                  ctx->tile_h, ctx->batch, ctx->persist, ctx->queue, st);
 }
@@ -506,14 +500,12 @@ void enqueue_forward(hgs_ctx *ctx, int nv, uint32_t n_tiles, hipStream_t st, hip
         if (ev) (void)hipEventRecord(ev[i], st);
     };
     mark(0);
-    launch_fill_u32((uint32_t *)ctx->ctr, 0u, sizeof(Counters) / 4, st);
+    launch_init(ctx->ctr, ctx->tile_hist, ctx->ranges, n_tiles, st);
     launch_cut_flags(h, ctx->views_dev, nv, ctx->masks, ctx->blk_counts, nb, st);
-    launch_scan(ctx->blk_counts, nullptr, (uint32_t)(nb * nv), nullptr, ctx->blk_offsets, &ctx->ctr->cut_total,
-                ctx->partial, st);
+    launch_scan(ctx->blk_counts, (uint32_t)(nb * nv), nullptr, ctx->blk_offsets, &ctx->ctr->cut_total, ctx->partial,
+                st);
     launch_cut_emit(h, ctx->views_dev, nv, ctx->masks, ctx->blk_offsets, nb, ctx->word_off, ctx->cut_ids, nullptr,
-                    ctx->cut_t,
-                    ctx->cut_cap, st);
-    launch_cut_finish(ctx->blk_offsets, ctx->blk_counts, nb, nv, ctx->cut_base, ctx->ctr, st);
+                    ctx->cut_t, ctx->cut_cap, ctx->cut_base, &ctx->ctr->cut_total, st);
     if (ctx->streaming)  // the cut's nodes and parents made resident in the cache
         launch_stream_frame(ctx->sd, ctx->pinfo, ctx->cut_ids, &ctx->ctr->cut_total, ctx->cut_cap,
                             ctx->host_params_dev, ctx->cache_params, st);
@@ -524,24 +516,22 @@ void enqueue_forward(hgs_ctx *ctx, int nv, uint32_t n_tiles, hipStream_t st, hip
                       ctx->vis_counts, ctx->tile_w, ctx->tile_h, st);
     mark(2);
     const uint32_t vblocks = (ctx->cut_cap + 255) / 256;
-    launch_scan(ctx->vis_counts, nullptr, vblocks, nullptr, ctx->vis_offsets, &ctx->ctr->vis_total, ctx->partial, st);
+    launch_scan(ctx->vis_counts, vblocks, nullptr, ctx->vis_offsets, &ctx->ctr->vis_total, ctx->partial, st);
     launch_compact_visible(ctx->vis_mask, ctx->vis_offsets, &ctx->ctr->cut_total, ctx->cut_cap, ctx->depth_key,
                            ctx->skeys, ctx->svals, ctx->vis_rank, ctx->vis_entry, st);
     // the visible splats keep the cut's view-major order: each view's run is
     // sorted by depth on its own (4 passes, in place), so that its pairs are
     // emitted as one run, which the tile sort then orders by the view's own
     // tile id (16 bits or fewer: 2 passes)
-    SortScratch sc{ctx->k2, ctx->v2, ctx->hist, ctx->hist_scan, ctx->partial, ctx->scan_total, ctx->sort_plan};
-    launch_vis_bounds(ctx->cut_base, nv, ctx->vis_mask, ctx->vis_offsets, &ctx->ctr->cut_total, ctx->cut_cap,
-                      &ctx->ctr->vis_total, ctx->vis_bounds, st);
-    launch_radix_sort(ctx->skeys, ctx->svals, ctx->cut_cap, &ctx->ctr->vis_total, 32, sc, st, ctx->vis_bounds, nv);
+    const SortScratch sc{ctx->k2, ctx->v2, ctx->hist, ctx->sort_tot, ctx->sort_plan};
+    launch_plan_depth(ctx->cut_base, nv, ctx->vis_mask, ctx->vis_offsets, &ctx->ctr->cut_total, ctx->cut_cap,
+                      &ctx->ctr->vis_total, ctx->vis_bounds, sc, st);
+    launch_radix_sort(ctx->skeys, ctx->svals, ctx->cut_cap, nv, 32, sc, st);
     mark(3);
     launch_gather_tiles(ctx->trec, ctx->svals, &ctx->ctr->vis_total, ctx->cut_cap, ctx->pair_offsets, ctx->rect,
                         ctx->jrank, st);
-    launch_scan(ctx->pair_offsets, nullptr, ctx->cut_cap, &ctx->ctr->vis_total, ctx->pair_offsets,
-                &ctx->ctr->pair_total, ctx->partial, st);  // in place
-    launch_pair_bounds(ctx->vis_bounds, ctx->views_dev, nv, ctx->pair_offsets, &ctx->ctr->vis_total, ctx->cut_cap,
-                       &ctx->ctr->pair_total, ctx->pair_cap, ctx->pair_bounds, ctx->seg_tile_base, st);
+    launch_scan_pairs(ctx->pair_offsets, ctx->cut_cap, &ctx->ctr->vis_total, &ctx->ctr->pair_total, ctx->partial,
+                      kDupPairs, ctx->pair_cap, ctx->dup_first, st);
     launch_duplicate(ctx->rect, ctx->views_dev, nv, ctx->cut_base, ctx->svals, ctx->pair_offsets, ctx->dup_first,
                      &ctx->ctr->vis_total, ctx->cut_cap, &ctx->ctr->pair_total, ctx->pair_cap, ctx->pkeys,
                      ctx->pvals, ctx->ctr, st);
@@ -549,22 +539,14 @@ void enqueue_forward(hgs_ctx *ctx, int nv, uint32_t n_tiles, hipStream_t st, hip
     uint32_t view_tiles = 1;  // tiles of the largest view
     for (int v = 0; v < nv; ++v)
         view_tiles = std::max(view_tiles, (uint32_t)(ctx->views_host[v].tiles_x * ctx->views_host[v].tiles_y));
-    ctx->pairs_in_scratch = launch_radix_sort(ctx->pkeys, ctx->pvals, ctx->pair_cap, &ctx->ctr->pair_total,
-                                              bits_for(view_tiles), sc, st, ctx->pair_bounds, nv, ctx->seg_tile_base);
+    const int tile_bits = bits_for(view_tiles);
+    launch_plan_pairs(ctx->vis_bounds, ctx->views_dev, nv, ctx->pair_offsets, &ctx->ctr->vis_total, ctx->cut_cap,
+                      &ctx->ctr->pair_total, ctx->pair_cap, tile_bits, sc, st);
+    ctx->pairs_in_scratch = launch_radix_sort(ctx->pkeys, ctx->pvals, ctx->pair_cap, nv, tile_bits, sc, st);
     mark(5);
     const uint32_t *keys = ctx->pairs_in_scratch ? ctx->k2 : ctx->pkeys;
-    const uint32_t *vals = ctx->pairs_in_scratch ? ctx->v2 : ctx->pvals;
-    launch_fill_u32((uint32_t *)ctx->ranges, 0u, (size_t)n_tiles * 2, st);
     launch_ranges(keys, &ctx->ctr->pair_total, ctx->pair_cap, ctx->ranges, st);
-    // longest tile lists first (one stable 8-bit pass over log-scaled lengths)
-    launch_tile_keys(ctx->ranges, n_tiles, ctx->tile_keys, ctx->tile_order, ctx->tile_n, st);
-    {
-        SortScratch ts{ctx->tile_k2, ctx->tile_v2, ctx->hist, ctx->hist_scan, ctx->partial, ctx->scan_total,
-                       ctx->sort_plan};
-        const bool in_scratch = launch_radix_sort(ctx->tile_keys, ctx->tile_order, n_tiles, ctx->tile_n, 8, ts, st);
-        ctx->tile_sorted = in_scratch ? ctx->tile_v2 : ctx->tile_order;
-    }
-    (void)vals;
+    launch_tile_order(ctx->ranges, n_tiles, ctx->tile_hist, ctx->tile_order, st);
     mark(6);
     if (with_blend) {
         KernelTimer kt(ctx, 0, st);
@@ -631,7 +613,7 @@ void enqueue_backward(hgs_ctx *ctx, int nv, const hgs_grads *out, const AdamRows
     {
         KernelTimer kt(ctx, 1, st);
         const DetArgs da{ctx->jrank, ctx->pair_offsets, ctx->rect, ctx->part};
-        launch_blend_backward(ctx->views_dev, nv, ctx->last_tiles, ctx->tile_sorted, ctx->ranges, vals, ctx->recs,
+        launch_blend_backward(ctx->views_dev, nv, ctx->last_tiles, ctx->tile_order, ctx->ranges, vals, ctx->recs,
                               ctx->axes, ctx->T_final, ctx->n_last, ctx->qbits, ctx->pair_cap, ctx->vis_rank,
                               ctx->sgrad, det ? &da : nullptr, ctx->wstats, ctx->ctr, ctx->r_tw, ctx->r_th,
                               ctx->r_batch, out && out->dt != nullptr, ctx->r_persist, ctx->queue + 1, st);
@@ -741,13 +723,12 @@ hgs_status hgs_create(hgs_ctx **out, int device, void *hip_stream)
         if ((s = dalloc(ctx, (void **)&ctx->views_dev, sizeof(DevView) * kMaxViews))) break;
         if ((s = dalloc(ctx, (void **)&ctx->ctr, sizeof(Counters)))) break;
         if ((s = dalloc(ctx, (void **)&ctx->hist, sizeof(uint32_t) * 256 * kSortBlocksMax))) break;
-        if ((s = dalloc(ctx, (void **)&ctx->hist_scan, sizeof(uint32_t) * 256 * kSortBlocksMax))) break;
         if ((s = dalloc(ctx, (void **)&ctx->partial, sizeof(uint32_t) * kScanBlocks))) break;
-        if ((s = dalloc(ctx, (void **)&ctx->scan_total, sizeof(uint32_t) * 4))) break;
-        if ((s = dalloc(ctx, (void **)&ctx->sort_plan, sizeof(SortBlock) * kSortBlocksMax))) break;
+        if ((s = dalloc(ctx, (void **)&ctx->sort_tot, sizeof(uint32_t) * sort_totals(32, kMaxViews)))) break;
+        if ((s = dalloc(ctx, (void **)&ctx->sort_plan.seg, sizeof(SortSeg) * kMaxViews))) break;
+        if ((s = dalloc(ctx, (void **)&ctx->sort_plan.first, sizeof(uint32_t) * (kMaxViews + 1)))) break;
         if ((s = dalloc(ctx, (void **)&ctx->vis_bounds, sizeof(uint32_t) * (kMaxViews + 1)))) break;
-        if ((s = dalloc(ctx, (void **)&ctx->pair_bounds, sizeof(uint32_t) * (kMaxViews + 1)))) break;
-        if ((s = dalloc(ctx, (void **)&ctx->seg_tile_base, sizeof(uint32_t) * kMaxViews))) break;
+        if ((s = dalloc(ctx, (void **)&ctx->tile_hist, sizeof(uint32_t) * 2 * kTileBins))) break;
         if ((s = dalloc(ctx, (void **)&ctx->queue, sizeof(uint32_t) * 2))) break;
         if ((s = dalloc(ctx, (void **)&ctx->l1_partial, sizeof(double) * kL1Blocks))) break;
         if ((s = dalloc(ctx, (void **)&ctx->adam_sc, sizeof(AdamScalars) * 5))) break;
@@ -1061,13 +1042,15 @@ hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *L, int src_on_device, 
     HIPC(hipMemcpyAsync(ndev, &nn, 4, hipMemcpyHostToDevice, st));
     launch_build_morton(in[0], n, lo, scale, lo0, hi0, valA, st);
     HIPC(hipMemcpyAsync(keyA, lo0, 4 * (size_t)n, hipMemcpyDeviceToDevice, st));
-    const SortScratch sc1{tk, tv, ctx->hist, ctx->hist_scan, ctx->partial, ctx->scan_total, ctx->sort_plan};
-    const bool sw1 = launch_radix_sort(keyA, valA, nn, ndev, 32, sc1, st);
+    const SortScratch sc1{tk, tv, ctx->hist, ctx->sort_tot, ctx->sort_plan};
+    launch_plan_whole(nn, ndev, 32, sc1, st);
+    const bool sw1 = launch_radix_sort(keyA, valA, nn, 1, 32, sc1, st);
     uint32_t *idx1 = sw1 ? tv : valA;
     uint32_t *spare = sw1 ? valA : tv;  // the values buffer the first pass left free
     launch_gather_u32(hi0, idx1, n, keyB, st);
-    const SortScratch sc2{tk, spare, ctx->hist, ctx->hist_scan, ctx->partial, ctx->scan_total, ctx->sort_plan};
-    const bool sw2 = launch_radix_sort(keyB, idx1, nn, ndev, 31, sc2, st);
+    const SortScratch sc2{tk, spare, ctx->hist, ctx->sort_tot, ctx->sort_plan};
+    launch_plan_whole(nn, ndev, 31, sc2, st);
+    const bool sw2 = launch_radix_sort(keyB, idx1, nn, 1, 31, sc2, st);
     uint32_t *idx2 = sw2 ? spare : idx1;  // leaves in (code, index) order
     uint32_t *slo = keyA, *shi = tk;       // their codes (both buffers are free again)
     launch_gather_u32(lo0, idx2, n, slo, st);
@@ -1116,7 +1099,7 @@ hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *L, int src_on_device, 
     for (int level = 1;; ++level) {
         if (level > 4096) return fail(ctx, HGS_ERR_INVALID_ARG, "hierarchy deeper than 4096 levels");
         launch_level_starts(node_of, sl, t, n, level, flag, st);
-        launch_scan(flag, nullptr, nn, nullptr, rank, cnt, ctx->partial, st);
+        launch_scan(flag, nn, nullptr, rank, cnt, ctx->partial, st);
         uint32_t c = 0;
         HIPC(hipMemcpyAsync(&c, cnt, 4, hipMemcpyDeviceToHost, st));
         HIPC(hipStreamSynchronize(st));
@@ -1138,7 +1121,7 @@ hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *L, int src_on_device, 
         uint32_t *ifl = nullptr;
         if ((s = talloc((void **)&ifl, 4 * (size_t)N))) return s;
         launch_interior_ranks(t.child_count, N, ifl, st);
-        launch_scan(ifl, nullptr, (uint32_t)N, nullptr, irank, cnt, ctx->partial, st);
+        launch_scan(ifl, (uint32_t)N, nullptr, irank, cnt, ctx->partial, st);
     }
     uint32_t n_int = 0;
     HIPC(hipMemcpyAsync(&n_int, cnt, 4, hipMemcpyDeviceToHost, st));
@@ -1290,7 +1273,7 @@ hgs_status hgs_cut(hgs_ctx *ctx, const hgs_view *view, int32_t *out_ids, float *
     const int nb = cut_blocks(ctx->n);
     launch_fill_u32((uint32_t *)ctx->ctr, 0u, sizeof(Counters) / 4, st);
     launch_cut_flags(h, ctx->views_dev, 1, ctx->masks, ctx->blk_counts, nb, st);
-    launch_scan(ctx->blk_counts, nullptr, (uint32_t)nb, nullptr, ctx->blk_offsets, &ctx->ctr->cut_total, ctx->partial,
+    launch_scan(ctx->blk_counts, (uint32_t)nb, nullptr, ctx->blk_offsets, &ctx->ctr->cut_total, ctx->partial,
                 st);
     HIPC(hipGetLastError());
     HIPC(hipMemcpyAsync(ctx->ctr_host, ctx->ctr, sizeof(Counters), hipMemcpyDeviceToHost, st));
@@ -1301,7 +1284,7 @@ hgs_status hgs_cut(hgs_ctx *ctx, const hgs_view *view, int32_t *out_ids, float *
                                                std::to_string(capacity));
     if (*out_count > 0)
         launch_cut_emit(h, ctx->views_dev, 1, ctx->masks, ctx->blk_offsets, nb, ctx->word_off, out_ids, out_t, nullptr,
-                        (uint32_t)capacity, st);
+                        (uint32_t)capacity, nullptr, nullptr, st);
     HIPC(hipGetLastError());
     HIPC(hipStreamSynchronize(st));
     return HGS_OK;
@@ -1338,7 +1321,7 @@ hgs_status hgs_cut_noalloc(hgs_ctx *ctx, const hgs_view *view, int32_t *out_ids,
     const int nb = cut_blocks(ctx->n);
     launch_fill_u32((uint32_t *)ctr, 0u, sizeof(Counters) / 4, st);
     launch_cut_flags(h, dview, 1, masks, counts, nb, st);
-    launch_scan(counts, nullptr, (uint32_t)nb, nullptr, offsets, &ctr->cut_total, partial, st);
+    launch_scan(counts, (uint32_t)nb, nullptr, offsets, &ctr->cut_total, partial, st);
     HIPC(hipGetLastError());
     HIPC(hipMemcpyAsync(ctx->ctr_host, ctr, sizeof(Counters), hipMemcpyDeviceToHost, st));
     HIPC(hipStreamSynchronize(st));
@@ -1347,7 +1330,8 @@ hgs_status hgs_cut_noalloc(hgs_ctx *ctx, const hgs_view *view, int32_t *out_ids,
         return fail(ctx, HGS_ERR_CAPACITY, "cut has " + std::to_string(*out_count) + " nodes, capacity " +
                                                std::to_string(capacity));
     if (*out_count > 0)
-        launch_cut_emit(h, dview, 1, masks, offsets, nb, word_off, out_ids, out_t, nullptr, (uint32_t)capacity, st);
+        launch_cut_emit(h, dview, 1, masks, offsets, nb, word_off, out_ids, out_t, nullptr, (uint32_t)capacity,
+                        nullptr, nullptr, st);
     HIPC(hipGetLastError());
     HIPC(hipStreamSynchronize(st));
     return HGS_OK;

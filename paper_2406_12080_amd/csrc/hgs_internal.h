@@ -132,44 +132,101 @@ void launch_compact_keep(const DevHier &h, const double *emax, double tau_min, i
 void launch_cut_flags(const DevHier &h, const DevView *views, int nv, uint64_t *masks, uint32_t *block_counts,
                       int nblocks, hipStream_t st);
 // Also writes word_off[v][w]: the cut position of the first selected node of
-// mask word w of view v (words holding a selected node only).
+// mask word w of view v (words holding a selected node only), and, when
+// cut_base is given, cut_base[v] = the cut position of view v's first
+// selected node (cut_base[nv] = *cut_total).
 void launch_cut_emit(const DevHier &h, const DevView *views, int nv, const uint64_t *masks,
                      const uint32_t *block_offsets, int nblocks, uint32_t *word_off, int32_t *out_ids, float *out_t,
-                     double *out_t64, uint32_t cap, hipStream_t st);
-void launch_cut_finish(const uint32_t *block_offsets, const uint32_t *block_counts, int nblocks, int nv,
-                       uint32_t *cut_base, Counters *ctr, hipStream_t st);
+                     double *out_t64, uint32_t cap, uint32_t *cut_base, const uint32_t *cut_total, hipStream_t st);
 
-// exclusive scan of uint32 (optionally of in[idx[i]], gathered once into
-// out); writes *total
-void launch_scan(const uint32_t *in, const uint32_t *idx, uint32_t n_host, const uint32_t *n_dev, uint32_t *out,
-                 uint32_t *total, uint32_t *partial, hipStream_t st);
+// exclusive scan of uint32; writes *total.  n: min(n_host, *n_dev when given).
+// Up to kScanSmall host-side elements in one launch, else two.
+void launch_scan(const uint32_t *in, uint32_t n_host, const uint32_t *n_dev, uint32_t *out, uint32_t *total,
+                 uint32_t *partial, hipStream_t st);
+// The same over the visible splats' tile counts, in place, also noting in
+// block_first[b] the splat that holds pair b * pairs_per_block of the list
+// the offsets describe, for every block that starts below
+// min(total, pair_cap).
+void launch_scan_pairs(uint32_t *counts, uint32_t n_host, const uint32_t *n_dev, uint32_t *total, uint32_t *partial,
+                       uint32_t pairs_per_block, uint32_t pair_cap, uint32_t *block_first, hipStream_t st);
 constexpr int kScanBlocks = 512;
+constexpr uint32_t kScanSmall = 16384;
 
-// stable LSD radix sort of (uint32 key, uint32 value) over bit range [0, bits)
-struct SortBlock {  // work of one block of a segmented sort
-    uint32_t b0, b1;    // its elements [b0, b1)
-    uint32_t hbase;     // histogram slot of digit 0; digit d at hbase + d * hstride
-    uint32_t hstride;   // 0: the block has no work
-    uint32_t kbase;     // subtracted from every key of its segment before the digits are taken
+// stable LSD radix sort of (uint32 key, uint32 value) over bit range [0,
+// bits), in one or more segments (nseg <= kMaxViews) that are each sorted on
+// their own and stay in place, on the digits of key - kbase of the segment
+struct SortSeg {
+    uint32_t lo, hi;  // elements [lo, hi)
+    uint32_t chunk;   // elements per block
+    uint32_t nb;      // blocks (0: the segment is empty)
+    uint32_t kbase;   // subtracted from every key before the digits are taken
     uint32_t pad[3];
 };
+struct SortPlan {
+    SortSeg *seg;     // [nseg]
+    uint32_t *first;  // [nseg + 1]: first block of each segment; [nseg] the blocks used
+};
 struct SortScratch {
-    uint32_t *k2, *v2;   // ping-pong buffers (capacity elements)
-    uint32_t *hist;      // 256 * kSortBlocksMax
-    uint32_t *hist_scan; // 256 * kSortBlocksMax
-    uint32_t *partial;   // kScanBlocks
-    uint32_t *total;     // 2: scan total, histogram length of a segmented sort
-    SortBlock *plan;     // kSortBlocksMax
+    uint32_t *k2, *v2;  // ping-pong buffers (capacity elements)
+    uint32_t *hist;     // 256 * kSortBlocksMax
+    uint32_t *tot;      // per pass and segment the 256 digit totals: sort_totals(32, kMaxViews)
+    SortPlan plan;      // kMaxViews segments
 };
 constexpr int kSortBlocksMax = 4096;
-// Returns true when the sorted result is in (s.k2, s.v2) (odd pass count).
-// With seg_bounds (device, nseg + 1 positions, ascending; nseg <= kMaxViews)
-// every segment [seg_bounds[i], seg_bounds[i + 1]) is sorted on its own and
-// stays in place, on the digits of key - seg_kbase[i] (seg_kbase may be NULL
-// for zero).
-bool launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t cap, const uint32_t *n_dev, int bits,
-                       const SortScratch &s, hipStream_t st, const uint32_t *seg_bounds = nullptr, int nseg = 0,
-                       const uint32_t *seg_kbase = nullptr);
+constexpr uint32_t kSortTile = 4096;  // keys a block ranks at a time
+int sort_grid(uint32_t cap, int nseg);            // blocks of a sort over at most cap elements
+uint32_t sort_totals(int bits, int nseg);         // digit totals a sort's plan clears
+
+// The plan of a sort over G blocks, made by one block of kMaxViews threads:
+// thread i < nseg gives its segment [lo, hi) (ascending, clamped by the
+// caller) and key base; n = all elements.  Every segment gets
+// ceil(size / chunk) blocks, the chunk chosen (a multiple of kSortTile) so
+// that all segments' blocks fit in G.  Also clears the ntot digit totals.
+__device__ __forceinline__ void sort_plan_block(uint32_t lo, uint32_t hi, uint32_t kbase, uint32_t n, int nseg, int G,
+                                                const SortPlan &plan, uint32_t *tot, uint32_t ntot)
+{
+    __shared__ uint32_t s_w[kMaxViews / 64];
+    const int i = threadIdx.x, lane = i & 63, w = i >> 6;
+    for (uint32_t k = (uint32_t)i; k < ntot; k += kMaxViews) tot[k] = 0u;
+    const uint32_t per = max(1u, (n + (uint32_t)(G - nseg) - 1) / (uint32_t)(G - nseg));
+    const uint32_t chunk = (per + kSortTile - 1) / kSortTile * kSortTile;
+    const uint32_t size = i < nseg ? hi - lo : 0u;
+    const uint32_t nb = (size + chunk - 1) / chunk;
+    uint32_t inc = nb;  // exclusive scan of the block counts over the segments
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += y;
+    }
+    if (lane == 63) s_w[w] = inc;
+    __syncthreads();
+    uint32_t first = inc - nb, used = 0;
+    for (int k = 0; k < kMaxViews / 64; ++k) {
+        first += k < w ? s_w[k] : 0u;
+        used += s_w[k];
+    }
+    if (used > (uint32_t)G) used = 0;  // cannot happen for ascending segments; never work past the grid
+    if (i < nseg) {
+        SortSeg s;
+        s.lo = lo;
+        s.hi = hi;
+        s.chunk = chunk;
+        s.nb = used ? nb : 0u;
+        s.kbase = kbase;
+        s.pad[0] = s.pad[1] = s.pad[2] = 0u;
+        plan.seg[i] = s;
+        plan.first[i] = used ? first : 0u;
+    }
+    if (i == 0) plan.first[nseg] = used;
+}
+
+// A plan of one segment [0, min(cap, *n_dev)); the sorts of the render path
+// make theirs with launch_plan_depth and launch_plan_pairs.
+void launch_plan_whole(uint32_t cap, const uint32_t *n_dev, int bits, const SortScratch &s, hipStream_t st);
+// Sorts by the plan in s.  Returns true when the sorted result is in
+// (s.k2, s.v2) (odd pass count).
+bool launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t cap, int nseg, int bits, const SortScratch &s,
+                       hipStream_t st);
 
 // preprocess: interpolation, EWA projection, SH colour, footprint, per cut entry
 void launch_preprocess(const DevHier &h, const DevView *views, int nv, const uint32_t *cut_base,
@@ -188,29 +245,36 @@ void launch_compact_visible(const uint64_t *vis_mask, const uint32_t *vis_block_
 // tile count, unused; written for visible entries).
 void launch_gather_tiles(const uint4 *trec, const uint32_t *sorted_vals, const uint32_t *vis_total, uint32_t vis_cap,
                          uint32_t *counts, uint2 *rect, uint32_t *jrank, hipStream_t st);
-// Per view: the depth-order slot of its first visible splat (vis_bounds,
-// nv + 1 entries, the last = visible total).
-void launch_vis_bounds(const uint32_t *cut_base, int nv, const uint64_t *vis_mask, const uint32_t *vis_offsets,
-                       const uint32_t *cut_total, uint32_t cap, const uint32_t *vis_total, uint32_t *bounds,
-                       hipStream_t st);
-// Per view: the position of its first (tile, splat) pair (nv + 1 entries,
-// the last = pair total) and its first global tile id.
-void launch_pair_bounds(const uint32_t *vis_bounds, const DevView *views, int nv, const uint32_t *pair_offsets,
-                        const uint32_t *vis_total, uint32_t vis_cap, const uint32_t *pair_total, uint32_t pair_cap,
-                        uint32_t *bounds, uint32_t *tile_base, hipStream_t st);
-// block_first: duplicate_blocks(pair_cap) + 1 entries of workspace.  rect:
-// tile rectangles in depth order (launch_gather_tiles).
+// The plan of the depth sort: one segment per view, which starts at the
+// view's first visible splat (noted in vis_bounds, nv + 1 entries, the last
+// = visible total).
+void launch_plan_depth(const uint32_t *cut_base, int nv, const uint64_t *vis_mask, const uint32_t *vis_offsets,
+                       const uint32_t *cut_total, uint32_t cap, const uint32_t *vis_total, uint32_t *vis_bounds,
+                       const SortScratch &s, hipStream_t st);
+// The plan of the tile sort: one segment per view, which starts at its first
+// (tile, splat) pair; keys count from the view's first global tile id.
+void launch_plan_pairs(const uint32_t *vis_bounds, const DevView *views, int nv, const uint32_t *pair_offsets,
+                       const uint32_t *vis_total, uint32_t vis_cap, const uint32_t *pair_total, uint32_t pair_cap,
+                       int bits, const SortScratch &s, hipStream_t st);
+// rect: tile rectangles in depth order (launch_gather_tiles); block_first:
+// the splat holding each emission block's first pair (launch_scan_pairs with
+// kDupPairs pairs per block; duplicate_blocks(pair_cap) + 1 entries).
+constexpr uint32_t kDupPairs = 2048;
 void launch_duplicate(const uint2 *rect, const DevView *views, int nv, const uint32_t *cut_base,
-                      const uint32_t *sorted_vals, const uint32_t *pair_offsets, uint32_t *block_first,
+                      const uint32_t *sorted_vals, const uint32_t *pair_offsets, const uint32_t *block_first,
                       const uint32_t *vis_total, uint32_t vis_cap, const uint32_t *pair_total, uint32_t pair_cap,
                       uint32_t *pair_keys, uint32_t *pair_vals, Counters *ctr, hipStream_t st);
 uint32_t duplicate_blocks(uint32_t pair_cap);
 void launch_ranges(const uint32_t *pair_keys, const uint32_t *pair_total, uint32_t pair_cap, uint2 *ranges,
                    hipStream_t st);
 void launch_fill_u32(uint32_t *p, uint32_t value, size_t n, hipStream_t st);
-// tiles ordered by descending list length (longest first) for the blend grid
-void launch_tile_keys(const uint2 *ranges, uint32_t n_tiles, uint32_t *keys, uint32_t *order, uint32_t *n_out,
-                      hipStream_t st);
+// Clears the counters, the tile-length histogram and the tile ranges.
+void launch_init(Counters *ctr, uint32_t *tile_hist, uint2 *ranges, uint32_t n_tiles, hipStream_t st);
+// Tiles ordered by descending list length (longest first, in steps of an
+// eighth of a power of two; any order within a step) for the blend grid.
+// tile_hist: 2 kTileBins cleared counters (bin counts, slots taken).
+constexpr int kTileBins = 256;
+void launch_tile_order(const uint2 *ranges, uint32_t n_tiles, uint32_t *tile_hist, uint32_t *order, hipStream_t st);
 
 // blend (tile_w x tile_h pixels per workgroup, `batch` records staged per step)
 bool blend_supported(int tw, int th, int batch);

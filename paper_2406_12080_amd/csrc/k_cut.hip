@@ -207,7 +207,9 @@ __global__ __launch_bounds__(kCutThreads) void k_cut_emit(DevHier h, const DevVi
                                                           const uint32_t *__restrict__ block_offsets, int nblocks,
                                                           uint32_t *__restrict__ word_off,
                                                           int32_t *__restrict__ out_ids, float *__restrict__ out_t,
-                                                          double *__restrict__ out_t64, uint32_t cap)
+                                                          double *__restrict__ out_t64, uint32_t cap,
+                                                          uint32_t *__restrict__ cut_base,
+                                                          const uint32_t *__restrict__ cut_total)
 {
     constexpr int W = kCutBlock / 64;  // mask words per block and view
     constexpr int VB = kEmitViews;
@@ -219,6 +221,11 @@ __global__ __launch_bounds__(kCutThreads) void k_cut_emit(DevHier h, const DevVi
     const int64_t words = (n + 63) >> 6;
     const int v0 = blockIdx.y * VB, nvb = min(VB, nv - v0);
     const int64_t w0 = (int64_t)blockIdx.x * W;
+    if (blockIdx.x == 0 && cut_base) {
+        if (threadIdx.x < (uint32_t)nvb)
+            cut_base[v0 + threadIdx.x] = block_offsets[(int64_t)(v0 + threadIdx.x) * nblocks];
+        if (threadIdx.x == 0 && v0 + nvb == nv) cut_base[nv] = *cut_total;
+    }
     if (threadIdx.x < VB * W) {
         const int u = threadIdx.x / W, k = threadIdx.x % W;
         const int64_t w = w0 + k;
@@ -272,14 +279,6 @@ __global__ __launch_bounds__(kCutThreads) void k_cut_emit(DevHier h, const DevVi
             if (out_t64) out_t64[pos] = t;
         }
     }
-}
-
-__global__ void k_cut_finish(const uint32_t *__restrict__ block_offsets, int nblocks, int nv,
-                             uint32_t *__restrict__ cut_base, const uint32_t *__restrict__ total)
-{
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < nv) cut_base[v] = block_offsets[(int64_t)v * nblocks];
-    if (v == nv) cut_base[nv] = *total;
 }
 
 // Hierarchy compaction (Sec. 5.2, "Compacting the Hierarchy").  For a set
@@ -391,17 +390,11 @@ void launch_cut_flags(const DevHier &h, const DevView *views, int nv, uint64_t *
 
 void launch_cut_emit(const DevHier &h, const DevView *views, int nv, const uint64_t *masks,
                      const uint32_t *block_offsets, int nblocks, uint32_t *word_off, int32_t *out_ids, float *out_t,
-                     double *out_t64, uint32_t cap, hipStream_t st)
+                     double *out_t64, uint32_t cap, uint32_t *cut_base, const uint32_t *cut_total, hipStream_t st)
 {
     hipLaunchKernelGGL(k_cut_emit, dim3(nblocks, (nv + kEmitViews - 1) / kEmitViews), dim3(kCutThreads), 0, st, h,
-                       views, nv, masks, block_offsets, nblocks, word_off, out_ids, out_t, out_t64, cap);
-}
-
-void launch_cut_finish(const uint32_t *block_offsets, const uint32_t *, int nblocks, int nv, uint32_t *cut_base,
-                       Counters *ctr, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_cut_finish, dim3((nv + 1 + 255) / 256), dim3(256), 0, st, block_offsets, nblocks, nv,
-                       cut_base, &ctr->cut_total);
+                       views, nv, masks, block_offsets, nblocks, word_off, out_ids, out_t, out_t64, cap,
+                       cut_base, cut_total);
 }
 
 }  // namespace hgs

@@ -182,38 +182,60 @@ __global__ __launch_bounds__(kT) void k_compact_visible(const uint64_t *__restri
     }
 }
 
-// Per view, the slot of its first visible splat: visible entries before cut
-// position cut_base[v] (the visible list keeps the cut's view-major order).
-__global__ void k_vis_bounds(const uint32_t *__restrict__ cut_base, int nv, const uint64_t *__restrict__ vis_mask,
-                             const uint32_t *__restrict__ vis_offsets, const uint32_t *__restrict__ cut_total,
-                             uint32_t cap, const uint32_t *__restrict__ vis_total, uint32_t *__restrict__ bounds)
+// The plan of the depth sort: one segment per view.  A view's first visible
+// splat sits behind the visible entries before cut position cut_base[v] (the
+// visible list keeps the cut's view-major order).
+__global__ __launch_bounds__(kMaxViews) void k_plan_depth(const uint32_t *__restrict__ cut_base, int nv,
+                                                          const uint64_t *__restrict__ vis_mask,
+                                                          const uint32_t *__restrict__ vis_offsets,
+                                                          const uint32_t *__restrict__ cut_total, uint32_t cap,
+                                                          const uint32_t *__restrict__ vis_total,
+                                                          uint32_t *__restrict__ bounds, SortPlan plan, int G,
+                                                          uint32_t *__restrict__ tot, uint32_t ntot)
 {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v > nv) return;
-    const uint32_t total = min(*cut_total, cap);
-    const uint32_t k = v < nv ? cut_base[v] : total;
-    if (k >= total) {
-        bounds[v] = min(*vis_total, cap);
-        return;
+    const uint32_t total = min(*cut_total, cap), nvis = min(*vis_total, cap);
+    auto bound = [&](int v) -> uint32_t {
+        const uint32_t k = v < nv ? cut_base[v] : total;
+        if (k >= total) return nvis;
+        uint32_t c = vis_offsets[k / kT];  // visible entries of the preprocess blocks before k's
+        for (uint32_t w = (k / kT) * (kT / 64); w < (k >> 6); ++w) c += (uint32_t)__popcll(vis_mask[w]);
+        if (k & 63u) c += (uint32_t)__popcll(vis_mask[k >> 6] & ((1ull << (k & 63u)) - 1ull));
+        return min(c, nvis);
+    };
+    const int v = threadIdx.x;
+    uint32_t lo = 0, hi = 0;
+    if (v < nv) {
+        lo = bound(v);
+        hi = bound(v + 1);
+        bounds[v] = lo;
     }
-    uint32_t c = vis_offsets[k / kT];  // visible entries of the preprocess blocks before k's
-    for (uint32_t w = (k / kT) * (kT / 64); w < (k >> 6); ++w) c += (uint32_t)__popcll(vis_mask[w]);
-    if (k & 63u) c += (uint32_t)__popcll(vis_mask[k >> 6] & ((1ull << (k & 63u)) - 1ull));
-    bounds[v] = c;
+    if (v == 0) bounds[nv] = nvis;
+    sort_plan_block(lo, hi, 0u, nvis, nv, G, plan, tot, ntot);
 }
 
-// Per view, the position of its first pair and its first global tile id.
-__global__ void k_pair_bounds(const uint32_t *__restrict__ vis_bounds, const DevView *__restrict__ views, int nv,
-                              const uint32_t *__restrict__ pair_offsets, const uint32_t *__restrict__ vis_total,
-                              uint32_t vis_cap, const uint32_t *__restrict__ pair_total, uint32_t pair_cap,
-                              uint32_t *__restrict__ bounds, uint32_t *__restrict__ tile_base)
+// The plan of the tile sort: one segment per view, its keys counted from the
+// view's first global tile id.
+__global__ __launch_bounds__(kMaxViews) void k_plan_pairs(const uint32_t *__restrict__ vis_bounds,
+                                                          const DevView *__restrict__ views, int nv,
+                                                          const uint32_t *__restrict__ pair_offsets,
+                                                          const uint32_t *__restrict__ vis_total, uint32_t vis_cap,
+                                                          const uint32_t *__restrict__ pair_total, uint32_t pair_cap,
+                                                          SortPlan plan, int G, uint32_t *__restrict__ tot,
+                                                          uint32_t ntot)
 {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v > nv) return;
     const uint32_t nvis = min(*vis_total, vis_cap), npairs = min(*pair_total, pair_cap);
-    const uint32_t j = vis_bounds[v];
-    bounds[v] = j < nvis ? min(pair_offsets[j], npairs) : npairs;
-    if (v < nv) tile_base[v] = views[v].tile_base;
+    auto bound = [&](int v) -> uint32_t {
+        const uint32_t j = vis_bounds[v];
+        return j < nvis ? min(pair_offsets[j], npairs) : npairs;
+    };
+    const int v = threadIdx.x;
+    uint32_t lo = 0, hi = 0, base = 0;
+    if (v < nv) {
+        lo = bound(v);
+        hi = bound(v + 1);
+        base = views[v].tile_base;
+    }
+    sort_plan_block(lo, hi, base, npairs, nv, G, plan, tot, ntot);
 }
 
 // The tile records of the visible splats in depth order: the one random
@@ -269,27 +291,14 @@ __global__ __launch_bounds__(kT) void k_det_sum(const double *__restrict__ part,
 // Pair emission, balanced by pairs: block b writes pairs [b P, (b + 1) P)
 // of the depth-ordered list, whatever the footprints of the splats they come
 // from (the nearest splats of every view sort first and may cover thousands
-// of tiles each).  k_dup_starts records the splat holding each block's first
-// pair; k_duplicate stages the block's slice of the pair offsets in LDS.
+// of tiles each).  The scan of the pair counts noted the splat that holds
+// each block's first pair; the block's slice of the pair offsets is staged
+// in LDS.
 // Each thread writes kDupPer consecutive pairs (one vector store per array
 // and thread, contiguous across the wave): a binary search finds the splat
 // of its first pair, then it walks forward tile by tile.
 constexpr int kDupPer = 8;
-constexpr uint32_t kDupPairs = kT * kDupPer;
-
-__global__ __launch_bounds__(kT) void k_dup_starts(const uint32_t *__restrict__ offsets,
-                                                   const uint32_t *__restrict__ vis_total, uint32_t vis_cap,
-                                                   const uint32_t *__restrict__ pair_total, uint32_t pair_cap,
-                                                   uint32_t *__restrict__ block_first)
-{
-    const uint32_t nvis = min(*vis_total, vis_cap);
-    const uint32_t npairs = min(*pair_total, pair_cap);
-    const uint32_t j = blockIdx.x * kT + threadIdx.x;
-    if (j >= nvis) return;
-    const uint32_t o = offsets[j];
-    const uint32_t e = j + 1 < nvis ? offsets[j + 1] : *pair_total;  // end of splat j's pairs
-    for (uint32_t b = (o + kDupPairs - 1) / kDupPairs; b * kDupPairs < min(e, npairs); ++b) block_first[b] = j;
-}
+static_assert(kDupPairs == (uint32_t)kT * kDupPer, "pairs per emission block");
 
 __global__ __launch_bounds__(kT) void k_duplicate(const uint2 *__restrict__ rect, const DevView *__restrict__ views,
                                                   int nv, const uint32_t *__restrict__ cut_base,
@@ -420,22 +429,87 @@ __global__ __launch_bounds__(kT) void k_ranges(const uint32_t *__restrict__ keys
     }
 }
 
-// Scheduling key of every tile: 255 minus 8 log2(list length + 1), so that
-// a stable ascending sort puts the longest lists first.
-__global__ __launch_bounds__(kT) void k_tile_keys(const uint2 *__restrict__ ranges, uint32_t n_tiles,
-                                                  uint32_t *__restrict__ keys, uint32_t *__restrict__ order,
-                                                  uint32_t *__restrict__ n_out)
+// Scheduling order of the tiles, longest lists first: 256 bins of 255 minus
+// 8 log2(list length + 1), counted (k_tile_bins) and filled (k_tile_place).
+// The order inside a bin is whatever the blocks' reservations give: it only
+// decides which tile a workgroup takes when.  Two launches (8 us for a view
+// of 8160 tiles; a radix pass over the bins took five).
+constexpr int kTilePer = 4;  // tiles per thread
+constexpr int kTileBlock = kT * kTilePer;
+
+__device__ __forceinline__ uint32_t tile_bin(const uint2 r)
 {
-    const uint32_t i = blockIdx.x * kT + threadIdx.x;
-    if (i == 0) *n_out = n_tiles;
-    if (i >= n_tiles) return;
-    const uint2 r = ranges[i];
     const uint32_t len = r.y - r.x + 1u;
-    const uint32_t lg = 31u - (uint32_t)__clz(len);                   // floor(log2)
+    const uint32_t lg = 31u - (uint32_t)__clz(len);  // floor(log2)
     const uint32_t frac = lg >= 3 ? (len >> (lg - 3)) & 7u : (len << (3 - lg)) & 7u;
-    const uint32_t k = min(255u, lg * 8u + frac);
-    keys[i] = 255u - k;
-    order[i] = i;
+    return 255u - min(255u, lg * 8u + frac);
+}
+
+__global__ __launch_bounds__(kT) void k_tile_bins(const uint2 *__restrict__ ranges, uint32_t n_tiles,
+                                                  uint32_t *__restrict__ hist)
+{
+    __shared__ uint32_t s_h[kTileBins];
+    s_h[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kTilePer; ++k) {
+        const uint32_t i = blockIdx.x * kTileBlock + k * kT + threadIdx.x;
+        if (i < n_tiles) atomicAdd(&s_h[tile_bin(ranges[i])], 1u);
+    }
+    __syncthreads();
+    if (s_h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], s_h[threadIdx.x]);
+}
+
+// hist: the bins' counts; next: kTileBins cleared counters of the slots
+// taken in each bin.
+__global__ __launch_bounds__(kT) void k_tile_place(const uint2 *__restrict__ ranges, uint32_t n_tiles,
+                                                   const uint32_t *__restrict__ hist, uint32_t *__restrict__ next,
+                                                   uint32_t *__restrict__ order)
+{
+    static_assert(kTileBins == kT, "one bin per thread");
+    __shared__ uint32_t s_h[kTileBins], s_w[kT / 64];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    s_h[t] = 0;
+    const uint32_t all = hist[t];
+    uint32_t inc = all;  // first slot of bin t: exclusive scan of the counts
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += y;
+    }
+    if (lane == 63) s_w[w] = inc;
+    __syncthreads();
+    uint32_t first = inc - all;
+#pragma unroll
+    for (int k = 0; k < kT / 64; ++k) first += k < w ? s_w[k] : 0u;
+    uint32_t bin[kTilePer], rank[kTilePer];
+#pragma unroll
+    for (int k = 0; k < kTilePer; ++k) {
+        const uint32_t i = blockIdx.x * kTileBlock + k * kT + t;
+        bin[k] = i < n_tiles ? tile_bin(ranges[i]) : ~0u;
+        if (bin[k] != ~0u) rank[k] = atomicAdd(&s_h[bin[k]], 1u);
+    }
+    __syncthreads();
+    const uint32_t c = s_h[t];
+    const uint32_t got = c ? atomicAdd(&next[t], c) : 0u;
+    __syncthreads();
+    s_h[t] = first + got;  // where this block's tiles of the bin go
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kTilePer; ++k)
+        if (bin[k] != ~0u) order[s_h[bin[k]] + rank[k]] = blockIdx.x * kTileBlock + k * kT + t;
+}
+
+// Clears what a render counts into: the counters, the tile-length bins and
+// the tile ranges.
+__global__ __launch_bounds__(kT) void k_init(uint32_t *__restrict__ ctr, uint32_t nctr, uint32_t *__restrict__ bins,
+                                             uint32_t nbins, uint2 *__restrict__ ranges, uint32_t n_tiles)
+{
+    for (uint32_t i = blockIdx.x * kT + threadIdx.x; i < n_tiles; i += gridDim.x * kT) ranges[i] = make_uint2(0u, 0u);
+    if (blockIdx.x == 0) {
+        for (uint32_t i = threadIdx.x; i < nctr; i += kT) ctr[i] = 0u;
+        for (uint32_t i = threadIdx.x; i < nbins; i += kT) bins[i] = 0u;
+    }
 }
 
 __global__ void k_fill_u32(uint32_t *__restrict__ p, uint32_t value, size_t n)
@@ -953,20 +1027,20 @@ void launch_zero_rows(double *rows, int width, const uint32_t *vis_total, uint32
     hipLaunchKernelGGL(k_zero_rows, dim3(blocks), dim3(kT), 0, st, rows, width, vis_total, vis_cap);
 }
 
-void launch_vis_bounds(const uint32_t *cut_base, int nv, const uint64_t *vis_mask, const uint32_t *vis_offsets,
-                       const uint32_t *cut_total, uint32_t cap, const uint32_t *vis_total, uint32_t *bounds,
-                       hipStream_t st)
+void launch_plan_depth(const uint32_t *cut_base, int nv, const uint64_t *vis_mask, const uint32_t *vis_offsets,
+                       const uint32_t *cut_total, uint32_t cap, const uint32_t *vis_total, uint32_t *vis_bounds,
+                       const SortScratch &s, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_vis_bounds, dim3((nv + 1 + 255) / 256), dim3(256), 0, st, cut_base, nv, vis_mask,
-                       vis_offsets, cut_total, cap, vis_total, bounds);
+    hipLaunchKernelGGL(k_plan_depth, dim3(1), dim3(kMaxViews), 0, st, cut_base, nv, vis_mask, vis_offsets, cut_total,
+                       cap, vis_total, vis_bounds, s.plan, sort_grid(cap, nv), s.tot, sort_totals(32, nv));
 }
 
-void launch_pair_bounds(const uint32_t *vis_bounds, const DevView *views, int nv, const uint32_t *pair_offsets,
-                        const uint32_t *vis_total, uint32_t vis_cap, const uint32_t *pair_total, uint32_t pair_cap,
-                        uint32_t *bounds, uint32_t *tile_base, hipStream_t st)
+void launch_plan_pairs(const uint32_t *vis_bounds, const DevView *views, int nv, const uint32_t *pair_offsets,
+                       const uint32_t *vis_total, uint32_t vis_cap, const uint32_t *pair_total, uint32_t pair_cap,
+                       int bits, const SortScratch &s, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_pair_bounds, dim3((nv + 1 + 255) / 256), dim3(256), 0, st, vis_bounds, views, nv,
-                       pair_offsets, vis_total, vis_cap, pair_total, pair_cap, bounds, tile_base);
+    hipLaunchKernelGGL(k_plan_pairs, dim3(1), dim3(kMaxViews), 0, st, vis_bounds, views, nv, pair_offsets, vis_total,
+                       vis_cap, pair_total, pair_cap, s.plan, sort_grid(pair_cap, nv), s.tot, sort_totals(bits, nv));
 }
 
 void launch_gather_tiles(const uint4 *trec, const uint32_t *sorted_vals, const uint32_t *vis_total, uint32_t vis_cap,
@@ -989,15 +1063,12 @@ void launch_det_sum(const double *part, const uint32_t *pair_offsets, const uint
 }
 
 void launch_duplicate(const uint2 *rect, const DevView *views, int nv, const uint32_t *cut_base,
-                      const uint32_t *sorted_vals, const uint32_t *pair_offsets, uint32_t *block_first,
+                      const uint32_t *sorted_vals, const uint32_t *pair_offsets, const uint32_t *block_first,
                       const uint32_t *vis_total, uint32_t vis_cap, const uint32_t *pair_total, uint32_t pair_cap,
                       uint32_t *pair_keys, uint32_t *pair_vals, Counters *ctr, hipStream_t st)
 {
-    const uint32_t sblocks = (vis_cap + kT - 1) / kT;
     const uint32_t dblocks = (pair_cap + kDupPairs - 1) / kDupPairs;
-    if (!sblocks || !dblocks) return;
-    hipLaunchKernelGGL(k_dup_starts, dim3(sblocks), dim3(kT), 0, st, pair_offsets, vis_total, vis_cap, pair_total,
-                       pair_cap, block_first);
+    if (!dblocks) return;
     hipLaunchKernelGGL(k_duplicate, dim3(dblocks), dim3(kT), 0, st, rect, views, nv, cut_base, sorted_vals,
                        pair_offsets, block_first, vis_total, vis_cap, pair_total, pair_cap, pair_keys, pair_vals, ctr);
 }
@@ -1015,12 +1086,20 @@ void launch_ranges(const uint32_t *pair_keys, const uint32_t *pair_total, uint32
     hipLaunchKernelGGL(k_ranges, dim3(blocks), dim3(kT), 0, st, pair_keys, pair_total, pair_cap, ranges);
 }
 
-void launch_tile_keys(const uint2 *ranges, uint32_t n_tiles, uint32_t *keys, uint32_t *order, uint32_t *n_out,
-                      hipStream_t st)
+void launch_init(Counters *ctr, uint32_t *tile_hist, uint2 *ranges, uint32_t n_tiles, hipStream_t st)
+{
+    const uint32_t blocks = std::min<uint32_t>(std::max<uint32_t>((n_tiles + kT - 1) / kT, 1u), 2048u);
+    hipLaunchKernelGGL(k_init, dim3(blocks), dim3(kT), 0, st, (uint32_t *)ctr, (uint32_t)(sizeof(Counters) / 4),
+                       tile_hist, 2u * kTileBins, ranges, n_tiles);
+}
+
+void launch_tile_order(const uint2 *ranges, uint32_t n_tiles, uint32_t *tile_hist, uint32_t *order, hipStream_t st)
 {
     if (!n_tiles) return;
-    hipLaunchKernelGGL(k_tile_keys, dim3((n_tiles + kT - 1) / kT), dim3(kT), 0, st, ranges, n_tiles, keys, order,
-                       n_out);
+    const uint32_t blocks = (n_tiles + kTileBlock - 1) / kTileBlock;
+    hipLaunchKernelGGL(k_tile_bins, dim3(blocks), dim3(kT), 0, st, ranges, n_tiles, tile_hist);
+    hipLaunchKernelGGL(k_tile_place, dim3(blocks), dim3(kT), 0, st, ranges, n_tiles, tile_hist, tile_hist + kTileBins,
+                       order);
 }
 
 void launch_fill_u32(uint32_t *p, uint32_t value, size_t n, hipStream_t st)

@@ -1,20 +1,32 @@
 // Stable LSD radix sort of (uint32 key, uint32 value) pairs, 8-bit digits,
-// LDS-staged.  A fixed grid of G blocks each owns one contiguous chunk of the
-// input (so the element count may be a device value and the launches can be
+// LDS-staged, over one or more segments (one per view), each sorted in place
+// on its own.  A fixed grid of blocks each owns one contiguous chunk of a
+// segment (the element count is a device value, so the launches can be
 // captured in a graph):
-//   hist    : per-block digit histogram -> hist[digit * G + block]
-//   scan    : exclusive scan of hist (digit-major) = first output slot of
-//             every (digit, block)
-//   scatter : each block walks its chunk in tiles of 2048 keys, ranks keys
-//             stably inside the tile (64-lane digit match from 8 ballots,
-//             per-wave running counts in LDS), regroups the tile by digit in
-//             LDS, and writes runs of equal digits contiguously.
+//   plan    : (once per sort) every segment's chunk size, blocks and first
+//             block; the per-pass digit totals cleared
+//   hist    : per-block digit histogram -> hist[segment][digit][block], and
+//             the segment's digit totals
+//   rowscan : one wave per (segment, digit): its first output slot (from the
+//             totals of the lower digits) and the exclusive scan over the
+//             segment's blocks, in place
+//   scatter : each block walks its chunk in tiles, ranks keys stably inside
+//             the tile (64-lane digit match from 8 ballots, per-wave running
+//             counts in LDS), regroups the tile by digit in LDS, and writes
+//             runs of equal digits contiguously.
 // Ranking order inside a tile is (wave, item, lane) = input order, so equal
 // keys keep their input order.
-// Segmented mode (one segment per view): k_seg_plan gives every segment its
-// own blocks, and lays the histogram out as (segment, digit, block), so that
-// the one exclusive scan over it places each segment's output exactly over
-// its input range.
+//
+// Bounds: at 30M-90M elements the scatter is HBM-bound by partial lines (a
+// digit's run in a tile of 4096 keys averages 64 B per array; tiles of 2048
+// moved 1.7x the bytes they wrote): the six passes of 32 views of 1920x1080
+// over 30M leaves (32M splats, 90M pairs) take 1.53 + 0.50 ms (scatter +
+// hist) against 2.04 + 0.81 with 2048-key tiles and a histogram by ballots.
+// Up to a few million elements the launches bound it: three per pass (five
+// with a device-wide scan of the histogram), and the plan is made by
+// segment, not by block (4.7 us; 35-70 us when one thread wrote the entries
+// of all of its segment's blocks).  One 1920x1080 view of 1M leaves: 828 ->
+// 593 us with the one- and two-launch scans (64 -> 38 launches).
 #include <algorithm>
 
 #include "hgs_internal.h"
@@ -23,11 +35,12 @@ namespace hgs {
 
 namespace {
 
-constexpr int kT = 256;
+constexpr int kT = 512;  // threads of the hist and scatter kernels
 constexpr int kWaves = kT / 64;
-constexpr int kItems = 8;
-constexpr int kTile = kT * kItems;
+constexpr int kTile = (int)kSortTile;
+constexpr int kItems = kTile / kT;
 constexpr int kRadix = 256;
+constexpr int kCopies = 16;  // histogram copies: one digit is at most 4-way contended within a wave
 
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
 {
@@ -41,158 +54,144 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
     return m;
 }
 
-__device__ __forceinline__ void chunk_of(uint32_t n, int G, uint32_t &b0, uint32_t &b1)
-{
-    const uint32_t chunk = (n + G - 1) / G;
-    b0 = min(n, blockIdx.x * chunk);
-    b1 = min(n, b0 + chunk);
-}
+// The work of one block of a sort: its element range, and its place in the
+// histogram (digit d of the block at hist[hbase + d * hstride]).
+struct BlockWork {
+    uint32_t b0, b1, hbase, hstride, kbase;
+    int seg;
+};
 
-// The work of this block: its element range, histogram slots and key base
-// (uniform chunks of [0, n) without a plan).  False: no work.
-__device__ __forceinline__ bool block_work(const SortBlock *plan, uint32_t n, int G, uint32_t &b0, uint32_t &b1,
-                                           uint32_t &hbase, uint32_t &hstride, uint32_t &kbase)
+// False: no work for this block.
+__device__ __forceinline__ bool block_work(const SortPlan &p, int nseg, BlockWork &w)
 {
-    if (plan) {
-        const SortBlock p = plan[blockIdx.x];
-        b0 = p.b0;
-        b1 = p.b1;
-        hbase = p.hbase;
-        hstride = p.hstride;
-        kbase = p.kbase;
-        return hstride != 0;
+    const uint32_t b = blockIdx.x;
+    if (b >= p.first[nseg]) return false;
+    int lo = 0, hi = nseg - 1;  // the last segment with first <= b (never an empty one)
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (p.first[mid] <= b) lo = mid;
+        else hi = mid - 1;
     }
-    chunk_of(n, G, b0, b1);
-    hbase = blockIdx.x;
-    hstride = (uint32_t)G;
-    kbase = 0;
+    const SortSeg s = p.seg[lo];
+    const uint32_t f = p.first[lo], j = b - f;
+    w.seg = lo;
+    w.b0 = s.lo + j * s.chunk;
+    w.b1 = min(s.hi, w.b0 + s.chunk);
+    w.hbase = kRadix * f + j;
+    w.hstride = s.nb;
+    w.kbase = s.kbase;
     return true;
 }
 
-// Plan of a segmented sort over G blocks: segment i of [bounds[i],
-// bounds[i + 1]) (clamped to n) gets ceil(size / C) blocks for one chunk size
-// C chosen so that the blocks of all segments fit in G.  One thread per
-// segment; *hist_n receives the histogram length 256 x (blocks used).
-__global__ __launch_bounds__(kMaxViews) void k_seg_plan(const uint32_t *__restrict__ bounds, int nseg,
-                                                        const uint32_t *__restrict__ kbase, uint32_t cap,
-                                                        const uint32_t *__restrict__ n_dev, int G,
-                                                        SortBlock *__restrict__ plan, uint32_t *__restrict__ hist_n)
+__global__ __launch_bounds__(kT) void k_rs_hist(const uint32_t *__restrict__ keys, int shift, SortPlan plan, int nseg,
+                                                uint32_t *__restrict__ hist, uint32_t *__restrict__ tot)
 {
-    __shared__ uint32_t s_w[kMaxViews / 64];
-    const uint32_t n = min(*n_dev, cap);
-    const int i = threadIdx.x;
-    uint32_t lo = 0, hi = 0;
-    if (i < nseg) {
-        lo = min(bounds[i], n);
-        hi = min(max(bounds[i + 1], lo), n);
-    }
-    const uint32_t chunk = max((uint32_t)kTile, (n + (uint32_t)(G - nseg) - 1) / (uint32_t)(G - nseg));
-    const uint32_t nb = (hi - lo + chunk - 1) / chunk;
-    // exclusive scan of the block counts over the segments
-    const int lane = i & 63, w = i >> 6;
-    uint32_t inc = nb;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(inc, d, 64);
-        if (lane >= d) inc += y;
-    }
-    if (lane == 63) s_w[w] = inc;
+    __shared__ uint32_t s_h[kRadix * kCopies];
+    BlockWork bw;
+    if (!block_work(plan, nseg, bw)) return;
+    for (int k = threadIdx.x; k < kRadix * kCopies; k += kT) s_h[k] = 0;
     __syncthreads();
-    uint32_t first = inc - nb, used = 0;
-    for (int k = 0; k < kMaxViews / 64; ++k) {
-        first += k < w ? s_w[k] : 0u;
-        used += s_w[k];
-    }
-    if (used > (uint32_t)G) {  // cannot happen for ascending bounds; never write past the plan
-        for (uint32_t b = (uint32_t)i; b < (uint32_t)G; b += kMaxViews) {
-            SortBlock p = {};
-            plan[b] = p;
-        }
-        if (i == 0) *hist_n = 0u;
-        return;
-    }
-    for (uint32_t j = 0; j < nb; ++j) {
-        SortBlock p;
-        p.b0 = lo + j * chunk;
-        p.b1 = min(hi, p.b0 + chunk);
-        p.hbase = 256u * first + j;
-        p.hstride = nb;
-        p.kbase = kbase ? kbase[i] : 0u;
-        p.pad[0] = p.pad[1] = p.pad[2] = 0u;
-        plan[first + j] = p;
-    }
-    __syncthreads();
-    for (uint32_t b = used + (uint32_t)i; b < (uint32_t)G; b += kMaxViews) {
-        SortBlock p = {};
-        plan[b] = p;  // no work
-    }
-    if (i == 0) *hist_n = 256u * used;
-}
-
-__global__ __launch_bounds__(kT) void k_rs_hist(const uint32_t *__restrict__ keys, uint32_t cap,
-                                                const uint32_t *__restrict__ n_dev, int shift,
-                                                uint32_t *__restrict__ hist, int G,
-                                                const SortBlock *__restrict__ plan)
-{
-    __shared__ uint32_t s_h[kRadix];
-    const uint32_t n = min(*n_dev, cap);
-    uint32_t b0, b1, hbase, hstride, kbase;
-    if (!block_work(plan, n, G, b0, b1, hbase, hstride, kbase)) return;
-    s_h[threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t lt = lanemask_lt();
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (uint32_t base = b0; base < b1; base += kTile) {
+    const uint32_t copy = threadIdx.x & (kCopies - 1);
+    for (uint32_t base = bw.b0; base < bw.b1; base += kTile) {
         uint32_t d[kItems];
 #pragma unroll
         for (int it = 0; it < kItems; ++it) {  // all loads of the tile in flight at once
-            const uint32_t i = base + (uint32_t)(w * 64 * kItems + it * 64 + lane);
-            d[it] = i < b1 ? ((keys[i] - kbase) >> shift) & 0xFFu : 0x100u;
+            const uint32_t i = base + (uint32_t)(it * kT) + threadIdx.x;
+            d[it] = i < bw.b1 ? ((keys[i] - bw.kbase) >> shift) & 0xFFu : 0x100u;
         }
 #pragma unroll
-        for (int it = 0; it < kItems; ++it) {
-            const bool valid = d[it] < 0x100u;
-            const uint64_t peers = match_digit(d[it] & 0xFFu, valid);
-            if (valid && (peers & lt) == 0) atomicAdd(&s_h[d[it]], (uint32_t)__popcll(peers));
-        }
+        for (int it = 0; it < kItems; ++it)
+            if (d[it] < 0x100u) atomicAdd(&s_h[d[it] * kCopies + copy], 1u);
     }
     __syncthreads();
-    hist[hbase + threadIdx.x * hstride] = s_h[threadIdx.x];
+    if (threadIdx.x < kRadix) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int k = 0; k < kCopies; ++k)
+            c += s_h[threadIdx.x * kCopies + ((k + threadIdx.x) & (kCopies - 1))];  // rotated: no bank conflicts
+        hist[bw.hbase + threadIdx.x * bw.hstride] = c;
+        if (c) atomicAdd(&tot[bw.seg * kRadix + (int)threadIdx.x], c);
+    }
+}
+
+// One wave per row (segment, digit) of the histogram, in place.
+__global__ __launch_bounds__(256) void k_rs_rowscan(SortPlan plan, const uint32_t *__restrict__ tot,
+                                                    uint32_t *__restrict__ hist)
+{
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int seg = row >> 8, d = row & 255;
+    const SortSeg s = plan.seg[seg];
+    if (s.nb == 0) return;
+    uint32_t base = 0;  // elements of the segment with a lower digit
+    {
+        const uint4 t = reinterpret_cast<const uint4 *>(tot + seg * kRadix)[lane];
+        const int e = 4 * lane;
+        base = (e < d ? t.x : 0u) + (e + 1 < d ? t.y : 0u) + (e + 2 < d ? t.z : 0u) + (e + 3 < d ? t.w : 0u);
+#pragma unroll
+        for (int k = 32; k >= 1; k >>= 1) base += __shfl_xor(base, k, 64);
+    }
+    uint32_t run = s.lo + base;
+    uint32_t *h = hist + (size_t)kRadix * plan.first[seg] + (size_t)d * s.nb;
+    for (uint32_t j0 = 0; j0 < s.nb; j0 += 256) {
+        uint32_t v[4], sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t j = j0 + 4u * lane + k;
+            v[k] = j < s.nb ? h[j] : 0u;
+            sum += v[k];
+        }
+        uint32_t inc = sum;
+#pragma unroll
+        for (int k = 1; k < 64; k <<= 1) {
+            const uint32_t y = __shfl_up(inc, k, 64);
+            if (lane >= k) inc += y;
+        }
+        uint32_t ex = run + inc - sum;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t j = j0 + 4u * lane + k;
+            if (j < s.nb) h[j] = ex;
+            ex += v[k];
+        }
+        run += __shfl(inc, 63, 64);
+    }
 }
 
 __global__ __launch_bounds__(kT) void k_rs_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
                                                    uint32_t *__restrict__ kout, uint32_t *__restrict__ vout,
-                                                   uint32_t cap, const uint32_t *__restrict__ n_dev, int shift,
-                                                   const uint32_t *__restrict__ offsets, int G,
-                                                   const SortBlock *__restrict__ plan)
+                                                   int shift, SortPlan plan, int nseg,
+                                                   const uint32_t *__restrict__ offsets)
 {
     __shared__ uint32_t s_keys[kTile];
     __shared__ uint32_t s_vals[kTile];
     __shared__ uint32_t s_wcnt[kWaves][kRadix];
-    __shared__ uint32_t s_run[kRadix];
-    __shared__ uint32_t s_start[kRadix];
-    __shared__ uint32_t s_tot[kRadix];
-    __shared__ uint32_t s_w[kWaves];
+    __shared__ uint32_t s_start[kRadix];  // first tile slot of the digit
+    __shared__ uint32_t s_out[kRadix];    // output slot of tile slot 0 if it were the digit's
+    __shared__ uint32_t s_w[kRadix / 64];
 
-    const uint32_t n = min(*n_dev, cap);
-    uint32_t b0, b1, hbase, hstride, kbase;
-    if (!block_work(plan, n, G, b0, b1, hbase, hstride, kbase)) return;
+    BlockWork bw;
+    if (!block_work(plan, nseg, bw)) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint64_t lt = lanemask_lt();
-    s_run[threadIdx.x] = offsets[hbase + threadIdx.x * hstride];
+    // thread d < 256 carries the next output slot of digit d
+    uint32_t run = threadIdx.x < kRadix ? offsets[bw.hbase + threadIdx.x * bw.hstride] : 0u;
 
-    for (uint32_t base = b0; base < b1; base += kTile) {
+    for (uint32_t base = bw.b0; base < bw.b1; base += kTile) {
 #pragma unroll
-        for (int k = 0; k < kWaves; ++k) s_wcnt[k][threadIdx.x] = 0;
-        __syncthreads();
+        for (int k = 0; k < kRadix * kWaves / kT; ++k) (&s_wcnt[0][0])[k * kT + threadIdx.x] = 0;
         uint32_t key[kItems], val[kItems], rank[kItems];
 #pragma unroll
-        for (int it = 0; it < kItems; ++it) {
+        for (int it = 0; it < kItems; ++it) {  // all loads of the tile in flight at once
             const uint32_t i = base + (uint32_t)(w * 64 * kItems + it * 64 + lane);
-            const bool valid = i < b1;
+            const bool valid = i < bw.b1;
             key[it] = valid ? kin[i] : 0u;
             val[it] = valid ? vin[i] : 0u;
-            const uint32_t d = ((key[it] - kbase) >> shift) & 0xFFu;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            const bool valid = base + (uint32_t)(w * 64 * kItems + it * 64 + lane) < bw.b1;
+            const uint32_t d = ((key[it] - bw.kbase) >> shift) & 0xFFu;
             const uint64_t peers = match_digit(d, valid);
             const uint32_t before = s_wcnt[w][d];
             rank[it] = before + (uint32_t)__popcll(peers & lt);
@@ -200,87 +199,101 @@ __global__ __launch_bounds__(kT) void k_rs_scatter(const uint32_t *__restrict__ 
             if (!valid) rank[it] = 0xFFFFFFFFu;
         }
         __syncthreads();
-        // per digit: wave offsets and tile total
-        {
+        // per digit: wave offsets and tile total, then the exclusive scan of
+        // the totals over the digits (one digit per thread)
+        uint32_t tot = 0, inc = 0;
+        if (threadIdx.x < kRadix) {
             const int d = threadIdx.x;
-            uint32_t acc = 0;
 #pragma unroll
             for (int k = 0; k < kWaves; ++k) {
                 const uint32_t c = s_wcnt[k][d];
-                s_wcnt[k][d] = acc;
-                acc += c;
+                s_wcnt[k][d] = tot;
+                tot += c;
             }
-            s_tot[d] = acc;
-            // exclusive scan of tile totals over digits (one digit per thread)
-            uint32_t x = acc;
-            uint32_t inc = x;
+            inc = tot;
 #pragma unroll
             for (int dd = 1; dd < 64; dd <<= 1) {
                 const uint32_t y = __shfl_up(inc, dd, 64);
                 if (lane >= dd) inc += y;
             }
             if (lane == 63) s_w[w] = inc;
-            __syncthreads();
-            uint32_t wb = 0;
+        }
+        __syncthreads();
+        if (threadIdx.x < kRadix) {
+            uint32_t start = inc - tot;
 #pragma unroll
-            for (int k = 0; k < kWaves; ++k) wb += k < w ? s_w[k] : 0u;
-            s_start[d] = wb + inc - x;
+            for (int k = 0; k < kRadix / 64; ++k) start += k < w ? s_w[k] : 0u;
+            s_start[threadIdx.x] = start;
+            s_out[threadIdx.x] = run - start;
+            run += tot;
         }
         __syncthreads();
 #pragma unroll
         for (int it = 0; it < kItems; ++it) {
             if (rank[it] == 0xFFFFFFFFu) continue;
-            const uint32_t d = ((key[it] - kbase) >> shift) & 0xFFu;
+            const uint32_t d = ((key[it] - bw.kbase) >> shift) & 0xFFu;
             const uint32_t lp = s_start[d] + s_wcnt[w][d] + rank[it];
             s_keys[lp] = key[it];
             s_vals[lp] = val[it];
         }
         __syncthreads();
-        const uint32_t cnt = min((uint32_t)kTile, b1 - base);
-        for (uint32_t j = threadIdx.x; j < cnt; j += kT) {
-            const uint32_t k2 = s_keys[j];
-            const uint32_t d = ((k2 - kbase) >> shift) & 0xFFu;
-            const uint32_t g = s_run[d] + (j - s_start[d]);
-            kout[g] = k2;
-            vout[g] = s_vals[j];
+        const uint32_t cnt = min((uint32_t)kTile, bw.b1 - base);
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            const uint32_t j = (uint32_t)(it * kT) + threadIdx.x;
+            if (j < cnt) {
+                const uint32_t k2 = s_keys[j];
+                const uint32_t g = s_out[((k2 - bw.kbase) >> shift) & 0xFFu] + j;
+                kout[g] = k2;
+                vout[g] = s_vals[j];
+            }
         }
-        __syncthreads();
-        s_run[threadIdx.x] += s_tot[threadIdx.x];
-        __syncthreads();
+        __syncthreads();  // the tile's LDS read before the next tile overwrites it
     }
+}
+
+// One segment of the whole array.
+__global__ __launch_bounds__(kMaxViews) void k_plan_whole(uint32_t cap, const uint32_t *__restrict__ n_dev,
+                                                          SortPlan plan, int G, uint32_t *__restrict__ tot,
+                                                          uint32_t ntot)
+{
+    sort_plan_block(0u, min(*n_dev, cap), 0u, min(*n_dev, cap), 1, G, plan, tot, ntot);
 }
 
 }  // namespace
 
+int sort_grid(uint32_t cap, int nseg)
+{
+    // one block per tile up to kSortBlocksMax, and one more per segment (a
+    // segment's last chunk is partial)
+    const uint64_t want = ((uint64_t)cap + kTile - 1) / kTile + (uint64_t)nseg + 1;
+    return (int)std::min<uint64_t>(kSortBlocksMax, want);
+}
+
+uint32_t sort_totals(int bits, int nseg) { return (uint32_t)((bits + 7) / 8) * (uint32_t)nseg * kRadix; }
+
+void launch_plan_whole(uint32_t cap, const uint32_t *n_dev, int bits, const SortScratch &s, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_plan_whole, dim3(1), dim3(kMaxViews), 0, st, cap, n_dev, s.plan, sort_grid(cap, 1), s.tot,
+                       sort_totals(bits, 1));
+}
+
 // Sorts (keys, vals) over bits [0, bits) with ceil(bits / 8) passes that
 // ping-pong between (keys, vals) and the scratch pair.  Returns true when the
 // pass count is odd, i.e. the sorted result is in (s.k2, s.v2).
-bool launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t cap, const uint32_t *n_dev, int bits,
-                       const SortScratch &s, hipStream_t st, const uint32_t *seg_bounds, int nseg,
-                       const uint32_t *seg_kbase)
+bool launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t cap, int nseg, int bits, const SortScratch &s,
+                       hipStream_t st)
 {
     if (cap == 0 || bits <= 0) return false;
     const int passes = (bits + 7) / 8;
-    // blocks of >= 4 tiles each, up to kSortBlocksMax: enough waves in flight
-    // to cover the memory latency of the digit passes
-    const uint32_t want = std::max<uint32_t>(1u, (cap + 4 * kTile - 1) / (4 * kTile));
-    int G = (int)std::min<uint32_t>(kSortBlocksMax, want);
-    const SortBlock *plan = nullptr;
-    const uint32_t *hist_n = nullptr;
-    if (seg_bounds) {
-        G = std::min(kSortBlocksMax, std::max(G, 2 * nseg + 1));
-        hipLaunchKernelGGL(k_seg_plan, dim3(1), dim3(kMaxViews), 0, st, seg_bounds, nseg, seg_kbase, cap, n_dev, G,
-                           s.plan, s.total + 1);
-        plan = s.plan;
-        hist_n = s.total + 1;
-    }
+    const int G = sort_grid(cap, nseg);
     uint32_t *ki = keys, *vi = vals, *ko = s.k2, *vo = s.v2;
     for (int p = 0; p < passes; ++p) {
         const int shift = p * 8;
-        hipLaunchKernelGGL(k_rs_hist, dim3(G), dim3(kT), 0, st, ki, cap, n_dev, shift, s.hist, G, plan);
-        launch_scan(s.hist, nullptr, (uint32_t)(kRadix * G), hist_n, s.hist_scan, s.total, s.partial, st);
-        hipLaunchKernelGGL(k_rs_scatter, dim3(G), dim3(kT), 0, st, ki, vi, ko, vo, cap, n_dev, shift, s.hist_scan,
-                           G, plan);
+        uint32_t *tot = s.tot + (size_t)p * nseg * kRadix;
+        hipLaunchKernelGGL(k_rs_hist, dim3(G), dim3(kT), 0, st, ki, shift, s.plan, nseg, s.hist, tot);
+        hipLaunchKernelGGL(k_rs_rowscan, dim3(nseg * (kRadix / 4)), dim3(256), 0, st, s.plan, tot, s.hist);
+        hipLaunchKernelGGL(k_rs_scatter, dim3(G), dim3(kT), 0, st, ki, vi, ko, vo, shift, s.plan, nseg, s.hist);
         std::swap(ki, ko);
         std::swap(vi, vo);
     }
