@@ -55,6 +55,7 @@ struct hgs_ctx {
     int64_t n = 0, n_leaves = 0;
     uint32_t *pinfo = nullptr;
     float *box = nullptr;
+    float4 *word_bounds = nullptr;  // per 64 nodes: bounds of their parents' boxes (the cut skips by them)
     int32_t *child_count = nullptr, *child_begin = nullptr;
     int32_t *interior = nullptr;  // ids of the interior nodes, ascending
     int32_t *leaf_src = nullptr;  // after hgs_build: input index of every leaf node (-1 interior)
@@ -298,6 +299,7 @@ DevHier dev_hier(const hgs_ctx *c)
     h.n = c->n;
     h.pinfo = c->pinfo;
     h.box = c->box;
+    h.word_bounds = c->word_bounds;
     h.child_count = c->child_count;
     h.child_begin = c->child_begin;
     float *const *P = c->use_bound ? c->bound : c->own;
@@ -583,7 +585,7 @@ void drop_hierarchy(hgs_ctx *ctx)
         ctx->own[k] = nullptr;
         ctx->bound[k] = nullptr;
     }
-    void **bufs[] = {(void **)&ctx->pinfo, (void **)&ctx->box, (void **)&ctx->child_count,
+    void **bufs[] = {(void **)&ctx->pinfo, (void **)&ctx->box, (void **)&ctx->word_bounds, (void **)&ctx->child_count,
                      (void **)&ctx->child_begin, (void **)&ctx->interior, (void **)&ctx->leaf_src};
     for (void **b : bufs) {
         dfree(ctx, *b);
@@ -921,6 +923,7 @@ hgs_status hgs_upload(hgs_ctx *ctx, const hgs_hierarchy_desc *d, int src_on_devi
     hgs_status s;
     if ((s = dalloc(ctx, (void **)&ctx->pinfo, 4 * N))) return s;
     if ((s = dalloc(ctx, (void **)&ctx->box, 24 * N))) return s;
+    if ((s = dalloc(ctx, (void **)&ctx->word_bounds, 32 * ((N + 63) / 64)))) return s;
     if ((s = dalloc(ctx, (void **)&ctx->child_count, 4 * N))) return s;
     if ((s = dalloc(ctx, (void **)&ctx->child_begin, 4 * N))) return s;
     std::vector<int32_t> interior;
@@ -952,8 +955,10 @@ hgs_status hgs_upload(hgs_ctx *ctx, const hgs_hierarchy_desc *d, int src_on_devi
     ctx->n_interior = (int64_t)interior.size();
     const hipMemcpyKind k2 = src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     for (int k = 0; k < 5; ++k) HIPC(hipMemcpy(ctx->own[k], src[k], 4 * comp[k] * N, k2));
-    HIPC(hipDeviceSynchronize());
     ctx->n = N;
+    launch_word_bounds(dev_hier(ctx), ctx->word_bounds, ctx->stream);
+    HIPC(hipGetLastError());
+    HIPC(hipDeviceSynchronize());
     ctx->n_leaves = leaves;
     ctx->has_hier = true;
     ctx->param_gen++;
@@ -1153,6 +1158,7 @@ hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *L, int src_on_device, 
         launch_box_level(t, (int32_t)base[d], (int32_t)(base[d + 1] - base[d]), bmin, bmax, st);
     if ((s = dalloc(ctx, (void **)&ctx->pinfo, 4 * (size_t)N))) return s;
     if ((s = dalloc(ctx, (void **)&ctx->box, 24 * (size_t)N))) return s;
+    if ((s = dalloc(ctx, (void **)&ctx->word_bounds, 32 * (((size_t)N + 63) / 64)))) return s;
     if ((s = dalloc(ctx, (void **)&ctx->child_count, 4 * (size_t)N))) return s;
     if ((s = dalloc(ctx, (void **)&ctx->child_begin, 4 * (size_t)N))) return s;
     if ((s = dalloc(ctx, (void **)&ctx->interior, 4 * (size_t)std::max<uint32_t>(n_int, 1)))) return s;
@@ -1162,9 +1168,10 @@ hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *L, int src_on_device, 
     HIPC(hipMemcpyAsync(ctx->child_begin, t.child_begin, 4 * (size_t)N, hipMemcpyDeviceToDevice, st));
     HIPC(hipMemcpyAsync(ctx->leaf_src, leaf_src, 4 * (size_t)N, hipMemcpyDeviceToDevice, st));
     launch_interior_list(t.child_count, irank, N, ctx->interior, st);
+    ctx->n = N;
+    launch_word_bounds(dev_hier(ctx), ctx->word_bounds, st);
     HIPC(hipGetLastError());
     HIPC(hipStreamSynchronize(st));
-    ctx->n = N;
     ctx->n_leaves = n;
     ctx->n_interior = n_int;
     ctx->has_hier = true;

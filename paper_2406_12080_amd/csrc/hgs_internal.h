@@ -42,6 +42,7 @@ struct DevHier {
     int64_t n;
     const uint32_t *pinfo;  // parent index | leaf bit
     const float *box;       // [6][n]: bmin x y z, bmax x y z
+    const float4 *word_bounds;  // [ceil(n / 64)][2]: bounds of each mask word's parents (k_word_bounds)
     const int32_t *child_count;
     const int32_t *child_begin;  // first child (children are contiguous); 0 for leaves
     const float *mean, *scale, *rot, *opacity, *sh;  // node-major: [N][3] [N][3] [N][4] [N] [N][48]
@@ -131,6 +132,8 @@ void launch_compact_keep(const DevHier &h, const double *emax, double tau_min, i
                          hipStream_t st);
 void launch_cut_flags(const DevHier &h, const DevView *views, int nv, uint64_t *masks, uint32_t *block_counts,
                       int nblocks, hipStream_t st);
+// The bounds of every mask word, two float4 each (once per hierarchy).
+void launch_word_bounds(const DevHier &h, float4 *bounds, hipStream_t st);
 // Also writes word_off[v][w]: the cut position of the first selected node of
 // mask word w of view v (words holding a selected node only), and, when
 // cut_base is given, cut_base[v] = the cut position of view v's first
