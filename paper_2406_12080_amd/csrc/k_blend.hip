@@ -24,6 +24,7 @@
 // DPP exchanges and over the rows and waves of the tile in LDS (FP64 atomics), and
 // adds it once per tile, in FP64, to the splat's screen-space gradient.
 #include <algorithm>
+#include <cstddef>
 #include <map>
 #include <mutex>
 
@@ -32,11 +33,6 @@
 namespace hgs {
 
 namespace {
-
-struct AlphaEval {
-    float G, an, ap, apr, q, alpha, u1, u2;  // q = (1 - a_p)^(1/K), apr = 1 - q
-    bool cn, cp;
-};
 
 // Staged splat, per 8x8 block of the tile: c = w . (block corner + 1/2 - mean)
 // in FP64, so that a lane only adds w . (its offset inside the block): the
@@ -53,33 +49,25 @@ __device__ __forceinline__ void block_offsets(const SplatRec &r, const double4 &
     dy0 = (float)dy;
 }
 
-// Identical instruction sequence in forward and backward (explicit FMAs, no
-// other contraction), so that the backward reproduces the forward's
-// decisions bit for bit.  `interp` (t > 0) is the same for every lane.
-__device__ __forceinline__ void eval_alpha(const float4 &W, const float4 &O, float2 c, float lx, float ly,
-                                           bool interp, AlphaEval &e)
+// Identical arithmetic in forward and backward (explicit FMAs, no other
+// contraction), so that the backward reproduces the forward's decisions bit
+// for bit.
+__device__ __forceinline__ float eval_gauss(const float4 &W, float2 c, float lx, float ly)
 {
 #pragma clang fp contract(off)
-    e.u1 = fmaf(ly, W.y, fmaf(lx, W.x, c.x));
-    e.u2 = fmaf(ly, W.w, fmaf(lx, W.z, c.y));
-    const float s = fmaf(e.u1, e.u1, e.u2 * e.u2);
-    e.G = __builtin_amdgcn_exp2f(-s);
-    const float an = O.x * e.G;
-    e.cn = an > kAlphaMax;
-    e.an = fminf(an, kAlphaMax);
-    e.alpha = e.an;
-    e.ap = 0.0f;
-    e.apr = 0.0f;
-    e.q = 1.0f;
-    e.cp = false;
-    if (interp) {
-        const float ap = O.y * e.G;
-        e.cp = ap > kAlphaMax;
-        e.ap = fminf(ap, kAlphaMax);
-        e.q = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(1.0f - e.ap) * O.w);
-        e.apr = 1.0f - e.q;
-        e.alpha = (1.0f - O.z) * e.an + O.z * e.apr;
-    }
+    const float u1 = fmaf(ly, W.y, fmaf(lx, W.x, c.x));
+    const float u2 = fmaf(ly, W.w, fmaf(lx, W.z, c.y));
+    const float s = fmaf(u1, u1, u2 * u2);
+    return __builtin_amdgcn_exp2f(-s);
+}
+
+// alpha of an interpolated splat from a_n, 1 - a_p, 1 - t, t and 1/K; q = (1 -
+// a_p)^(1/K).  With t = 0 it is a_n exactly (q is finite).
+__device__ __forceinline__ float eval_interp(float an, float omap, float omt, float t, float invK, float &q)
+{
+#pragma clang fp contract(off)
+    q = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(omap) * invK);
+    return omt * an + t * (1.0f - q);
 }
 
 // True when no pixel of a square of (E + 1) x (E + 1) pixels can take the
@@ -312,13 +300,17 @@ __device__ __forceinline__ void blend_tile(const DevView *__restrict__ views, in
                 const uint64_t gm = hm & alive;
                 n_eval += (uint32_t)__popcll(gm);
                 n_eval_t += (uint32_t)__popcll(gm & __ballot(Ov.z > 0.0f));
-                AlphaEval e;
-                eval_alpha(s_w[j], Ov, s_u[w][j], lx, ly, interp, e);
-                if (go && e.alpha >= kAlphaMin) {
-                    const float Tn = T * (1.0f - e.alpha);
+                const float G = eval_gauss(s_w[j], s_u[w][j], lx, ly);
+                float alpha = fminf(Ov.x * G, kAlphaMax);
+                if (interp) {
+                    float qp;
+                    alpha = eval_interp(alpha, 1.0f - fminf(Ov.y * G, kAlphaMax), 1.0f - Ov.z, Ov.z, Ov.w, qp);
+                }
+                if (go && alpha >= kAlphaMin) {
+                    const float Tn = T * (1.0f - alpha);
                     const bool stop = Tn < kTMin;
                     const float4 Cc = s_c[j];
-                    const float wgt = stop ? 0.0f : e.alpha * T;
+                    const float wgt = stop ? 0.0f : alpha * T;
                     C0 += Cc.x * wgt;
                     C1 += Cc.y * wgt;
                     C2 += Cc.z * wgt;
@@ -382,60 +374,38 @@ __global__ __launch_bounds__(TW *TH) void k_blend(const DevView *__restrict__ vi
     }
 }
 
-// Sum over each row of 16 lanes (one 4x4 quarter of the wave's block) of 12
-// per-lane values, taken as six pairs (first, second): four halvings with
-// DPP inside the row (partners l ^ 8, l ^ 7, l ^ 2 and l ^ 1), each keeping
-// one of the two values of a pair per lane.  The caller gives the first
-// halving's operands, chosen per lane by bit 3 of the lane: S1[k] = second
-// if set, else first; S2[k] = the other one.  Lane l of the row ends with the
-// row's total of value row_slot(l) (value 2 k + 1 is the second of pair k;
-// -1: a copy of another lane's total).
-__device__ __forceinline__ float row_reduce12(const float (&S1)[6], const float (&S2)[6], int lane)
-{
-    const bool b2 = (lane & 4) != 0, b1 = (lane & 2) != 0, b0 = (lane & 1) != 0;
-    float A[6], B[3];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) A[k] = S1[k] + dpp_move<0x128>(S2[k]);  // row_ror:8
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-        B[m] = (b2 ? A[2 * m + 1] : A[2 * m]) + dpp_move<0x141>(b2 ? A[2 * m] : A[2 * m + 1]);  // half mirror
-    const float C0 = (b1 ? B[1] : B[0]) + dpp_move<0x4E>(b1 ? B[0] : B[1]);
-    const float C1 = B[2] + dpp_move<0x4E>(B[2]);
-    return (b0 ? C1 : C0) + dpp_move<0xB1>(b0 ? C0 : C1);
-}
-
-__device__ __forceinline__ int row_slot(int lane)
-{
-    const int b3 = (lane >> 3) & 1, b2 = (lane >> 2) & 1, b1 = (lane >> 1) & 1, b0 = lane & 1;
-    return b0 == 0 ? 4 * b1 + 2 * b2 + b3 : (b1 == 0 ? 8 + 2 * b2 + b3 : -1);
-}
+// Pixel of lane l inside its wave's 8x8 block in the backward: column l & 3
+// and row l >> 4 of the 4x4 quarter (l >> 2) & 3, so that the lane swaps of
+// the reduction (l ^ 32, l ^ 16) run over a quarter's rows.
+__device__ __forceinline__ int bwd_quarter(int lane) { return (lane >> 2) & 3; }
+__device__ __forceinline__ int bwd_x(int lane) { return (bwd_quarter(lane) & 1) * 4 + (lane & 3); }
+__device__ __forceinline__ int bwd_y(int lane) { return (bwd_quarter(lane) >> 1) * 4 + (lane >> 4); }
 
 constexpr int kG = 12;  // floats per splat in the screen-space gradient
 
-// Per-lane gradient slots of one (pixel, splat) pair, summed over the tile:
-//   0, 1    P'_i = h v_i                  with h = G dL/dG (G the Gaussian)
-//   2, 3    Q'_11, Q'_22 = h v_1 v_1, h v_2 v_2
-//   4       Q'_12 = h v_1 v_2
+// Gradient slots of a splat, summed over the pixels of the tile.  With h = G
+// dL/dG (G the Gaussian) and (x, y) the pixel's offset from the tile centre:
+//   0, 1    h x, h y
+//   2, 3    h x x, h y y
+//   4       h x y
 //   5       S = h
 //   6, 7    dL/dA_n, dL/dA_p (A = kappa |o|)
 //   8..10   dL/d colour
 //   11      dL/dt through alpha (only when the caller asks for dL/dt)
-// Here v = u - c is the pixel's position on the conic's scaled eigen-axes
-// relative to the tile's centre (c, formed in FP64 at staging): v is the
-// pixel's offset from the tile centre mapped by the axes.  The moments
-// about the splat's centre follow in FP64 at the flush, P = P' + c S and
-// Q = Q' + c P'^T + P' c^T + c c^T S.  Taken directly about the splat's
-// centre, the moments of a large splat whose centre lies far off screen are
-// dominated by c S and c c^T S, and the mean and covariance gradients built
-// from them cancel almost entirely in the chain through the projection:
-// separately rounded FP32 sums of P and Q then leave errors far above the
-// result.  With the moments about the tile both large parts carry the one
-// rounded S, and the cancellation removes its error with it.  What remains
-// is the FP32 rounding of P' and Q', which grows with |v|^2: hence the
-// tile's centre (|v| at most half the tile's diagonal) rather than a
-// corner, and S summed from the same per-pixel h as P' and Q' (forming it
-// from slots 5 and 6 instead, equal in exact arithmetic, leaves per-pixel
-// differences that c c^T amplifies).
+// The flush maps the moments by the conic's scaled eigen-axes (v = W (x, y),
+// u = v + c, c the tile centre's offset formed in FP64 at staging) and about
+// the splat's centre, in FP64: P = P' + c S and Q = Q' + c P'^T + P' c^T +
+// c c^T S.  Taken directly about the splat's centre, the moments of a large
+// splat whose centre lies far off screen are dominated by c S and c c^T S,
+// and the mean and covariance gradients built from them cancel almost
+// entirely in the chain through the projection: separately rounded FP32 sums
+// of P and Q then leave errors far above the result.  With the moments about
+// the tile both large parts carry the one rounded S, and the cancellation
+// removes its error with it.  What remains is the FP32 rounding of the
+// moments, which grows with the squared offset: hence the tile's centre
+// (at most half the tile's diagonal) rather than a corner, and S summed from
+// the same per-pixel h (forming it from slots 6 and 7 instead, equal in exact
+// arithmetic, leaves per-pixel differences that c c^T amplifies).
 // The screen-space gradient follows from the tile sums by the splat's
 // (per-tile constant) axes: with g = conic d = (u1 w1 + u2 w2) / kHalfLog2e
 // and G = exp(-q/2), dL/dmean = sum h g and dL/dSigma2' = -sum (h / 2) g g^T
@@ -465,12 +435,79 @@ __device__ __forceinline__ double2 centre_offsets(const SplatRec &r, const doubl
     return make_double2(dx * W.x + dy * W.y, dx * W.z + dy * W.w);
 }
 
-// DET (the deterministic mode): no floating-point atomics.  Each row of 16
-// lanes stores its FP32 partial sums in a slot of its own, the flush adds the
-// rows in a fixed order (FP64), and the tile's 11 terms for a splat go with
-// plain stores to det.part at the pair's position in the list k_duplicate
-// emitted (the splat's first pair plus the tile's row-major index in its
-// tile rectangle); launch_det_sum then adds each splat's rows in order.
+// Reduction.  Each step (one splat per quarter, one pixel per lane) leaves
+// six values per lane, h, the three colour terms, dL/dA_n and dL/dA_p, of
+// which h enters weighted by 1, y and y^2 (y the pixel's row in its quarter):
+// eight sums over the four rows of a quarter's columns.  Two steps are taken
+// together: v_permlane32_swap of a value of the first and of the second step,
+// and an add, halve both at once; v_permlane16_swap does the same for the sums
+// 0-3 against 4-7, so that 24 instructions leave, for both steps, four sums
+// per lane (row r of 16 lanes: sums 0-3 or 4-7 by r & 1, of step r >> 1).  The
+// shift to the tile centre, the weights x and x^2 and two quad exchanges
+// finish the sums over the columns, and the totals go to the tile's LDS sums
+// (FP64 atomics).
+//
+// The kernel issues VALU instructions near the limit (1.07 of one per 4 cycles
+// and SIMD) with the LDS 0.57 busy, so what counts is their number per step,
+// about 93 (119 with the 12 slots formed per lane and summed by four DPP
+// halvings, 34 instructions and their operands' selects): the walk's order is
+// a list made per batch instead of a bit mask taken apart step by step, the
+// colour behind enters as its product with the cotangent, and a record sits
+// at one LDS address.  v_mfma_f32_16x16x4_f32 for the same sums was slower
+// (six per step; FP32 matrix instructions hold the VALU for their 32 cycles:
+// 11.5 against 9.0 ms), larger batches too (7.6 -> 8.9 ms at 128 entries:
+// fewer tiles resident).  32 views of 1920x1080 over 30M leaves, 16x8 tiles:
+// 9.0 -> 7.6 ms; 16x16 tiles 10.0 -> 7.6, 32x16 19.2 -> 9.7; 8 views of
+// 1280x720 over 2M leaves 4.2 -> 3.4 ms.
+//
+// DET (the deterministic mode): no floating-point atomics.  Each quarter
+// stores its FP32 partial sums in a slot of its own, the flush adds the
+// quarters in a fixed order (FP64), and the tile's 11 terms for a splat go
+// with plain stores to det.part at the pair's position in the list
+// k_duplicate emitted (the splat's first pair plus the tile's row-major index
+// in its tile rectangle); launch_det_sum then adds each splat's rows in order.
+// Sums of lanes l and l ^ 32 of a in the lower half of the wave, of b in the upper.
+__device__ __forceinline__ float fold32(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Sums of lanes l and l ^ 16 of a in the even rows of 16 lanes, of b in the odd rows.
+__device__ __forceinline__ float fold16(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Over each quad of lanes: the sum of v, and sum_k c[k] v(lane k).
+__device__ __forceinline__ float quad_sum(float v)
+{
+    v += dpp_move<0xB1>(v);
+    return v + dpp_move<0x4E>(v);
+}
+__device__ __forceinline__ float quad_dot(float v, const float (&c)[4])
+{
+    float s = c[0] * dpp_move<0x00>(v);
+    s = fmaf(c[1], dpp_move<0x55>(v), s);
+    s = fmaf(c[2], dpp_move<0xAA>(v), s);
+    return fmaf(c[3], dpp_move<0xFF>(v), s);
+}
+
+// A splat staged for one tile by the backward.
+template <int NB>
+struct __align__(16) BwdStaged {
+    float4 w;      // axes
+    float4 o;      // A_n, A_p, t, 1/K
+    float4 c;      // colour, 1 - t
+    float2 u[NB];  // per 8x8 block: the offsets of its corner pixel on the axes
+    double g[kG];  // the tile's sums; the flush turns them into the splat's 11 terms in place
+    // Bytes from one record to the next: an odd number of 16-byte units, so
+    // that the different records that the four quarters of a wave read at once
+    // collide in a bank for a distance of 16 records only (LDS conflict
+    // cycles of the 8 x 1280x720 workload 0.21 -> 0.11 of the kernel's time).
+    static constexpr uint32_t kStride = 16u * ((uint32_t)(3 + (NB + 1) / 2 + kG / 2) | 1u);
+};
+
 template <int TW, int TH, int BATCH, bool DT, bool DET>
 __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views, int nv,
                                                const uint32_t *__restrict__ tile_order,
@@ -488,35 +525,53 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
     constexpr int SX = TW / 8;
     constexpr int NB = (TW / 8) * (TH / 8);
     constexpr int NQW = BATCH / 32;  // 32-entry words of a quarter's mask
-    static_assert(BATCH % 32 == 0 && BATCH <= 32 * NW && NB <= 8, "tile/batch combination");
-    __shared__ float4 s_w[BATCH], s_o[BATCH], s_c[BATCH];
-    __shared__ float2 s_u[NB][BATCH];  // c1, c2
-    __shared__ uint32_t s_id[BATCH];
-    __shared__ __align__(16) double s_g[DET ? 1 : BATCH][kG];  // the quarters' partial sums, added in FP64
-    __shared__ double s_d[DET ? 1 : BATCH * 11];  // the flushed terms, splat-major
-    __shared__ float s_gr[DET ? 4 * NW : 1][DET ? BATCH : 1][kG];  // DET: each row's partial sums
+    constexpr int PER = BATCH >= 64 * NW ? 64 : 32;  // entries that a wave stages and flushes
+    static_assert(BATCH % PER == 0 && BATCH <= PER * NW && NB <= 8, "tile/batch combination");
+    using Rec = BwdStaged<NB>;
+    constexpr uint32_t kRec = Rec::kStride, kDead = kRec * BATCH;
+    static_assert(sizeof(Rec) <= kRec && kDead < 65536, "a list entry is a 16-bit byte offset");
+    // the last record blends nowhere: for a quarter past its list's end
+    __shared__ __align__(16) unsigned char s_rec[kRec * (BATCH + 1)];
+    auto rec_at = [&](uint32_t off) -> Rec & { return *reinterpret_cast<Rec *>(s_rec + off); };
+    __shared__ uint32_t s_id[BATCH];  // gradient rows
+    __shared__ float s_gr[DET ? 4 * NW : 1][DET ? BATCH : 1][kG];  // DET: each quarter's partial sums
     __shared__ uint32_t s_pq[DET ? BATCH : 1];  // DET: the pair's position in the emitted list
     __shared__ double2 s_ref[BATCH];    // the tile centre's offsets on the axes (FP64)
-    // bit b of word k: quarter q of block bk may take entry 32 k + 31 - b
-    // (reversed, so that the lowest set bit is the next entry back to front)
-    __shared__ uint32_t s_qm[NB][4][NQW];
+    __shared__ uint32_t s_qm[NB][4][NQW];     // bit b of word k: quarter q of block bk blended entry 32 k + b
+    // the records a quarter walks, back to front (byte offsets in s_r)
+    constexpr int LIST = BATCH + 4;
+    __shared__ __align__(4) uint16_t s_list[NB][4][LIST];
     __shared__ uint32_t s_max;
     const uint32_t tile = tile_order[tslot];  // longest lists first
     const int vi = view_of_tile(views, nv, tile);
     const DevView &V = views[vi];
     const uint32_t lt = tile - V.tile_base;
     const int tx = (int)(lt % (uint32_t)V.tiles_x), ty = (int)(lt / (uint32_t)V.tiles_x);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, q = bwd_quarter(lane);
     const int ox = tx * TW, oy = ty * TH;
-    const int bx = quarter_x(lane), by = quarter_y(lane);
+    const int bx = bwd_x(lane), by = bwd_y(lane);
     const int px = ox + (w % SX) * 8 + bx, py = oy + (w / SX) * 8 + by;
     const bool inside = px < V.W && py < V.H;
     const float lx = (float)bx, ly = (float)by;
-    // the pixel's offset from the tile centre (the moments' reference; exact)
-    const float lxt = (float)(px - ox) - 0.5f * (TW - 1), lyt = (float)(py - oy) - 0.5f * (TH - 1);
     const uint2 rg = ranges[tile];
-    const int slot = row_slot(lane);
-    const bool b3 = (lane & 8) != 0;  // which value of each pair this lane keeps in the first halving
+
+    const float yl = (float)(lane >> 4) - 1.5f, yl2 = yl * yl;  // the pixel's row about the quarter's centre
+    // the finish: in rows 0 and 2 of 16 lanes (sums 0-3 of a step) lane x of a
+    // quad forms S, S x, S x^2 from the four columns (weights cw; x = 3: the
+    // sum of colour 0), in rows 1 and 3 the plain sums
+    const bool low = (lane & 16) == 0;
+    const int qx = lane & 3;
+    const float yq = low ? (float)((w / SX) * 8 + (q >> 1) * 4) + 1.5f - 0.5f * (TH - 1) : 0.0f;
+    float cw[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float xt = (float)((w % SX) * 8 + (q & 1) * 4 + k) - 0.5f * (TW - 1);  // column k about the tile's centre
+        cw[k] = qx == 0 ? 1.0f : (qx == 1 ? xt : xt * xt);
+    }
+    // (11: nothing to put)
+    const int slot_a = low ? (qx == 0 ? 5 : (qx == 1 ? 0 : (qx == 2 ? 2 : 8))) : (qx == 0 ? 9 : (qx == 3 ? 7 : 11));
+    const int slot_b = low ? (qx == 0 ? 1 : (qx == 1 ? 4 : (qx == 2 ? 3 : 11))) : (qx == 0 ? 10 : (qx == 2 ? 6 : 11));
+    const uint32_t off_a = (uint32_t)offsetof(Rec, g) + 8u * slot_a, off_b = (uint32_t)offsetof(Rec, g) + 8u * slot_b;
 
     float T = 1.0f, g0 = 0.0f, g1 = 0.0f, g2 = 0.0f;
     uint32_t last = 0;
@@ -529,48 +584,55 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
         g1 = V.dL[3 * p + 1];
         g2 = V.dL[3 * p + 2];
     }
-    // the colour cotangents as the first halving takes them (pairs (0, 1), (2, -))
-    const float ga = b3 ? g1 : g0, gb = b3 ? g0 : g1, g2a = b3 ? 0.0f : g2, g2b = b3 ? g2 : 0.0f;
     if (threadIdx.x == 0) s_max = 0;
     __syncthreads();
-    // the quarter's last contributor (rows of 16 lanes), then the tile's
+    // the quarter's last contributor, then the tile's
     uint32_t qm = last;
-#pragma unroll
-    for (int d = 8; d >= 1; d >>= 1) qm = max(qm, (uint32_t)__shfl_xor((int)qm, d, 64));
-    uint32_t wm = max(qm, (uint32_t)__shfl_xor((int)qm, 16, 64));
-    wm = max(wm, (uint32_t)__shfl_xor((int)wm, 32, 64));
+    qm = max(qm, (uint32_t)__shfl_xor((int)qm, 1, 64));
+    qm = max(qm, (uint32_t)__shfl_xor((int)qm, 2, 64));
+    qm = max(qm, (uint32_t)__shfl_xor((int)qm, 16, 64));
+    qm = max(qm, (uint32_t)__shfl_xor((int)qm, 32, 64));
+    uint32_t wm = max(qm, (uint32_t)__shfl_xor((int)qm, 4, 64));
+    wm = max(wm, (uint32_t)__shfl_xor((int)wm, 8, 64));
     if (lane == 0) atomicMax(&s_max, wm);
     __syncthreads();
     const uint32_t end = rg.x + s_max;
-    float R0 = 0.0f, R1 = 0.0f, R2 = 0.0f;  // colour composited behind the current splat
+    float Rg = 0.0f;  // cotangent . colour composited behind the current splat
     uint32_t n_eval = 0, n_eval_t = 0, n_con = 0;  // wave totals (scalar)
+
+    if (threadIdx.x == 0) {  // (ordered before its first read by the barrier after the staging)
+        Rec &dead = rec_at(kDead);
+        dead.w = dead.o = dead.c = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+        for (int bk = 0; bk < NB; ++bk) dead.u[bk] = make_float2(0.0f, 0.0f);
+    }
 
     for (uint32_t hi = end; hi > rg.x;) {
         const uint32_t lo = hi - rg.x > (uint32_t)BATCH ? hi - BATCH : rg.x;
         const int cnt = (int)(hi - lo);
         {
-            // wave w stages entries 32 w .. 32 w + 31 on its lanes 0-31 (the
-            // batch holds at most 32 entries per wave), so that the staging
-            // work is spread over the waves of the tile
-            const int j = 32 * w + lane;
+            // wave w stages entries PER w .. PER w + PER - 1, so that the
+            // staging work is spread over the waves of the tile
+            const int j = PER * w + lane;
             uint32_t live = 0u;
-            if (lane < 32 && j < cnt) {
+            if (lane < PER && j < cnt) {
                 const uint32_t sidx = pair_vals[lo + j];
                 const SplatRec r = recs[sidx];
                 const double4 W64 = axes[sidx];
                 const float4 W = make_float4((float)W64.x, (float)W64.y, (float)W64.z, (float)W64.w);
+                Rec &sr = rec_at(kRec * (uint32_t)j);
 #pragma unroll
                 for (int bk = 0; bk < NB; ++bk) {
                     float c1, c2, d0, d1;
                     block_offsets(r, W64, ox + (bk % SX) * 8, oy + (bk / SX) * 8, c1, c2, d0, d1);
-                    s_u[bk][j] = make_float2(c1, c2);
+                    sr.u[bk] = make_float2(c1, c2);
                     // the quarters of this block that blended the splat in the forward
                     live |= (uint32_t)qbits[(size_t)bk * qstride + lo + (uint32_t)j] << (4 * bk);
                 }
-                s_id[j] = vis_rank[sidx];  // gradient row
-                s_w[j] = W;
-                s_o[j] = make_float4(r.An, r.Ap, r.t, r.invK);
-                s_c[j] = make_float4(r.r, r.g, r.b, 0.0f);
+                s_id[j] = vis_rank[sidx];
+                sr.w = W;
+                sr.o = make_float4(r.An, r.Ap, r.t, r.invK);
+                sr.c = make_float4(r.r, r.g, r.b, 1.0f - r.t);
                 s_ref[j] = centre_offsets<TW, TH>(r, W64, ox, oy);
                 if constexpr (DET) {
                     for (int row = 0; row < 4 * NW; ++row)
@@ -582,102 +644,158 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
                     s_pq[j] = det.pair_offsets[jr] + ((uint32_t)ty - ty0) * (tx1 - tx0 + 1u) + ((uint32_t)tx - tx0);
                 } else {
 #pragma unroll
-                    for (int k = 0; k < kG; ++k) s_g[j][k] = 0.0;
+                    for (int k = 0; k < kG; ++k) sr.g[k] = 0.0;
                 }
-            } else if (lane < 32 && j < BATCH) {  // padding read by quarters with nothing left: alpha = 0
-                s_w[j] = s_o[j] = s_c[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-                for (int bk = 0; bk < NB; ++bk) s_u[bk][j] = make_float2(0.0f, 0.0f);
             }
-            if (32 * w < BATCH) {  // this wave's word of the quarter masks
+            if (PER * w < BATCH) {  // this wave's words of the quarter masks
 #pragma unroll
                 for (int bq = 0; bq < 4 * NB; ++bq) {
                     const uint64_t m = __ballot((live >> bq) & 1u);
-                    if (lane == 0) s_qm[bq >> 2][bq & 3][w] = __builtin_bitreverse32((uint32_t)m);
+                    if (lane < PER / 32) s_qm[bq >> 2][bq & 3][PER / 32 * w + lane] = (uint32_t)(lane ? m >> 32 : m);
                 }
             }
         }
         __syncthreads();
-        // each quarter walks, back to front, the entries some pixel of it blended
-        // in the forward (those before its last contributor: later records are
-        // not written); the four quarters of a wave step together
+        // the entries each quarter of this wave's block walks: those some pixel
+        // of it blended in the forward, before its last contributor (later
+        // records are not written); two quarters at a time, one lane per
+        // entry, the rest of the list filled with the dead record
         const uint32_t base = lo - rg.x;  // list position of entry 0
-        const int lim = qm > base ? (int)min(qm - base, (uint32_t)cnt) : 0;
-        for (int k = (cnt - 1) >> 5; k >= 0; --k) {
-            uint32_t m = s_qm[w][q][k];
-            const int lk = lim - 32 * k;  // entries 32 k + i, i < lk, come before the last contributor
-            m &= lk >= 32 ? ~0u : (lk <= 0 ? 0u : ~((1u << (32 - lk)) - 1u));
-            for (;;) {
-                // lane masks straight from the compares (no per-lane booleans
-                // carried across the branches)
-                const uint64_t hm = __ballot(m != 0u);
-                if (hm == 0ull) break;
-                const bool has = m != 0u;
-                const int j = 32 * k + 31 - __builtin_ctz(m | 0x80000000u);  // entry 32 k when nothing is left
-                m &= m - 1u;
-                const uint64_t rm = __ballot(base + (uint32_t)j < last);
-                const float4 Wv = s_w[j], Ov = s_o[j];
-                const float2 U = s_u[w][j];
-                const uint64_t tm = __ballot(Ov.z > 0.0f);
-                const bool interp = Ov.z > 0.0f;
-                AlphaEval e;
-                eval_alpha(Wv, Ov, U, lx, ly, interp, e);
-                const uint64_t irm = hm & rm;
-                const uint64_t cm = irm & __ballot(e.alpha >= kAlphaMin);
+        int steps = 0;                    // entries of the longest list
+#pragma unroll
+        for (int k = 0; k < 4 * LIST / 2; k += 64)
+            if (k + 64 <= 4 * LIST / 2 || k + lane < 4 * LIST / 2)
+                reinterpret_cast<uint32_t *>(&s_list[w][0][0])[k + lane] = kDead * 0x10001u;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int qa = 2 * h + (lane >> 5), i = lane & 31;
+            const uint32_t qma = (uint32_t)__builtin_amdgcn_readlane((int)qm, 8 * h),
+                           qmb = (uint32_t)__builtin_amdgcn_readlane((int)qm, 8 * h + 4);
+            const uint32_t lastq = lane < 32 ? qma : qmb;
+            const int limq = lastq > base ? (int)min(lastq - base, (uint32_t)cnt) : 0;
+            int n = 0;
+#pragma unroll
+            for (int k = NQW - 1; k >= 0; --k) {
+                const int lk = limq - 32 * k;  // entries 32 k + i, i < lk, come before the last contributor
+                uint32_t m = 32 * k < cnt ? s_qm[w][qa][k] : 0u;
+                m &= lk >= 32 ? ~0u : (lk <= 0 ? 0u : (1u << lk) - 1u);
+                if ((m >> i) & 1u) s_list[w][qa][n + __popc((m >> i) >> 1)] = (uint16_t)((32 * k + i) * kRec);
+                n += __popc(m);
+            }
+            steps = max(steps, max(__builtin_amdgcn_readlane(n, 0), __builtin_amdgcn_readlane(n, 32)));
+        }
+        steps = __builtin_amdgcn_readfirstlane(steps);
+        __builtin_amdgcn_wave_barrier();  // the lists are this wave's own
+        // each quarter walks its list, the four quarters of the wave together,
+        // two entries at a time
+        const uint32_t *walk = reinterpret_cast<const uint32_t *>(&s_list[w][q][0]);
+        const uint32_t lim = (uint32_t)min((int)(last - min(last, base)), cnt) * kRec;  // the pixel's last contributor
+        uint32_t two = walk[0];
+        for (int p = 0; p < steps; p += 2) {
+            const uint32_t off[2] = {two & 0xFFFFu, two >> 16};
+            two = walk[(p >> 1) + 1];
+            float4 Ov[2];
+            float G[2], al[2], anr[2], apr[2], omt[2], omap[2], qp[2], cg[2];
+            bool con[2];
+            uint64_t tm[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const Rec &r = rec_at(off[s]);
+                const float4 Wv = r.w, Cc = r.c;
+                Ov[s] = r.o;
+                omt[s] = Cc.w;
+                cg[s] = fmaf(Cc.z, g2, fmaf(Cc.y, g1, Cc.x * g0));
+                tm[s] = __builtin_amdgcn_ballot_w64(Ov[s].z > 0.0f);
+                G[s] = eval_gauss(Wv, r.u[w], lx, ly);
+                anr[s] = Ov[s].x * G[s];
+                al[s] = fminf(anr[s], kAlphaMax);
+                apr[s] = 0.0f;
+                omap[s] = qp[s] = 1.0f;
+            }
+            const bool any_t = (tm[0] | tm[1]) != 0ull;  // with t = 0 the interpolated form gives a_n exactly
+            if (any_t) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    apr[s] = Ov[s].y * G[s];
+                    omap[s] = 1.0f - fminf(apr[s], kAlphaMax);
+                    al[s] = eval_interp(al[s], omap[s], omt[s], Ov[s].z, Ov[s].w, qp[s]);
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                // lane masks straight from the compares
+                const uint64_t irm = __builtin_amdgcn_ballot_w64(off[s] < lim);
                 n_eval += (uint32_t)__popcll(irm);
-                n_eval_t += (uint32_t)__popcll(irm & tm);
-                if (cm == 0ull) continue;
-                const bool contrib = has && base + (uint32_t)j < last && e.alpha >= kAlphaMin;
-                n_con += (uint32_t)__popcll(cm);
-                // every lane runs the update; a non-contributing lane has a = 0 and
-                // dL/dalpha = 0, which leaves T and R as they are and all slots 0
-                const float4 Cc = s_c[j];
-                const float a = contrib ? e.alpha : 0.0f;
+                n_eval_t += (uint32_t)__popcll(irm & tm[s]);
+                n_con += (uint32_t)__popcll(irm & __builtin_amdgcn_ballot_w64(al[s] >= kAlphaMin));
+                con[s] = off[s] < lim && al[s] >= kAlphaMin;
+            }
+            float van[2], vap[2], aT[2], dal[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                // every lane runs the update; with a = 0 it leaves T and R as they are
+                const float a = con[s] ? al[s] : 0.0f;
                 T = T * __builtin_amdgcn_rcpf(1.0f - a);
-                const float dal_raw = T * ((Cc.x - R0) * g0 + (Cc.y - R1) * g1 + (Cc.z - R2) * g2);
-                const float dal = contrib ? dal_raw : 0.0f;
-                const float aT = a * T;
-                R0 = fmaf(a, Cc.x - R0, R0);
-                R1 = fmaf(a, Cc.y - R1, R1);
-                R2 = fmaf(a, Cc.z - R2, R2);
-                float dan = dal, dap = 0.0f, dtv = 0.0f;
-                if (interp) {
-                    dan = (1.0f - Ov.z) * dal;
-                    const float dapr = Ov.z * dal;
-                    if constexpr (DT) dtv = (e.apr - e.an) * dal;
-                    // d apr / d a_p = (1/K) (1 - a_p)^(1/K - 1) = (1/K) q / (1 - a_p)
-                    dap = dapr * Ov.w * (e.q * __builtin_amdgcn_rcpf(1.0f - e.ap));
+                const float df = cg[s] - Rg;
+                dal[s] = T * df;
+                aT[s] = a * T;
+                Rg = fmaf(a, df, Rg);
+            }
+            // dL/da_n, dL/da_p (zero through the clamps), times G
+            if (any_t) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    // d alpha' / d a_p = (1/K) (1 - a_p)^(1/K - 1) = (1/K) q / (1 - a_p)
+                    const float dap = (Ov[s].z * dal[s]) * Ov[s].w * (qp[s] * __builtin_amdgcn_rcpf(omap[s]));
+                    van[s] = G[s] * (con[s] && !(anr[s] > kAlphaMax) ? omt[s] * dal[s] : 0.0f);
+                    vap[s] = G[s] * (con[s] && !(apr[s] > kAlphaMax) ? dap : 0.0f);
                 }
-                const float dan_c = e.cn ? 0.0f : dan, dap_c = e.cp ? 0.0f : dap;
-                const float h = e.G * (dan_c * Ov.x + dap_c * Ov.y);  // G dL/dG
-                const float v1 = fmaf(lyt, Wv.y, lxt * Wv.x), v2 = fmaf(lyt, Wv.w, lxt * Wv.z);
-                // the six pairs of the slots, as the first halving takes them
-                const float pa = b3 ? v2 : v1, pb = b3 ? v1 : v2;
-                const float ha = h * pa, hb = h * pb, hab = ha * pb;
-                float S1[6], S2[6];
-                S1[0] = ha;                      // P'_1, P'_2
-                S2[0] = hb;
-                S1[1] = ha * pa;                 // Q'_11, Q'_22
-                S2[1] = hb * pb;
-                S1[2] = b3 ? h : hab;            // Q'_12, S
-                S2[2] = b3 ? hab : h;
-                S1[3] = e.G * (b3 ? dap_c : dan_c);  // dL/dA_n, dL/dA_p
-                S2[3] = e.G * (b3 ? dan_c : dap_c);
-                S1[4] = aT * ga;                 // colour 0, 1
-                S2[4] = aT * gb;
-                if constexpr (DT) {              // colour 2, dL/dt
-                    const float c2 = aT * g2;
-                    S1[5] = b3 ? dtv : c2;
-                    S2[5] = b3 ? c2 : dtv;
-                } else {
-                    S1[5] = aT * g2a;
-                    S2[5] = aT * g2b;
+            } else {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    van[s] = G[s] * (con[s] && !(anr[s] > kAlphaMax) ? dal[s] : 0.0f);
+                    vap[s] = 0.0f;
                 }
-                const float tot = row_reduce12(S1, S2, lane);
-                if constexpr (DET) {
-                    if (has && slot >= 0) s_gr[4 * w + q][j][slot] = tot;
-                } else {
-                    if (has && slot >= 0 && tot != 0.0f) unsafeAtomicAdd(&s_g[j][slot], (double)tot);
+            }
+            const float vh0 = fmaf(van[0], Ov[0].x, vap[0] * Ov[0].y);  // G dL/dG
+            const float vh1 = fmaf(van[1], Ov[1].x, vap[1] * Ov[1].y);
+            // rows 0 / 1 of 16 lanes: S, S y, S y^2, colour 0 / colour 1, colour 2,
+            // dL/dA_n, dL/dA_p of the first step; rows 2 / 3 of the second
+            const float D0 = fold16(fold32(vh0, vh1), fold32(aT[0] * g1, aT[1] * g1));
+            const float D1 = fold16(fold32(vh0 * yl, vh1 * yl), fold32(aT[0] * g2, aT[1] * g2));
+            const float D2 = fold16(fold32(vh0 * yl2, vh1 * yl2), fold32(van[0], van[1]));
+            const float D3 = fold16(fold32(aT[0] * g0, aT[1] * g0), fold32(vap[0], vap[1]));
+            const float Sy = fmaf(yq, D0, D1);
+            const float Syy = fmaf(yq, Sy + D1, D2);
+            const float f0 = quad_dot(D0, cw), f1 = quad_dot(Sy, cw), f2 = quad_sum(Syy), f3 = quad_sum(D3);
+            float va = qx == 3 ? f3 : f0, vb = qx == 2 ? f2 : f1;
+            // formed by every lane here, where the lane exchanges fold into the
+            // arithmetic, not under the masks of the adds below
+            asm volatile("" : "+v"(va), "+v"(vb));
+            const uint32_t os = lane & 32 ? off[1] : off[0];
+            if constexpr (DET) {
+                if (os != kDead) {
+                    float *o = s_gr[4 * w + q][os / kRec];
+                    if (slot_a != 11) o[slot_a] = va;
+                    if (slot_b != 11) o[slot_b] = vb;
+                }
+            } else {  // past a list's end: zeros, to the dead record
+                if (slot_a != 11) unsafeAtomicAdd(reinterpret_cast<double *>(s_rec + os + off_a), (double)va);
+                if (slot_b != 11) unsafeAtomicAdd(reinterpret_cast<double *>(s_rec + os + off_b), (double)vb);
+            }
+            if constexpr (DT) {  // dL/dt through alpha: (a'_p - a_n) dL/dalpha
+                float d[2];
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+                    d[s] = con[s] && Ov[s].z > 0.0f ? ((1.0f - qp[s]) - fminf(anr[s], kAlphaMax)) * dal[s] : 0.0f;
+                float f = fold32(d[0], d[1]);
+                f = quad_sum(fold16(f, f));
+                if (qx == 0 && low) {
+                    if constexpr (DET) {
+                        if (os != kDead) s_gr[4 * w + q][os / kRec][11] = f;
+                    } else {
+                        unsafeAtomicAdd(&rec_at(os).g[11], (double)f);
+                    }
                 }
             }
         }
@@ -685,29 +803,34 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
         // flush: one lane per splat turns the tile's partial sums into the
         // 11 screen-space terms (FP64); then the terms of all splats go out
         // as consecutive atomics, row by row
-        if (const int j = 32 * w + lane; lane < 32 && j < cnt) {  // wave w: entries 32 w .. 32 w + 31
-            double gd[kG];
+        if (const int j = PER * w + lane; lane < PER && j < cnt) {  // the entries this wave staged
+            Rec &sr = rec_at(kRec * (uint32_t)j);
+            double g[kG];
             if constexpr (DET) {
 #pragma unroll
-                for (int k = 0; k < kG; ++k) gd[k] = 0.0;
-                for (int row = 0; row < 4 * NW; ++row)  // rows in a fixed order
+                for (int k = 0; k < kG; ++k) g[k] = 0.0;
+                for (int row = 0; row < 4 * NW; ++row)  // quarters in a fixed order
 #pragma unroll
-                    for (int k = 0; k < kG; ++k) gd[k] += (double)s_gr[row][j][k];
+                    for (int k = 0; k < kG; ++k) g[k] += (double)s_gr[row][j][k];
             } else {
 #pragma unroll
-                for (int k = 0; k < kG; ++k) gd[k] = s_g[j][k];
+                for (int k = 0; k < kG; ++k) g[k] = sr.g[k];
             }
-            const double *g = gd;
-            // moments about the splat's centre from those about the tile's
+            // moments on the splat's axes about the tile's centre, then about the splat's
+            const float4 W = sr.w;
+            const double wx = W.x, wy = W.y, wz = W.z, ww = W.w;
             const double2 cr = s_ref[j];
             const double S = g[5];
-            const double P1 = g[0], P2 = g[1], Q11 = g[2], Q22 = g[3], Q12 = g[4];
+            const double P1 = wx * g[0] + wy * g[1], P2 = wz * g[0] + ww * g[1];
+            const double Q11 = wx * wx * g[2] + 2.0 * wx * wy * g[4] + wy * wy * g[3];
+            const double Q22 = wz * wz * g[2] + 2.0 * wz * ww * g[4] + ww * ww * g[3];
+            const double Q12 = wx * wz * g[2] + (wx * ww + wy * wz) * g[4] + wy * ww * g[3];
             const double P[2] = {P1 + cr.x * S, P2 + cr.y * S};
             const double Q[3] = {Q11 + 2.0 * cr.x * P1 + cr.x * cr.x * S,
                                  Q12 + cr.x * P2 + cr.y * P1 + cr.x * cr.y * S,
                                  Q22 + 2.0 * cr.y * P2 + cr.y * cr.y * S};
             double sc[5];
-            screen_grad(s_w[j], P, Q, sc);
+            screen_grad(W, P, Q, sc);
             double dd[11];
 #pragma unroll
             for (int k = 0; k < 5; ++k) dd[k] = sc[k];
@@ -719,14 +842,14 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
                 for (int k = 0; k < 11; ++k) o[k] = dd[k];
             } else {
 #pragma unroll
-                for (int k = 0; k < 11; ++k) s_d[j * 11 + k] = dd[k];
+                for (int k = 0; k < 11; ++k) sr.g[k] = dd[k];
             }
         }
         __syncthreads();
         if constexpr (!DET) {
             for (int idx = threadIdx.x; idx < cnt * 11; idx += NT) {
-                const double val = s_d[idx];
                 const int j = idx / 11, k = idx - 11 * j;
+                const double val = rec_at(kRec * (uint32_t)j).g[k];
                 if (val != 0.0) unsafeAtomicAdd(&sgrad[(size_t)s_id[j] * kG + k], val);
             }
             __syncthreads();
@@ -849,6 +972,13 @@ void launch_blend_t(const DevView *views, int nv, uint32_t n_tiles, const uint32
     }
 }
 
+// Splats the backward stages per batch.
+constexpr int bwd_batch(int tw, int th, int batch)
+{
+    const int nw = tw * th / 64;
+    return std::min(batch, 32 * nw);
+}
+
 template <int TW, int TH, int B, bool DT>
 void launch_blend_bwd_dt(const DevView *views, int nv, uint32_t n_tiles, const uint32_t *order, const uint2 *ranges,
                          const uint32_t *pair_vals, const SplatRec *recs, const double4 *axes, const float *T_final,
@@ -884,8 +1014,7 @@ void launch_blend_bwd_t(const DevView *views, int nv, uint32_t n_tiles, const ui
     // the backward stages at most 32 splats per wave and step: its LDS holds
     // the FP32 partial sums and the FP64 flushed terms of every staged
     // splat, and a smaller footprint keeps more tiles resident per CU
-    constexpr int BMAX = 32 * (TW * TH / 64);
-    constexpr int B = BATCH < BMAX ? BATCH : BMAX;
+    constexpr int B = bwd_batch(TW, TH, BATCH);
     if (want_dt)
         launch_blend_bwd_dt<TW, TH, B, true>(views, nv, n_tiles, order, ranges, pair_vals, recs, axes, T_final,
                                              n_last, qbits, qstride, vis_rank, sgrad, det, wstats, persist, queue, st);
@@ -903,8 +1032,7 @@ void launch_blend_bwd_t(const DevView *views, int nv, uint32_t n_tiles, const ui
 template <int TW, int TH, int BATCH>
 void prepare_t()
 {
-    constexpr int BMAX = 32 * (TW * TH / 64);
-    constexpr int B = BATCH < BMAX ? BATCH : BMAX;
+    constexpr int B = bwd_batch(TW, TH, BATCH);
     (void)resident_grid(k_blend<TW, TH, BATCH, true>, TW * TH);
     (void)resident_grid(k_blend_bwd<TW, TH, B, true, true, false>, TW * TH);
     (void)resident_grid(k_blend_bwd<TW, TH, B, false, true, false>, TW * TH);
