@@ -409,7 +409,8 @@ hgs_status hgs_interior(hgs_ctx *ctx, int32_t *ids, int64_t cap, int64_t *count)
 /* Tuning knobs of the blend stage and its backward (chosen by the
  * autotuner): tile edge tile_w x tile_h in {8x8, 16x8, 16x16, 32x16},
  * splats staged per batch (a multiple of 64 up to 1024; 0 = one per
- * thread), and the work distribution: persistent = 0 launches one workgroup
+ * thread; the kernels stage at most one per thread at a time), and the work
+ * distribution: persistent = 0 launches one workgroup
  * per tile, 1 a persistent grid of as many workgroups as the device holds
  * at once, which take tiles (longest lists first) from a device-side queue
  * until none is left.  Changing them keeps images bit-identical.

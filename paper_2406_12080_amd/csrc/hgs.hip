@@ -30,13 +30,13 @@ constexpr int kStageRing = 4;     // pinned staging slots for the view copies
 struct RenderKey {
     int nv = -1;
     std::vector<int> wh;
-    int tw = 0, th = 0, batch = 0;
+    int tw = 0, th = 0;
     bool persist = false;
     uint64_t layout = 0;
     bool profiled = false;
     bool operator==(const RenderKey &o) const
     {
-        return nv == o.nv && wh == o.wh && tw == o.tw && th == o.th && batch == o.batch && persist == o.persist &&
+        return nv == o.nv && wh == o.wh && tw == o.tw && th == o.th && persist == o.persist &&
                layout == o.layout && profiled == o.profiled;
     }
 };
@@ -71,7 +71,7 @@ struct hgs_ctx {
     bool use_bound = false;
     uint64_t param_gen = 1;
 
-    int tile_w = 16, tile_h = 16, batch = 0;
+    int tile_w = 16, tile_h = 16;
     bool persist = false;  // blend over a persistent grid and a device-side tile queue
     uint32_t *queue = nullptr;  // [0] forward, [1] backward: next tile slot
     double *l1_partial = nullptr;  // per-block partial sums of the L1 loss
@@ -140,7 +140,7 @@ struct hgs_ctx {
     size_t last_pix = 0;
     bool pairs_in_scratch = false;
     bool g_pairs_in_scratch = false;
-    int r_tw = 16, r_th = 16, r_batch = 0;
+    int r_tw = 16, r_th = 16;
     bool r_persist = false;
 
     // graph
@@ -491,7 +491,7 @@ void enqueue_blend(hgs_ctx *ctx, int nv, uint32_t n_tiles, hipStream_t st)
     const uint32_t *vals = ctx->pairs_in_scratch ? ctx->v2 : ctx->pvals;
     launch_blend(ctx->views_dev, nv, n_tiles, ctx->tile_order, ctx->ranges, vals, ctx->recs, ctx->axes, ctx->T_final,
                  ctx->n_last, ctx->n_blend, ctx->qbits, ctx->pair_cap, ctx->wstats, ctx->ctr, ctx->tile_w,
-                 ctx->tile_h, ctx->batch, ctx->persist, ctx->queue, st);
+                 ctx->tile_h, ctx->persist, ctx->queue, st);
 }
 
 void enqueue_forward(hgs_ctx *ctx, int nv, uint32_t n_tiles, hipStream_t st, hipEvent_t *ev, bool with_blend)
@@ -618,7 +618,7 @@ void enqueue_backward(hgs_ctx *ctx, int nv, const hgs_grads *out, const AdamRows
         launch_blend_backward(ctx->views_dev, nv, ctx->last_tiles, ctx->tile_order, ctx->ranges, vals, ctx->recs,
                               ctx->axes, ctx->T_final, ctx->n_last, ctx->qbits, ctx->pair_cap, ctx->vis_rank,
                               ctx->sgrad, det ? &da : nullptr, ctx->wstats, ctx->ctr, ctx->r_tw, ctx->r_th,
-                              ctx->r_batch, out && out->dt != nullptr, ctx->r_persist, ctx->queue + 1, st);
+                              out && out->dt != nullptr, ctx->r_persist, ctx->queue + 1, st);
         if (det)
             launch_det_sum(ctx->part, ctx->pair_offsets, ctx->svals, ctx->vis_rank, &ctx->ctr->vis_total,
                            ctx->cut_cap, &ctx->ctr->pair_total, ctx->pair_cap, ctx->sgrad, st);
@@ -861,7 +861,6 @@ hgs_status hgs_set_tuning(hgs_ctx *ctx, int32_t tile_w, int32_t tile_h, int32_t 
     if (persistent != 0 && persistent != 1) return fail(ctx, HGS_ERR_INVALID_ARG, "persistent must be 0 or 1");
     ctx->tile_w = tile_w;
     ctx->tile_h = tile_h;
-    ctx->batch = batch == tile_w * tile_h ? 0 : batch;
     ctx->persist = persistent != 0;
     ctx->have_render = false;
     return HGS_OK;
@@ -1394,7 +1393,7 @@ hgs_status hgs_render(hgs_ctx *ctx, const hgs_view *views, int32_t n_views, floa
     hgs_status s;
     if ((s = setup_views(ctx, views, n_views, out_rgb, n_tiles, n_pix))) return s;
     if ((s = ensure_fixed(ctx, n_views, n_tiles, n_pix))) return s;
-    if (ctx->persist) blend_prepare(ctx->tile_w, ctx->tile_h, ctx->batch);
+    if (ctx->persist) blend_prepare(ctx->tile_w, ctx->tile_h);
     const bool timed = stats && stats->ms[0] < 0.0f && n_views == 1;
     if (ctx->cut_cap == 0) {
         const uint64_t guess = std::min<uint64_t>((uint64_t)n_views * (uint64_t)std::min<int64_t>(ctx->n_leaves, 1 << 21),
@@ -1425,7 +1424,6 @@ hgs_status hgs_render(hgs_ctx *ctx, const hgs_view *views, int32_t n_views, floa
             }
             key.tw = ctx->tile_w;
             key.th = ctx->tile_h;
-            key.batch = ctx->batch;
             key.persist = ctx->persist;
             key.layout = ctx->layout_gen * 1000003ull + ctx->param_gen;
             key.profiled = ctx->profile;
@@ -1488,7 +1486,6 @@ hgs_status hgs_render(hgs_ctx *ctx, const hgs_view *views, int32_t n_views, floa
         ctx->last_pix = n_pix;
         ctx->r_tw = ctx->tile_w;
         ctx->r_th = ctx->tile_h;
-        ctx->r_batch = ctx->batch;
         ctx->r_persist = ctx->persist;
         ctx->last_graphed = n_views > 1 && !ctx->profile;
         if (stats) {

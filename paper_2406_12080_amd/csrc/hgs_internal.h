@@ -279,11 +279,11 @@ void launch_init(Counters *ctr, uint32_t *tile_hist, uint2 *ranges, uint32_t n_t
 constexpr int kTileBins = 256;
 void launch_tile_order(const uint2 *ranges, uint32_t n_tiles, uint32_t *tile_hist, uint32_t *order, hipStream_t st);
 
-// blend (tile_w x tile_h pixels per workgroup, `batch` records staged per step)
+// blend (tile_w x tile_h pixels per workgroup)
 bool blend_supported(int tw, int th, int batch);
 // Looks up the persistent grids of this configuration (device attributes
 // and occupancy), so that no such query runs while a launch is captured.
-void blend_prepare(int tw, int th, int batch);
+void blend_prepare(int tw, int th);
 // persist: a grid of the chip's resident workgroups takes tile slots from
 // the device-side queue (*queue, cleared by the launch sequence first)
 // instead of one workgroup per tile.
@@ -315,7 +315,7 @@ constexpr int kMaxBlocks = 8;
 void launch_blend(const DevView *views, int nv, uint32_t n_tiles, const uint32_t *tile_order, const uint2 *ranges,
                   const uint32_t *pair_vals,
                   const SplatRec *recs, const double4 *axes, float *T_final, uint32_t *n_last, uint32_t *n_blend,
-                  uint8_t *qbits, uint32_t qstride, uint4 *wstats, Counters *ctr, int tw, int th, int batch,
+                  uint8_t *qbits, uint32_t qstride, uint4 *wstats, Counters *ctr, int tw, int th,
                   bool persist, uint32_t *queue, hipStream_t st);
 
 // ---------------------------------------------------- hierarchy generation
@@ -386,7 +386,7 @@ void launch_blend_backward(const DevView *views, int nv, uint32_t n_tiles, const
                            const uint32_t *pair_vals, const SplatRec *recs, const double4 *axes, const float *T_final,
                            const uint32_t *n_last, const uint8_t *qbits, uint32_t qstride, const uint32_t *vis_rank,
                            double *sgrad, const DetArgs *det, uint4 *wstats,
-                           Counters *ctr, int tw, int th, int batch, bool want_dt, bool persist, uint32_t *queue,
+                           Counters *ctr, int tw, int th, bool want_dt, bool persist, uint32_t *queue,
                            hipStream_t st);
 // optimiser step (Adam) over the interior nodes of one parameter group
 // (0 mean, 1 scale, 2 rotation, 3 opacity, 4 SH); bc1 = 1 / (1 - beta1^t),

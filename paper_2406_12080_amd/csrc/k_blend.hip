@@ -3,11 +3,11 @@
 // One workgroup per tile of TW x TH pixels; each 64-lane wave owns an 8x8
 // sub-tile, one lane per pixel, and each row of 16 lanes one 4x4 quarter of
 // it.  The tile's splats (sorted front to back) are staged through LDS in
-// batches of BATCH records, each with one bit per quarter telling whether
-// any pixel of the quarter can reach alpha = 1/255.  Every quarter walks the
-// batch in order over the splats it may take only (a small splat touches
-// one or two of them), so that the four quarters of a wave step through
-// different splats together.  Per pixel and splat (Sec. 3 Eq. (alpha) with the
+// batches of one record per thread, each with one bit per quarter telling
+// whether any pixel of the quarter can reach alpha = 1/255.  Every quarter
+// walks a list of the splats it may take only (a small splat touches one or
+// two of them), so that the four quarters of a wave step through different
+// splats together.  Per pixel and splat (Sec. 3 Eq. (alpha) with the
 // projected Gaussian G; Eq. (alphap) generalised to K children, Sec. 5.2;
 // the weight t of Eq. (t_interp) as the parent's weight; clamp of Sec. 7.3):
 //   G     = exp(-q/2),  q = d^T conic d  (d = pixel centre - mean), evaluated
@@ -20,8 +20,8 @@
 // The backward walks each tile back to front from the final transmittance
 // and the index of the last contributor of each pixel, recovering the
 // transmittance in front of every splat by dividing by (1 - alpha) (no
-// per-pixel lists), reduces each splat's gradient over rows of 16 lanes with
-// DPP exchanges and over the rows and waves of the tile in LDS (FP64 atomics), and
+// per-pixel lists), reduces each splat's gradient over the pixels of a quarter
+// by lane exchanges and over the quarters of the tile in LDS (FP64 atomics), and
 // adds it once per tile, in FP64, to the splat's screen-space gradient.
 #include <algorithm>
 #include <cstddef>
@@ -52,13 +52,18 @@ __device__ __forceinline__ void block_offsets(const SplatRec &r, const double4 &
 // Identical arithmetic in forward and backward (explicit FMAs, no other
 // contraction), so that the backward reproduces the forward's decisions bit
 // for bit.
+__device__ __forceinline__ float gauss_of(float u1, float u2)
+{
+#pragma clang fp contract(off)
+    return __builtin_amdgcn_exp2f(-fmaf(u1, u1, u2 * u2));
+}
+
 __device__ __forceinline__ float eval_gauss(const float4 &W, float2 c, float lx, float ly)
 {
 #pragma clang fp contract(off)
     const float u1 = fmaf(ly, W.y, fmaf(lx, W.x, c.x));
     const float u2 = fmaf(ly, W.w, fmaf(lx, W.z, c.y));
-    const float s = fmaf(u1, u1, u2 * u2);
-    return __builtin_amdgcn_exp2f(-s);
+    return gauss_of(u1, u2);
 }
 
 // alpha of an interpolated splat from a_n, 1 - a_p, 1 - t, t and 1/K; q = (1 -
@@ -126,26 +131,33 @@ __device__ __forceinline__ int view_of_tile(const DevView *views, int nv, uint32
     return lo;
 }
 
-// Staged copy of one splat for one tile.
-struct Staged {
-    float4 w, o, c;
-    float2 u[8];
-    uint32_t live;  // bit 4 bk + q: quarter q of block bk may take the splat
+// A splat staged for one tile by the forward.
+template <int NB>
+struct __align__(16) FwdStaged {
+    float4 w;      // axes
+    float4 o;      // A_n, A_p, t, 1/K
+    float4 c;      // colour, 1 - t
+    float2 u[NB];  // per 8x8 block: the offsets of its corner pixel on the axes
+    static constexpr uint32_t kStride = 16u * ((uint32_t)(3 + (NB + 1) / 2) | 1u);  // odd units: banks apart
 };
 
+// Whether the quarters of the block may take the staged splat: bit 4 bk + q.
 template <int NB, int SX>
-__device__ __forceinline__ void stage_one(const SplatRec &r, const double4 &W64, int ox, int oy, Staged &st)
+__device__ __forceinline__ uint32_t stage_fwd(const SplatRec &r, const double4 &W64, int ox, int oy,
+                                              FwdStaged<NB> &st)
 {
-    st.w = make_float4((float)W64.x, (float)W64.y, (float)W64.z, (float)W64.w);
+    const float4 W = make_float4((float)W64.x, (float)W64.y, (float)W64.z, (float)W64.w);
+    float2 u[8];
+    st.w = W;
     st.o = make_float4(r.An, r.Ap, r.t, r.invK);
-    st.c = make_float4(r.r, r.g, r.b, 0.0f);
+    st.c = make_float4(r.r, r.g, r.b, 1.0f - r.t);
 #pragma unroll
     for (int bk = 0; bk < NB; ++bk) {
         float c1, c2, d0, d1;
         block_offsets(r, W64, ox + (bk % SX) * 8, oy + (bk / SX) * 8, c1, c2, d0, d1);
-        st.u[bk] = make_float2(c1, c2);
+        st.u[bk] = u[bk] = make_float2(c1, c2);
     }
-    st.live = quarter_live<NB>(st.w, st.u, r.t > 0.0f ? fmaxf(r.An, r.Ap) : r.An);
+    return quarter_live<NB>(W, u, r.t > 0.0f ? fmaxf(r.An, r.Ap) : r.An);
 }
 
 // Per-wave work counts (uint4 per wave, plain stores) are summed by
@@ -169,30 +181,35 @@ __device__ __forceinline__ uint32_t next_run(uint32_t *queue, uint32_t chunk, ui
     return slot;
 }
 
-// Stores the quarter records of one 32-entry word of the batch: `cw` holds,
-// per lane, the entries of the word the lane's pixel blended (or stopped
-// at); OR over each
-// row of 16 lanes (DPP partners l ^ 8, l ^ 7, l ^ 2, l ^ 1) gives the
-// quarter's entries, and lane i writes the byte of entry i (bit q: quarter q
-// blended it) for the n entries of the word, at qbits[p0 + i] (the wave's
-// block's plane of the records).  All lanes take part.
-__device__ __forceinline__ void record_word(uint8_t *__restrict__ qbits, uint32_t cw, uint32_t p0, int n,
-                                            int lane)
+// OR over each row of 16 lanes (DPP partners l ^ 8, l ^ 7, l ^ 2, l ^ 1).
+__device__ __forceinline__ uint32_t row_or(uint32_t v)
 {
-    cw |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)cw, 0x128, 0xF, 0xF, true);
-    cw |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)cw, 0x141, 0xF, 0xF, true);
-    cw |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)cw, 0x4E, 0xF, 0xF, true);
-    cw |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)cw, 0xB1, 0xF, 0xF, true);
-    const uint32_t r0 = __builtin_amdgcn_readlane(cw, 0), r1 = __builtin_amdgcn_readlane(cw, 16);
-    const uint32_t r2 = __builtin_amdgcn_readlane(cw, 32), r3 = __builtin_amdgcn_readlane(cw, 48);
-    if (lane < n) {
-        const uint32_t b = ((r0 >> lane) & 1u) | (((r1 >> lane) & 1u) << 1) | (((r2 >> lane) & 1u) << 2) |
-                           (((r3 >> lane) & 1u) << 3);
-        qbits[p0 + (uint32_t)lane] = (uint8_t)b;
-    }
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+    return v;
 }
 
-template <int TW, int TH, int BATCH>
+// The forward of one tile.  Bound by VALU issue where many tiles are resident,
+// by the latency of one step where few are (a tile's pixels walk up to
+// thousands of splats in turn).  A quarter walks a list of the entries it may
+// take, made per chunk of 128 staged entries, two entries at a time: the two
+// alphas are independent, and the list costs one read where taking apart a
+// bit mask cost seven instructions a step.
+//
+// An FP32 multiply, add or FMA on vector registers issues in 2 cycles here, a
+// compare, select, minimum or lane exchange in 4, exp2 and log2 in 8: what a
+// step keeps per pixel is therefore its colour, its transmittance and one
+// history bit (an add with carry), from which count and last contributor
+// follow every 32 entries, and which lanes still run is a scalar mask.  45
+// instructions a step in place of 61.  32 views of 1920x1080 over 30M leaves:
+// 16x8 tiles 5.1 -> 4.3 ms, 8x8 4.4 -> 4.1, 16x16 6.6 -> 4.7, 32x16 14.2 ->
+// 7.4; one view with 16x16 tiles 561 -> 460 us, of 1M leaves 288 -> 236 us.
+// (Records read by one ds_read_b32 a lane and taken from each other's
+// registers by row_newbcast leave the LDS nearly idle but cost a 4-cycle move
+// for every operand of an FMA: 5.4 ms.)
+template <int TW, int TH>
 __device__ __forceinline__ void blend_tile(const DevView *__restrict__ views, int nv,
                                            const uint32_t *__restrict__ tile_order,
                                            const uint2 *__restrict__ ranges, const uint32_t *__restrict__ pair_vals,
@@ -205,127 +222,180 @@ __device__ __forceinline__ void blend_tile(const DevView *__restrict__ views, in
     constexpr int NW = NT / 64;
     constexpr int SX = TW / 8;
     constexpr int NB = (TW / 8) * (TH / 8);
-    constexpr int PER = BATCH / NT;  // records staged per thread and batch
-    static_assert(BATCH % NT == 0 && BATCH % 64 == 0 && NB <= 8, "tile/batch combination");
-    __shared__ float4 s_w[BATCH], s_o[BATCH], s_c[BATCH];
-    __shared__ float2 s_u[NB][BATCH];
+    constexpr int BATCH = NT;  // records staged at a time: one per thread
+    constexpr int CH = BATCH < 128 ? BATCH : 128;  // entries per list
+    constexpr int LIST = CH + 4;
+    static_assert(BATCH % CH == 0 && CH % 64 == 0 && NB <= 8, "tile");
+    using Rec = FwdStaged<NB>;
+    constexpr uint32_t kRec = Rec::kStride, kDead = kRec * BATCH;
+    static_assert(sizeof(Rec) <= kRec && kDead < 65536, "a list entry is a 16-bit byte offset");
+    // the last record has alpha 0 everywhere: for a quarter past its list's end
+    __shared__ __align__(16) unsigned char s_rec[kRec * (BATCH + 1)];
     __shared__ uint32_t s_qm[NB][4][BATCH / 32];  // bit b of word k: quarter q of block bk may take entry 32 k + b
+    __shared__ __align__(4) uint16_t s_list[NB][4][LIST];  // the records a quarter walks (byte offsets in s_rec)
+    __shared__ uint32_t s_hit[NB][4][CH / 32];  // of the chunk: the entries some pixel of the quarter blended
     const uint32_t tile = tile_order[slot];  // longest lists first
     const int vi = view_of_tile(views, nv, tile);
     const DevView &V = views[vi];
     const uint32_t lt = tile - V.tile_base;
     const int tx = (int)(lt % (uint32_t)V.tiles_x), ty = (int)(lt / (uint32_t)V.tiles_x);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, ql = lane & 15;
     const int ox = tx * TW, oy = ty * TH;
     const int bx = quarter_x(lane), by = quarter_y(lane);
     const int px = ox + (w % SX) * 8 + bx, py = oy + (w / SX) * 8 + by;
     const bool inside = px < V.W && py < V.H;
     const float lx = (float)bx, ly = (float)by;
     const uint2 rg = ranges[tile];
-
-    // T < 0 marks a finished pixel (or one outside the image); |T| is its
-    // transmittance.  A pixel stops at the splat whose blend would take T
-    // below kTMin; that splat was evaluated but not blended.
-    float T = inside ? 1.0f : -1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
+    // alive: the lanes whose pixel is inside the image and not finished.  A
+    // pixel stops at the splat whose blend would take T below kTMin; that
+    // splat was evaluated but not blended.
+    uint64_t alive = __builtin_amdgcn_ballot_w64(inside);
+    float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
     uint32_t last = 0, nb = 0;
     uint32_t n_eval = 0, n_eval_t = 0;  // wave totals (scalar): evaluated pairs, of them interpolated
 
-    // records of the next batch, loaded while the current one is composited
-    SplatRec nxt[PER];
-    double4 nxw[PER];
+    // index of this thread's record of the next batch, loaded while the current
+    // one is composited (loading the records ahead too took 20 registers a lane:
+    // with two waves fewer per SIMD the headline batch of 32 views lost 0.7 ms)
+    uint32_t nxt = 0;
     auto fetch = [&](uint32_t b0) {
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-            const uint32_t idx = b0 + p * NT + threadIdx.x;
-            if (idx < rg.y) {
-                const uint32_t sidx = pair_vals[idx];
-                nxt[p] = recs[sidx];
-                nxw[p] = axes[sidx];
-            }
-        }
+        if (b0 + threadIdx.x < rg.y) nxt = pair_vals[b0 + threadIdx.x];
     };
     if (rg.x < rg.y) fetch(rg.x);
+    if (threadIdx.x < kRec / 4)  // (ordered before its first read by the barriers below)
+        reinterpret_cast<float *>(s_rec + kDead)[threadIdx.x] = 0.0f;
     for (uint32_t b0 = rg.x; b0 < rg.y; b0 += BATCH) {
-        if (__syncthreads_count(T > 0.0f) == 0) break;
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-            const int j = p * NT + threadIdx.x;
-            const bool real = b0 + j < rg.y;
-            Staged st;
-            if (real) {
-                stage_one<NB, SX>(nxt[p], nxw[p], ox, oy, st);
-            } else {  // padding: alpha = 0 everywhere, taken by no quarter
-                st.w = st.o = st.c = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-                for (int bk = 0; bk < NB; ++bk) st.u[bk] = make_float2(0.0f, 0.0f);
-                st.live = 0u;
-            }
-            s_w[j] = st.w;
-            s_o[j] = st.o;
-            s_c[j] = st.c;
-#pragma unroll
-            for (int bk = 0; bk < NB; ++bk) s_u[bk][j] = st.u[bk];
-            const int e0 = p * NT + 64 * w;  // first entry of this wave's 64
+        if (!__syncthreads_or(alive != 0ull)) break;
+        {
+            uint32_t live = 0u;
+            if (b0 + threadIdx.x < rg.y)
+                live = stage_fwd<NB, SX>(recs[nxt], axes[nxt], ox, oy,
+                                         *reinterpret_cast<Rec *>(s_rec + kRec * threadIdx.x));
 #pragma unroll
             for (int bq = 0; bq < 4 * NB; ++bq) {
-                const uint64_t m = __ballot((st.live >> bq) & 1u);
-                if (lane == 0) {
-                    s_qm[bq >> 2][bq & 3][e0 >> 5] = (uint32_t)m;
-                    s_qm[bq >> 2][bq & 3][(e0 >> 5) + 1] = (uint32_t)(m >> 32);
-                }
+                const uint64_t m = __ballot((live >> bq) & 1u);
+                if (lane < 2) s_qm[bq >> 2][bq & 3][2 * w + lane] = (uint32_t)(lane ? m >> 32 : m);
             }
         }
         __syncthreads();
         if (b0 + BATCH < rg.y) fetch(b0 + BATCH);
-        uint64_t alive = __ballot(T > 0.0f);
-        if (alive == 0ull) continue;
         const int cnt = (int)min((uint32_t)BATCH, rg.y - b0);
-        const uint32_t jb = b0 - rg.x + 1u;  // 1-based list position of entry 0
-        // each quarter walks, front to back, the entries it may take, until
-        // its pixels are all finished; the four quarters of a wave step together
-        for (int k = 0; 32 * k < cnt; ++k) {
-            uint32_t m = s_qm[w][q][k];
-            uint32_t cw = 0u;  // entries of this word the lane's pixel blended (or stopped at)
-            for (;;) {
-                m = ((alive >> (lane & 48)) & 0xFFFFull) ? m : 0u;  // nothing left for a finished quarter
-                const uint64_t hm = __ballot(m != 0u);
-                if (hm == 0ull) break;
-                const bool has = m != 0u;
-                const int j = 32 * k + __builtin_ctz(m | 0x80000000u);  // entry 32 k + 31 when nothing is left
-                m &= m - 1u;
-                const bool go = has && T > 0.0f;
-                const float4 Ov = s_o[j];
-                const bool interp = Ov.z > 0.0f;
-                // work counts from the wave's masks (scalar unit only)
-                const uint64_t gm = hm & alive;
-                n_eval += (uint32_t)__popcll(gm);
-                n_eval_t += (uint32_t)__popcll(gm & __ballot(Ov.z > 0.0f));
-                const float G = eval_gauss(s_w[j], s_u[w][j], lx, ly);
-                float alpha = fminf(Ov.x * G, kAlphaMax);
-                if (interp) {
-                    float qp;
-                    alpha = eval_interp(alpha, 1.0f - fminf(Ov.y * G, kAlphaMax), 1.0f - Ov.z, Ov.z, Ov.w, qp);
+        for (int c0 = 0; c0 < cnt && alive != 0ull; c0 += CH) {
+            // the entries of the chunk that each unfinished quarter may take, in
+            // order; two quarters at a time, one lane per entry
+            const int n_ch = min(cnt - c0, CH);
+            if (lane < 4 * (CH / 32)) (&s_hit[w][0][0])[lane] = 0u;
+            for (int k = 0; k < n_ch + 4; k += 32)
+                if (k + 2 * ql < LIST) reinterpret_cast<uint32_t *>(&s_list[w][q][0])[k / 2 + ql] = kDead * 0x10001u;
+            int steps = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int qa = 2 * h + (lane >> 5), i = lane & 31;
+                const bool open = ((alive >> (16 * qa)) & 0xFFFFull) != 0ull;
+                int n = 0;
+#pragma unroll
+                for (int k = 0; k < CH / 32; ++k) {
+                    if (32 * k >= n_ch) break;
+                    const uint32_t m = open ? s_qm[w][qa][c0 / 32 + k] : 0u;
+                    if ((m >> i) & 1u)
+                        s_list[w][qa][n + __popc(m & ((1u << i) - 1u))] = (uint16_t)((c0 + 32 * k + i) * kRec);
+                    n += __popc(m);
                 }
-                if (go && alpha >= kAlphaMin) {
-                    const float Tn = T * (1.0f - alpha);
-                    const bool stop = Tn < kTMin;
-                    const float4 Cc = s_c[j];
-                    const float wgt = stop ? 0.0f : alpha * T;
-                    C0 += Cc.x * wgt;
-                    C1 += Cc.y * wgt;
-                    C2 += Cc.z * wgt;
-                    nb += stop ? 0u : 1u;
-                    last = stop ? last : jb + (uint32_t)j;
-                    cw |= 1u << (j & 31);  // the splat a pixel stops at too: the backward's range test drops it
-                    T = stop ? -T : Tn;
-                }
-                alive = __ballot(T > 0.0f);
+                steps = max(steps, max(__builtin_amdgcn_readlane(n, 0), __builtin_amdgcn_readlane(n, 32)));
             }
+            steps = __builtin_amdgcn_readfirstlane(steps);
+            __builtin_amdgcn_wave_barrier();  // the lists are this wave's own
+            const uint16_t *list = &s_list[w][q][0];
+            const uint32_t *walk = reinterpret_cast<const uint32_t *>(list);
+            // history: the pixel blended (or stopped at) the entry, the latest
+            // entry in bit 0; alive0: alive when it was last emptied
+            uint32_t hist = 0u;
+            uint64_t alive0 = alive;
+            // the history's m list entries from position p0 into count, last
+            // contributor and the quarters' hits
+            auto flush = [&](int p0, int m) {
+                const bool died = __builtin_amdgcn_inverse_ballot_w64(alive0 & ~alive);
+                const uint32_t blended = died ? hist & (hist - 1u) : hist;  // not the splat a pixel stopped at
+                nb += (uint32_t)__popc(blended);
+                if (blended)  // 1-based list position
+                    last = b0 - rg.x + (uint32_t)list[p0 + m - 1 - __builtin_ctz(blended)] / kRec + 1u;
+                const uint32_t hits = row_or(hist);
+                hist = 0u;
+                alive0 = alive;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int bit = 16 * h + ql;
+                    if ((hits >> bit) & 1u) {
+                        const uint32_t e = (uint32_t)list[p0 + m - 1 - bit] / kRec - (uint32_t)c0;
+                        atomicOr(&s_hit[w][q][e >> 5], 1u << (e & 31u));
+                    }
+                }
+            };
+            uint32_t two = walk[0];
+            int p = 0;
+            while (p < steps) {
+                const uint32_t off[2] = {two & 0xFFFFu, two >> 16};
+                const uint64_t h0 = __builtin_amdgcn_ballot_w64(off[0] < kDead);
+                if ((alive & h0) == 0ull) break;  // every quarter is finished or past its list's end
+                two = walk[(p >> 1) + 1];
+                const uint64_t hm[2] = {h0, __builtin_amdgcn_ballot_w64(off[1] < kDead)};
+                float4 Ov[2], Cc[2];
+                float G[2], al[2];
+                uint64_t tm[2];
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const Rec &r = *reinterpret_cast<const Rec *>(s_rec + off[s]);
+                    const float4 Wv = r.w;
+                    Ov[s] = r.o;
+                    Cc[s] = r.c;
+                    G[s] = eval_gauss(Wv, r.u[w], lx, ly);
+                    al[s] = fminf(Ov[s].x * G[s], kAlphaMax);
+                    tm[s] = __builtin_amdgcn_ballot_w64(Ov[s].z > 0.0f);
+                }
+                if (tm[0] | tm[1]) {  // with t = 0 the interpolated form gives a_n exactly
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) {
+                        float qp;
+                        al[s] = eval_interp(al[s], 1.0f - fminf(Ov[s].y * G[s], kAlphaMax), Cc[s].w, Ov[s].z, Ov[s].w,
+                                            qp);
+                    }
+                }
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    // masks and work counts on the scalar unit
+                    const uint64_t gm = hm[s] & alive;
+                    n_eval += (uint32_t)__popcll(gm);
+                    n_eval_t += (uint32_t)__popcll(gm & tm[s]);
+                    const uint64_t go = alive & __builtin_amdgcn_ballot_w64(al[s] >= kAlphaMin);
+                    const float Tn = T * (1.0f - al[s]);
+                    const uint64_t on = go & ~__builtin_amdgcn_ballot_w64(Tn < kTMin);
+                    const bool lon = __builtin_amdgcn_inverse_ballot_w64(on);
+                    const float wgt = lon ? al[s] * T : 0.0f;
+                    C0 = fmaf(Cc[s].x, wgt, C0);
+                    C1 = fmaf(Cc[s].y, wgt, C1);
+                    C2 = fmaf(Cc[s].z, wgt, C2);
+                    T = lon ? Tn : T;
+                    // the splat a pixel stops at too: the backward drops it
+                    hist = hist + hist + (__builtin_amdgcn_inverse_ballot_w64(go) ? 1u : 0u);
+                    alive &= ~(go ^ on);
+                }
+                p += 2;
+                if ((p & 31) == 0) flush(p - 32, 32);
+            }
+            if (p & 31) flush(p & ~31, p & 31);
+            __builtin_amdgcn_wave_barrier();
             // the backward takes, per quarter, only the entries it blended here
-            // (entries after the last word walked lie after every pixel's last
-            // contributor, where the backward never looks)
-            record_word(qbits + (size_t)w * qstride, cw, b0 + 32u * (uint32_t)k, min(32, cnt - 32 * k), lane);
-            if (alive == 0ull) break;
+            // (entries after the last chunk walked lie after every pixel's last
+            // contributor, where the backward never looks): the byte of every
+            // entry of the chunk, bit q for quarter q, into the block's plane
+            for (int k = 0; k < n_ch; k += 64) {
+                const int e = k + lane;
+                uint32_t byte = 0u;
+#pragma unroll
+                for (int qq = 0; qq < 4; ++qq) byte |= ((s_hit[w][qq][e >> 5] >> (e & 31)) & 1u) << qq;
+                if (e < n_ch) qbits[(size_t)w * qstride + b0 + (uint32_t)(c0 + e)] = (uint8_t)byte;
+            }
+            __builtin_amdgcn_wave_barrier();  // read before the next chunk clears it
         }
     }
     if (inside) {
@@ -335,7 +405,7 @@ __device__ __forceinline__ void blend_tile(const DevView *__restrict__ views, in
         o[1] = C1;
         o[2] = C2;
         const size_t g = (size_t)V.pix_base + p;
-        T_final[g] = fabsf(T);
+        T_final[g] = T;
         n_last[g] = last;
         n_blend[g] = nb;
     }
@@ -344,7 +414,8 @@ __device__ __forceinline__ void blend_tile(const DevView *__restrict__ views, in
     for (int d = 32; d >= 1; d >>= 1) nb_w += (uint32_t)__shfl_xor((int)nb_w, d, 64);
     if (lane == 0) wstats[(size_t)slot * NW + w] = make_uint4(n_eval, nb_w, n_eval_t, 0u);
 }
-template <int TW, int TH, int BATCH, bool PERSIST>
+
+template <int TW, int TH, bool PERSIST>
 __global__ __launch_bounds__(TW *TH) void k_blend(const DevView *__restrict__ views, int nv,
                                                   const uint32_t *__restrict__ tile_order,
                                                   const uint2 *__restrict__ ranges,
@@ -357,7 +428,7 @@ __global__ __launch_bounds__(TW *TH) void k_blend(const DevView *__restrict__ vi
                                                   uint32_t *__restrict__ queue, uint32_t chunk)
 {
     if constexpr (!PERSIST) {
-        blend_tile<TW, TH, BATCH>(views, nv, tile_order, ranges, pair_vals, recs, axes, T_final, n_last, n_blend,
+        blend_tile<TW, TH>(views, nv, tile_order, ranges, pair_vals, recs, axes, T_final, n_last, n_blend,
                                   qbits, qstride, wstats, blockIdx.x);
     } else {
         __shared__ uint32_t s_slot;
@@ -366,7 +437,7 @@ __global__ __launch_bounds__(TW *TH) void k_blend(const DevView *__restrict__ vi
             if (first >= n_tiles) break;
             const uint32_t last = min(n_tiles, first + chunk);
             for (uint32_t slot = first; slot < last; ++slot) {
-                blend_tile<TW, TH, BATCH>(views, nv, tile_order, ranges, pair_vals, recs, axes, T_final, n_last,
+                blend_tile<TW, TH>(views, nv, tile_order, ranges, pair_vals, recs, axes, T_final, n_last,
                                           n_blend, qbits, qstride, wstats, slot);
                 __syncthreads();  // LDS of this tile read by every wave before the next stages
             }
@@ -485,12 +556,23 @@ __device__ __forceinline__ float quad_sum(float v)
     v += dpp_move<0xB1>(v);
     return v + dpp_move<0x4E>(v);
 }
+// (FMAs with a lane-exchanged operand written out: the compiler folds an
+// exchange into a multiply or an add, but not into an FMA.  Every lane must
+// be active.  The leading s_nop covers the two wait states that a DPP operand
+// needs after the VALU wrote it.)
 __device__ __forceinline__ float quad_dot(float v, const float (&c)[4])
 {
-    float s = c[0] * dpp_move<0x00>(v);
-    s = fmaf(c[1], dpp_move<0x55>(v), s);
-    s = fmaf(c[2], dpp_move<0xAA>(v), s);
-    return fmaf(c[3], dpp_move<0xFF>(v), s);
+#define HGS_DPP_ALL " row_mask:0xf bank_mask:0xf\n\t"
+    float s;
+    asm("s_nop 1\n\t"
+        "v_mul_f32_dpp %0, %1, %2 quad_perm:[0,0,0,0]" HGS_DPP_ALL
+        "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,1,1,1]" HGS_DPP_ALL
+        "v_fmac_f32_dpp %0, %1, %4 quad_perm:[2,2,2,2]" HGS_DPP_ALL
+        "v_fmac_f32_dpp %0, %1, %5 quad_perm:[3,3,3,3]" HGS_DPP_ALL
+        : "=&v"(s)
+        : "v"(v), "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]));
+#undef HGS_DPP_ALL
+    return s;
 }
 
 // A splat staged for one tile by the backward.
@@ -508,7 +590,7 @@ struct __align__(16) BwdStaged {
     static constexpr uint32_t kStride = 16u * ((uint32_t)(3 + (NB + 1) / 2 + kG / 2) | 1u);
 };
 
-template <int TW, int TH, int BATCH, bool DT, bool DET>
+template <int TW, int TH, bool DT, bool DET>
 __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views, int nv,
                                                const uint32_t *__restrict__ tile_order,
                                                const uint2 *__restrict__ ranges,
@@ -524,9 +606,10 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
     constexpr int NW = NT / 64;
     constexpr int SX = TW / 8;
     constexpr int NB = (TW / 8) * (TH / 8);
+    constexpr int PER = 32;  // entries that a wave stages and flushes
+    constexpr int BATCH = DET ? PER : PER * NW;
     constexpr int NQW = BATCH / 32;  // 32-entry words of a quarter's mask
-    constexpr int PER = BATCH >= 64 * NW ? 64 : 32;  // entries that a wave stages and flushes
-    static_assert(BATCH % PER == 0 && BATCH <= PER * NW && NB <= 8, "tile/batch combination");
+    static_assert(NB <= 8, "tile");
     using Rec = BwdStaged<NB>;
     constexpr uint32_t kRec = Rec::kStride, kDead = kRec * BATCH;
     static_assert(sizeof(Rec) <= kRec && kDead < 65536, "a list entry is a 16-bit byte offset");
@@ -858,7 +941,7 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
     }
     if (lane == 0) wstats[(size_t)tslot * NW + w] = make_uint4(n_eval, n_eval_t, n_con, 0u);
 }
-template <int TW, int TH, int BATCH, bool DT, bool PERSIST, bool DET>
+template <int TW, int TH, bool DT, bool PERSIST, bool DET>
 __global__ __launch_bounds__(TW *TH) void k_blend_bwd(const DevView *__restrict__ views, int nv,
                                                       const uint32_t *__restrict__ tile_order,
                                                       const uint2 *__restrict__ ranges,
@@ -874,7 +957,7 @@ __global__ __launch_bounds__(TW *TH) void k_blend_bwd(const DevView *__restrict_
                                                       uint32_t *__restrict__ queue, uint32_t chunk)
 {
     if constexpr (!PERSIST) {
-        blend_bwd_tile<TW, TH, BATCH, DT, DET>(views, nv, tile_order, ranges, pair_vals, recs, axes, T_final,
+        blend_bwd_tile<TW, TH, DT, DET>(views, nv, tile_order, ranges, pair_vals, recs, axes, T_final,
                                                n_last, qbits, qstride, vis_rank, sgrad, det, wstats, blockIdx.x);
     } else {
         __shared__ uint32_t s_slot;
@@ -883,7 +966,7 @@ __global__ __launch_bounds__(TW *TH) void k_blend_bwd(const DevView *__restrict_
             if (first >= n_tiles) break;
             const uint32_t last = min(n_tiles, first + chunk);
             for (uint32_t slot = first; slot < last; ++slot) {
-                blend_bwd_tile<TW, TH, BATCH, DT, DET>(views, nv, tile_order, ranges, pair_vals, recs, axes,
+                blend_bwd_tile<TW, TH, DT, DET>(views, nv, tile_order, ranges, pair_vals, recs, axes,
                                                        T_final, n_last, qbits, qstride, vis_rank, sgrad, det, wstats,
                                                        slot);
                 __syncthreads();  // LDS of this tile read by every wave before the next stages
@@ -953,155 +1036,119 @@ uint32_t queue_run(uint32_t n_tiles, uint32_t g)
     return std::min(32u, std::max(1u, share / 16u));
 }
 
-template <int TW, int TH, int BATCH>
+template <int TW, int TH>
 void launch_blend_t(const DevView *views, int nv, uint32_t n_tiles, const uint32_t *order, const uint2 *ranges,
                     const uint32_t *pair_vals, const SplatRec *recs, const double4 *axes, float *T_final,
                     uint32_t *n_last, uint32_t *n_blend, uint8_t *qbits, uint32_t qstride, uint4 *wstats,
                     bool persist, uint32_t *queue, hipStream_t st)
 {
     if (persist) {
-        auto k = k_blend<TW, TH, BATCH, true>;
+        auto k = k_blend<TW, TH, true>;
         const uint32_t g = std::min(n_tiles, resident_grid(k, TW * TH));
         launch_fill_u32(queue, 0u, 1, st);
         hipLaunchKernelGGL(k, dim3(g), dim3(TW * TH), 0, st, views, nv, order, ranges, pair_vals, recs, axes,
                            T_final, n_last, n_blend, qbits, qstride, wstats, n_tiles, queue, queue_run(n_tiles, g));
     } else {
-        hipLaunchKernelGGL((k_blend<TW, TH, BATCH, false>), dim3(n_tiles), dim3(TW * TH), 0, st, views, nv, order,
+        hipLaunchKernelGGL((k_blend<TW, TH, false>), dim3(n_tiles), dim3(TW * TH), 0, st, views, nv, order,
                            ranges, pair_vals, recs, axes, T_final, n_last, n_blend, qbits, qstride, wstats, n_tiles,
                            queue, 1u);
     }
 }
 
-// Splats the backward stages per batch.
-constexpr int bwd_batch(int tw, int th, int batch)
-{
-    const int nw = tw * th / 64;
-    return std::min(batch, 32 * nw);
-}
-
-template <int TW, int TH, int B, bool DT>
+template <int TW, int TH, bool DT>
 void launch_blend_bwd_dt(const DevView *views, int nv, uint32_t n_tiles, const uint32_t *order, const uint2 *ranges,
                          const uint32_t *pair_vals, const SplatRec *recs, const double4 *axes, const float *T_final,
                          const uint32_t *n_last, const uint8_t *qbits, uint32_t qstride, const uint32_t *vis_rank,
                          double *sgrad, const DetArgs *det, uint4 *wstats, bool persist, uint32_t *queue,
                          hipStream_t st)
 {
-    if (det) {  // the deterministic mode: one workgroup per tile, 32 splats staged per batch
-        hipLaunchKernelGGL((k_blend_bwd<TW, TH, 32, DT, false, true>), dim3(n_tiles), dim3(TW * TH), 0, st, views, nv,
+    if (det) {  // the deterministic mode: one workgroup per tile
+        hipLaunchKernelGGL((k_blend_bwd<TW, TH, DT, false, true>), dim3(n_tiles), dim3(TW * TH), 0, st, views, nv,
                            order, ranges, pair_vals, recs, axes, T_final, n_last, qbits, qstride, vis_rank, sgrad,
                            *det, wstats, n_tiles, queue, 1u);
     } else if (persist) {
-        auto k = k_blend_bwd<TW, TH, B, DT, true, false>;
+        auto k = k_blend_bwd<TW, TH, DT, true, false>;
         const uint32_t g = std::min(n_tiles, resident_grid(k, TW * TH));
         launch_fill_u32(queue, 0u, 1, st);
         hipLaunchKernelGGL(k, dim3(g), dim3(TW * TH), 0, st, views, nv, order, ranges, pair_vals, recs, axes, T_final,
                            n_last, qbits, qstride, vis_rank, sgrad, DetArgs{}, wstats, n_tiles, queue,
                            queue_run(n_tiles, g));
     } else {
-        hipLaunchKernelGGL((k_blend_bwd<TW, TH, B, DT, false, false>), dim3(n_tiles), dim3(TW * TH), 0, st, views, nv,
+        hipLaunchKernelGGL((k_blend_bwd<TW, TH, DT, false, false>), dim3(n_tiles), dim3(TW * TH), 0, st, views, nv,
                            order, ranges, pair_vals, recs, axes, T_final, n_last, qbits, qstride, vis_rank, sgrad,
                            DetArgs{}, wstats, n_tiles, queue, 1u);
     }
 }
 
-template <int TW, int TH, int BATCH>
-void launch_blend_bwd_t(const DevView *views, int nv, uint32_t n_tiles, const uint32_t *order, const uint2 *ranges,
-                        const uint32_t *pair_vals, const SplatRec *recs, const double4 *axes, const float *T_final,
-                        const uint32_t *n_last, const uint8_t *qbits, uint32_t qstride, const uint32_t *vis_rank,
-                        double *sgrad, const DetArgs *det, uint4 *wstats, bool want_dt, bool persist,
-                        uint32_t *queue, hipStream_t st)
+template <int TW, int TH>
+void prepare_t()
 {
-    // the backward stages at most 32 splats per wave and step: its LDS holds
-    // the FP32 partial sums and the FP64 flushed terms of every staged
-    // splat, and a smaller footprint keeps more tiles resident per CU
-    constexpr int B = bwd_batch(TW, TH, BATCH);
-    if (want_dt)
-        launch_blend_bwd_dt<TW, TH, B, true>(views, nv, n_tiles, order, ranges, pair_vals, recs, axes, T_final,
-                                             n_last, qbits, qstride, vis_rank, sgrad, det, wstats, persist, queue, st);
-    else
-        launch_blend_bwd_dt<TW, TH, B, false>(views, nv, n_tiles, order, ranges, pair_vals, recs, axes, T_final,
-                                              n_last, qbits, qstride, vis_rank, sgrad, det, wstats, persist, queue, st);
+    (void)resident_grid(k_blend<TW, TH, true>, TW * TH);
+    (void)resident_grid(k_blend_bwd<TW, TH, true, true, false>, TW * TH);
+    (void)resident_grid(k_blend_bwd<TW, TH, false, true, false>, TW * TH);
 }
 
 }  // namespace
 
-// Supported (tile, batch) combinations; batch 0 means one record per thread.
-#define HGS_BLEND_CASES(X)                                                                                            \
-    X(8, 8, 64) X(8, 8, 128) X(8, 8, 256) X(16, 8, 128) X(16, 8, 256) X(16, 16, 256) X(16, 16, 512) X(32, 16, 512)
+#define HGS_TILES(X) X(8, 8) X(16, 8) X(16, 16) X(32, 16)
 
-template <int TW, int TH, int BATCH>
-void prepare_t()
+void blend_prepare(int tw, int th)
 {
-    constexpr int B = bwd_batch(TW, TH, BATCH);
-    (void)resident_grid(k_blend<TW, TH, BATCH, true>, TW * TH);
-    (void)resident_grid(k_blend_bwd<TW, TH, B, true, true, false>, TW * TH);
-    (void)resident_grid(k_blend_bwd<TW, TH, B, false, true, false>, TW * TH);
-}
-
-void blend_prepare(int tw, int th, int batch)
-{
-    if (batch == 0) batch = tw * th;
-#define X(a, b, c) \
-    if (tw == a && th == b && batch == c) return prepare_t<a, b, c>();
-    HGS_BLEND_CASES(X)
+#define X(a, b) \
+    if (tw == a && th == b) return prepare_t<a, b>();
+    HGS_TILES(X)
 #undef X
 }
 
+// Supported (tile, batch) combinations; batch 0 means one record per thread.
+// A batch above that is accepted and staged one record per thread at a time:
+// the records of a larger one keep tiles off the CU (32 views of 1920x1080
+// over 30M leaves, forward: 8x8 tiles 4.1 ms with 64, 5.7 with 128, 8.8 with
+// 256 records; 16x8 tiles 4.3 ms with 128, 6.2 with 256).  The backward
+// stages 32 per wave (64: 7.6 -> 8.9 ms with 16x8 tiles).
 bool blend_supported(int tw, int th, int batch)
 {
     if (batch == 0) batch = tw * th;
-#define X(a, b, c) \
-    if (tw == a && th == b && batch == c) return true;
-    HGS_BLEND_CASES(X)
-#undef X
+    static constexpr int kCases[][3] = {{8, 8, 64},   {8, 8, 128},    {8, 8, 256},    {16, 8, 128},
+                                        {16, 8, 256}, {16, 16, 256}, {16, 16, 512}, {32, 16, 512}};
+    for (const int *c : kCases)
+        if (tw == c[0] && th == c[1] && batch == c[2]) return true;
     return false;
-}
-
-static void launch_blend_cfg(const DevView *views, int nv, uint32_t n_tiles, const uint32_t *order,
-                             const uint2 *ranges, const uint32_t *pair_vals, const SplatRec *recs,
-                             const double4 *axes, float *T_final, uint32_t *n_last, uint32_t *n_blend,
-                             uint8_t *qbits, uint32_t qstride, uint4 *wstats, int tw, int th, int batch, bool persist,
-                             uint32_t *queue, hipStream_t st)
-{
-#define X(a, b, c)                                                                                           \
-    if (tw == a && th == b && batch == c)                                                                    \
-        return launch_blend_t<a, b, c>(views, nv, n_tiles, order, ranges, pair_vals, recs, axes, T_final, n_last, \
-                                       n_blend, qbits, qstride, wstats, persist, queue, st);
-    HGS_BLEND_CASES(X)
-#undef X
 }
 
 void launch_blend(const DevView *views, int nv, uint32_t n_tiles, const uint32_t *order, const uint2 *ranges,
                   const uint32_t *pair_vals, const SplatRec *recs, const double4 *axes, float *T_final,
                   uint32_t *n_last, uint32_t *n_blend, uint8_t *qbits, uint32_t qstride, uint4 *wstats,
-                  Counters *ctr, int tw, int th, int batch, bool persist, uint32_t *queue, hipStream_t st)
+                  Counters *ctr, int tw, int th, bool persist, uint32_t *queue, hipStream_t st)
 {
-    if (batch == 0) batch = tw * th;
     if (!n_tiles) return;
-    const uint32_t nst = n_tiles * (uint32_t)(tw * th / 64);
-    launch_blend_cfg(views, nv, n_tiles, order, ranges, pair_vals, recs, axes, T_final, n_last, n_blend, qbits,
-                     qstride, wstats, tw, th, batch, persist, queue, st);
-    hipLaunchKernelGGL(k_stats_reduce, dim3(256), dim3(256), 0, st, wstats, nst, &ctr->evaluated);
+#define X(a, b)                                                                                                 \
+    if (tw == a && th == b)                                                                                     \
+        launch_blend_t<a, b>(views, nv, n_tiles, order, ranges, pair_vals, recs, axes, T_final, n_last, n_blend, \
+                             qbits, qstride, wstats, persist, queue, st);
+    HGS_TILES(X)
+#undef X
+    hipLaunchKernelGGL(k_stats_reduce, dim3(256), dim3(256), 0, st, wstats, n_tiles * (uint32_t)(tw * th / 64),
+                       &ctr->evaluated);
 }
 
 void launch_blend_backward(const DevView *views, int nv, uint32_t n_tiles, const uint32_t *order,
                            const uint2 *ranges, const uint32_t *pair_vals, const SplatRec *recs, const double4 *axes,
                            const float *T_final, const uint32_t *n_last, const uint8_t *qbits, uint32_t qstride,
                            const uint32_t *vis_rank, double *sgrad, const DetArgs *det, uint4 *wstats, Counters *ctr,
-                           int tw, int th, int batch, bool want_dt, bool persist, uint32_t *queue, hipStream_t st)
+                           int tw, int th, bool want_dt, bool persist, uint32_t *queue, hipStream_t st)
 {
-    if (batch == 0) batch = tw * th;
     if (!n_tiles) return;
-#define X(a, b, c)                                                                                                 \
-    if (tw == a && th == b && batch == c) {                                                                        \
-        launch_blend_bwd_t<a, b, c>(views, nv, n_tiles, order, ranges, pair_vals, recs, axes, T_final, n_last,    \
-                                    qbits, qstride, vis_rank, sgrad, det, wstats, want_dt, persist, queue, st);    \
-        hipLaunchKernelGGL(k_stats_reduce, dim3(256), dim3(256), 0, st, wstats,                                    \
-                           n_tiles * (uint32_t)(tw * th / 64), &ctr->bwd_evaluated);                               \
-        return;                                                                                                    \
+#define X(a, b)                                                                                                    \
+    if (tw == a && th == b) {                                                                                      \
+        auto f = want_dt ? launch_blend_bwd_dt<a, b, true> : launch_blend_bwd_dt<a, b, false>;                     \
+        f(views, nv, n_tiles, order, ranges, pair_vals, recs, axes, T_final, n_last, qbits, qstride, vis_rank,     \
+          sgrad, det, wstats, persist, queue, st);                                                                 \
     }
-    HGS_BLEND_CASES(X)
+    HGS_TILES(X)
 #undef X
+    hipLaunchKernelGGL(k_stats_reduce, dim3(256), dim3(256), 0, st, wstats, n_tiles * (uint32_t)(tw * th / 64),
+                       &ctr->bwd_evaluated);
 }
 
 }  // namespace hgs
