@@ -452,6 +452,30 @@ __device__ __forceinline__ int bwd_quarter(int lane) { return (lane >> 2) & 3; }
 __device__ __forceinline__ int bwd_x(int lane) { return (bwd_quarter(lane) & 1) * 4 + (lane & 3); }
 __device__ __forceinline__ int bwd_y(int lane) { return (bwd_quarter(lane) >> 1) * 4 + (lane >> 4); }
 
+// Sums over each row of 16 lanes (one 4x4 quarter of the wave's block) of 12
+// per-lane values, taken as six pairs: four halvings with DPP inside the row
+// (partners l ^ 8, l ^ 7, l ^ 2 and l ^ 1), each keeping one of the two
+// values of a pair per lane.  A: the pairs after the first halving.  Lane l of
+// the row ends with the row's total of value row_slot(l) (value 2 k + 1 is the
+// second of pair k; -1: a copy of another lane's total).
+__device__ __forceinline__ float row_reduce12(const float (&A)[6], int lane)
+{
+    const bool b2 = (lane & 4) != 0, b1 = (lane & 2) != 0, b0 = (lane & 1) != 0;
+    float B[3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+        B[m] = (b2 ? A[2 * m + 1] : A[2 * m]) + dpp_move<0x141>(b2 ? A[2 * m] : A[2 * m + 1]);  // half mirror
+    const float C0 = (b1 ? B[1] : B[0]) + dpp_move<0x4E>(b1 ? B[0] : B[1]);
+    const float C1 = B[2] + dpp_move<0x4E>(B[2]);
+    return (b0 ? C1 : C0) + dpp_move<0xB1>(b0 ? C0 : C1);
+}
+
+__device__ __forceinline__ int row_slot(int lane)
+{
+    const int b3 = (lane >> 3) & 1, b2 = (lane >> 2) & 1, b1 = (lane >> 1) & 1, b0 = lane & 1;
+    return b0 == 0 ? 4 * b1 + 2 * b2 + b3 : (b1 == 0 ? 8 + 2 * b2 + b3 : -1);
+}
+
 constexpr int kG = 12;  // floats per splat in the screen-space gradient
 
 // Gradient slots of a splat, summed over the pixels of the tile.  With h = G
@@ -531,6 +555,16 @@ __device__ __forceinline__ double2 centre_offsets(const SplatRec &r, const doubl
 // 9.0 -> 7.6 ms; 16x16 tiles 10.0 -> 7.6, 32x16 19.2 -> 9.7; 8 views of
 // 1280x720 over 2M leaves 4.2 -> 3.4 ms.
 //
+// AXES (32x16 tiles): the colour behind is kept per channel and the moments
+// are formed per lane on the splat's axes and summed by four DPP halvings over
+// the quarter's row of 16 lanes.  Sixteen pixels from the tile's centre the
+// moments of a large splat nearly cancel, and the FP32 rounding of either form
+// moves single elements of the scale and rotation gradients by up to 2e-3 of
+// their RMS; this form, with its operations and order written out, keeps the
+// results of this tile what they have always been (up to 16x16 the two forms
+// stay within 6e-4).  It costs 5 to 7% here: 10.3 against 9.8 ms at 1.5 M
+// splats, 32 views of 1080p (19.2 ms with one entry a step).
+//
 // DET (the deterministic mode): no floating-point atomics.  Each quarter
 // stores its FP32 partial sums in a slot of its own, the flush adds the
 // quarters in a fixed order (FP64), and the tile's 11 terms for a splat go
@@ -606,6 +640,7 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
     constexpr int NW = NT / 64;
     constexpr int SX = TW / 8;
     constexpr int NB = (TW / 8) * (TH / 8);
+    constexpr bool AXES = NT > 256;
     constexpr int PER = 32;  // entries that a wave stages and flushes
     constexpr int BATCH = DET ? PER : PER * NW;
     constexpr int NQW = BATCH / 32;  // 32-entry words of a quarter's mask
@@ -630,9 +665,10 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
     const DevView &V = views[vi];
     const uint32_t lt = tile - V.tile_base;
     const int tx = (int)(lt % (uint32_t)V.tiles_x), ty = (int)(lt / (uint32_t)V.tiles_x);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, q = bwd_quarter(lane);
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, q = AXES ? lane >> 4 : bwd_quarter(lane);
+    constexpr int Q1 = AXES ? 16 : 4;  // the first lane of quarter 1
     const int ox = tx * TW, oy = ty * TH;
-    const int bx = bwd_x(lane), by = bwd_y(lane);
+    const int bx = AXES ? quarter_x(lane) : bwd_x(lane), by = AXES ? quarter_y(lane) : bwd_y(lane);
     const int px = ox + (w % SX) * 8 + bx, py = oy + (w / SX) * 8 + by;
     const bool inside = px < V.W && py < V.H;
     const float lx = (float)bx, ly = (float)by;
@@ -655,6 +691,11 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
     const int slot_a = low ? (qx == 0 ? 5 : (qx == 1 ? 0 : (qx == 2 ? 2 : 8))) : (qx == 0 ? 9 : (qx == 3 ? 7 : 11));
     const int slot_b = low ? (qx == 0 ? 1 : (qx == 1 ? 4 : (qx == 2 ? 3 : 11))) : (qx == 0 ? 10 : (qx == 2 ? 6 : 11));
     const uint32_t off_a = (uint32_t)offsetof(Rec, g) + 8u * slot_a, off_b = (uint32_t)offsetof(Rec, g) + 8u * slot_b;
+    // AXES: the pixel's offset from the tile centre, this lane's slot, and
+    // which value of each pair it keeps in the first halving
+    const float lxt = (float)(px - ox) - 0.5f * (TW - 1), lyt = (float)(py - oy) - 0.5f * (TH - 1);
+    const int slot = row_slot(lane);
+    const bool b3 = (lane & 8) != 0;
 
     float T = 1.0f, g0 = 0.0f, g1 = 0.0f, g2 = 0.0f;
     uint32_t last = 0;
@@ -673,14 +714,15 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
     uint32_t qm = last;
     qm = max(qm, (uint32_t)__shfl_xor((int)qm, 1, 64));
     qm = max(qm, (uint32_t)__shfl_xor((int)qm, 2, 64));
-    qm = max(qm, (uint32_t)__shfl_xor((int)qm, 16, 64));
-    qm = max(qm, (uint32_t)__shfl_xor((int)qm, 32, 64));
-    uint32_t wm = max(qm, (uint32_t)__shfl_xor((int)qm, 4, 64));
-    wm = max(wm, (uint32_t)__shfl_xor((int)wm, 8, 64));
+    qm = max(qm, (uint32_t)__shfl_xor((int)qm, AXES ? 4 : 16, 64));
+    qm = max(qm, (uint32_t)__shfl_xor((int)qm, AXES ? 8 : 32, 64));
+    uint32_t wm = max(qm, (uint32_t)__shfl_xor((int)qm, AXES ? 16 : 4, 64));
+    wm = max(wm, (uint32_t)__shfl_xor((int)wm, AXES ? 32 : 8, 64));
     if (lane == 0) atomicMax(&s_max, wm);
     __syncthreads();
     const uint32_t end = rg.x + s_max;
     float Rg = 0.0f;  // cotangent . colour composited behind the current splat
+    float R0 = 0.0f, R1 = 0.0f, R2 = 0.0f;  // AXES: that colour instead
     uint32_t n_eval = 0, n_eval_t = 0, n_con = 0;  // wave totals (scalar)
 
     if (threadIdx.x == 0) {  // (ordered before its first read by the barrier after the staging)
@@ -752,8 +794,8 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int qa = 2 * h + (lane >> 5), i = lane & 31;
-            const uint32_t qma = (uint32_t)__builtin_amdgcn_readlane((int)qm, 8 * h),
-                           qmb = (uint32_t)__builtin_amdgcn_readlane((int)qm, 8 * h + 4);
+            const uint32_t qma = (uint32_t)__builtin_amdgcn_readlane((int)qm, 2 * h * Q1),
+                           qmb = (uint32_t)__builtin_amdgcn_readlane((int)qm, (2 * h + 1) * Q1);
             const uint32_t lastq = lane < 32 ? qma : qmb;
             const int limq = lastq > base ? (int)min(lastq - base, (uint32_t)cnt) : 0;
             int n = 0;
@@ -777,19 +819,20 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
         for (int p = 0; p < steps; p += 2) {
             const uint32_t off[2] = {two & 0xFFFFu, two >> 16};
             two = walk[(p >> 1) + 1];
-            float4 Ov[2];
+            float4 Ov[2], Wv[2], Cv[2];
             float G[2], al[2], anr[2], apr[2], omt[2], omap[2], qp[2], cg[2];
             bool con[2];
             uint64_t tm[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 const Rec &r = rec_at(off[s]);
-                const float4 Wv = r.w, Cc = r.c;
+                Cv[s] = r.c;
+                Wv[s] = r.w;
                 Ov[s] = r.o;
-                omt[s] = Cc.w;
-                cg[s] = fmaf(Cc.z, g2, fmaf(Cc.y, g1, Cc.x * g0));
+                omt[s] = Cv[s].w;
+                cg[s] = fmaf(Cv[s].z, g2, fmaf(Cv[s].y, g1, Cv[s].x * g0));
                 tm[s] = __builtin_amdgcn_ballot_w64(Ov[s].z > 0.0f);
-                G[s] = eval_gauss(Wv, r.u[w], lx, ly);
+                G[s] = eval_gauss(Wv[s], r.u[w], lx, ly);
                 anr[s] = Ov[s].x * G[s];
                 al[s] = fminf(anr[s], kAlphaMax);
                 apr[s] = 0.0f;
@@ -813,71 +856,114 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
                 n_con += (uint32_t)__popcll(irm & __builtin_amdgcn_ballot_w64(al[s] >= kAlphaMin));
                 con[s] = off[s] < lim && al[s] >= kAlphaMin;
             }
-            float van[2], vap[2], aT[2], dal[2];
+            float dan[2], dap[2], aT[2], dal[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 // every lane runs the update; with a = 0 it leaves T and R as they are
                 const float a = con[s] ? al[s] : 0.0f;
                 T = T * __builtin_amdgcn_rcpf(1.0f - a);
-                const float df = cg[s] - Rg;
-                dal[s] = T * df;
                 aT[s] = a * T;
-                Rg = fmaf(a, df, Rg);
+                if constexpr (AXES) {
+                    const float d0 = Cv[s].x - R0, d1 = Cv[s].y - R1, d2 = Cv[s].z - R2;
+                    dal[s] = T * fmaf(d2, g2, fmaf(d0, g0, d1 * g1));
+                    R0 = fmaf(a, d0, R0);
+                    R1 = fmaf(a, d1, R1);
+                    R2 = fmaf(a, d2, R2);
+                } else {
+                    const float df = cg[s] - Rg;
+                    dal[s] = T * df;
+                    Rg = fmaf(a, df, Rg);
+                }
             }
-            // dL/da_n, dL/da_p (zero through the clamps), times G
+            // dL/da_n, dL/da_p (zero through the clamps)
             if (any_t) {
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
                     // d alpha' / d a_p = (1/K) (1 - a_p)^(1/K - 1) = (1/K) q / (1 - a_p)
-                    const float dap = (Ov[s].z * dal[s]) * Ov[s].w * (qp[s] * __builtin_amdgcn_rcpf(omap[s]));
-                    van[s] = G[s] * (con[s] && !(anr[s] > kAlphaMax) ? omt[s] * dal[s] : 0.0f);
-                    vap[s] = G[s] * (con[s] && !(apr[s] > kAlphaMax) ? dap : 0.0f);
+                    const float dp = (Ov[s].z * dal[s]) * Ov[s].w * (qp[s] * __builtin_amdgcn_rcpf(omap[s]));
+                    dan[s] = con[s] && !(anr[s] > kAlphaMax) ? omt[s] * dal[s] : 0.0f;
+                    dap[s] = con[s] && !(apr[s] > kAlphaMax) ? dp : 0.0f;
                 }
             } else {
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
-                    van[s] = G[s] * (con[s] && !(anr[s] > kAlphaMax) ? dal[s] : 0.0f);
-                    vap[s] = 0.0f;
+                    dan[s] = con[s] && !(anr[s] > kAlphaMax) ? dal[s] : 0.0f;
+                    dap[s] = 0.0f;
                 }
             }
-            const float vh0 = fmaf(van[0], Ov[0].x, vap[0] * Ov[0].y);  // G dL/dG
-            const float vh1 = fmaf(van[1], Ov[1].x, vap[1] * Ov[1].y);
-            // rows 0 / 1 of 16 lanes: S, S y, S y^2, colour 0 / colour 1, colour 2,
-            // dL/dA_n, dL/dA_p of the first step; rows 2 / 3 of the second
-            const float D0 = fold16(fold32(vh0, vh1), fold32(aT[0] * g1, aT[1] * g1));
-            const float D1 = fold16(fold32(vh0 * yl, vh1 * yl), fold32(aT[0] * g2, aT[1] * g2));
-            const float D2 = fold16(fold32(vh0 * yl2, vh1 * yl2), fold32(van[0], van[1]));
-            const float D3 = fold16(fold32(aT[0] * g0, aT[1] * g0), fold32(vap[0], vap[1]));
-            const float Sy = fmaf(yq, D0, D1);
-            const float Syy = fmaf(yq, Sy + D1, D2);
-            const float f0 = quad_dot(D0, cw), f1 = quad_dot(Sy, cw), f2 = quad_sum(Syy), f3 = quad_sum(D3);
-            float va = qx == 3 ? f3 : f0, vb = qx == 2 ? f2 : f1;
-            // formed by every lane here, where the lane exchanges fold into the
-            // arithmetic, not under the masks of the adds below
-            asm volatile("" : "+v"(va), "+v"(vb));
-            const uint32_t os = lane & 32 ? off[1] : off[0];
-            if constexpr (DET) {
-                if (os != kDead) {
-                    float *o = s_gr[4 * w + q][os / kRec];
-                    if (slot_a != 11) o[slot_a] = va;
-                    if (slot_b != 11) o[slot_b] = vb;
-                }
-            } else {  // past a list's end: zeros, to the dead record
-                if (slot_a != 11) unsafeAtomicAdd(reinterpret_cast<double *>(s_rec + os + off_a), (double)va);
-                if (slot_b != 11) unsafeAtomicAdd(reinterpret_cast<double *>(s_rec + os + off_b), (double)vb);
-            }
-            if constexpr (DT) {  // dL/dt through alpha: (a'_p - a_n) dL/dalpha
-                float d[2];
+            float dt[2] = {0.0f, 0.0f};  // dL/dt through alpha: (a'_p - a_n) dL/dalpha
+            if constexpr (DT)
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
-                    d[s] = con[s] && Ov[s].z > 0.0f ? ((1.0f - qp[s]) - fminf(anr[s], kAlphaMax)) * dal[s] : 0.0f;
-                float f = fold32(d[0], d[1]);
-                f = quad_sum(fold16(f, f));
-                if (qx == 0 && low) {
-                    if constexpr (DET) {
-                        if (os != kDead) s_gr[4 * w + q][os / kRec][11] = f;
+                    dt[s] = con[s] && Ov[s].z > 0.0f ? ((1.0f - qp[s]) - fminf(anr[s], kAlphaMax)) * dal[s] : 0.0f;
+            if constexpr (AXES) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const float4 W = Wv[s];
+                    const float h = G[s] * fmaf(dap[s], Ov[s].y, dan[s] * Ov[s].x);  // G dL/dG
+                    const float v1 = fmaf(lyt, W.y, lxt * W.x), v2 = fmaf(lyt, W.w, lxt * W.z);
+                    // the six pairs and their first halving (row_ror:8): a lane
+                    // keeps the second value of a pair where bit 3 is set
+                    const float pa = b3 ? v2 : v1, pb = b3 ? v1 : v2;
+                    const float ha = h * pa, hb = h * pb, hab = ha * pb;
+                    float A[6];
+                    A[0] = fmaf(h, pa, dpp_move<0x128>(hb));                            // P'_1, P'_2
+                    A[1] = fmaf(ha, pa, dpp_move<0x128>(hb * pb));                      // Q'_11, Q'_22
+                    A[2] = (b3 ? h : hab) + dpp_move<0x128>(b3 ? hab : h);              // Q'_12, S
+                    A[3] = fmaf(G[s], b3 ? dap[s] : dan[s], dpp_move<0x128>(G[s] * (b3 ? dan[s] : dap[s])));
+                    A[4] = fmaf(aT[s], b3 ? g1 : g0, dpp_move<0x128>(aT[s] * (b3 ? g0 : g1)));  // colour 0, 1
+                    if constexpr (DT) {  // colour 2, dL/dt
+                        const float c2 = aT[s] * g2;
+                        A[5] = (b3 ? dt[s] : c2) + dpp_move<0x128>(b3 ? c2 : dt[s]);
                     } else {
-                        unsafeAtomicAdd(&rec_at(os).g[11], (double)f);
+                        A[5] = fmaf(aT[s], b3 ? 0.0f : g2, dpp_move<0x128>(aT[s] * (b3 ? g2 : 0.0f)));
+                    }
+                    const float tot = row_reduce12(A, lane);
+                    if (slot >= 0) {
+                        if constexpr (DET) {
+                            if (off[s] != kDead) s_gr[4 * w + q][off[s] / kRec][slot] = tot;
+                        } else {
+                            if (tot != 0.0f) unsafeAtomicAdd(&rec_at(off[s]).g[slot], (double)tot);
+                        }
+                    }
+                }
+            } else {
+                const float van0 = G[0] * dan[0], van1 = G[1] * dan[1], vap0 = G[0] * dap[0], vap1 = G[1] * dap[1];
+                const float vh0 = fmaf(van0, Ov[0].x, vap0 * Ov[0].y);  // G dL/dG
+                const float vh1 = fmaf(van1, Ov[1].x, vap1 * Ov[1].y);
+                // rows 0 / 1 of 16 lanes: S, S y, S y^2, colour 0 / colour 1, colour 2,
+                // dL/dA_n, dL/dA_p of the first step; rows 2 / 3 of the second
+                const float D0 = fold16(fold32(vh0, vh1), fold32(aT[0] * g1, aT[1] * g1));
+                const float D1 = fold16(fold32(vh0 * yl, vh1 * yl), fold32(aT[0] * g2, aT[1] * g2));
+                const float D2 = fold16(fold32(vh0 * yl2, vh1 * yl2), fold32(van0, van1));
+                const float D3 = fold16(fold32(aT[0] * g0, aT[1] * g0), fold32(vap0, vap1));
+                const float Sy = fmaf(yq, D0, D1);
+                const float Syy = fmaf(yq, Sy + D1, D2);
+                const float f0 = quad_dot(D0, cw), f1 = quad_dot(Sy, cw), f2 = quad_sum(Syy), f3 = quad_sum(D3);
+                float va = qx == 3 ? f3 : f0, vb = qx == 2 ? f2 : f1;
+                // formed by every lane here, where the lane exchanges fold into the
+                // arithmetic, not under the masks of the adds below
+                asm volatile("" : "+v"(va), "+v"(vb));
+                const uint32_t os = lane & 32 ? off[1] : off[0];
+                if constexpr (DET) {
+                    if (os != kDead) {
+                        float *o = s_gr[4 * w + q][os / kRec];
+                        if (slot_a != 11) o[slot_a] = va;
+                        if (slot_b != 11) o[slot_b] = vb;
+                    }
+                } else {  // past a list's end: zeros, to the dead record
+                    if (slot_a != 11) unsafeAtomicAdd(reinterpret_cast<double *>(s_rec + os + off_a), (double)va);
+                    if (slot_b != 11) unsafeAtomicAdd(reinterpret_cast<double *>(s_rec + os + off_b), (double)vb);
+                }
+                if constexpr (DT) {
+                    float f = fold32(dt[0], dt[1]);
+                    f = quad_sum(fold16(f, f));
+                    if (qx == 0 && low) {
+                        if constexpr (DET) {
+                            if (os != kDead) s_gr[4 * w + q][os / kRec][11] = f;
+                        } else {
+                            unsafeAtomicAdd(&rec_at(os).g[11], (double)f);
+                        }
                     }
                 }
             }
@@ -904,10 +990,14 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
             const double wx = W.x, wy = W.y, wz = W.z, ww = W.w;
             const double2 cr = s_ref[j];
             const double S = g[5];
-            const double P1 = wx * g[0] + wy * g[1], P2 = wz * g[0] + ww * g[1];
-            const double Q11 = wx * wx * g[2] + 2.0 * wx * wy * g[4] + wy * wy * g[3];
-            const double Q22 = wz * wz * g[2] + 2.0 * wz * ww * g[4] + ww * ww * g[3];
-            const double Q12 = wx * wz * g[2] + (wx * ww + wy * wz) * g[4] + wy * ww * g[3];
+            double P1 = g[0], P2 = g[1], Q11 = g[2], Q22 = g[3], Q12 = g[4];
+            if constexpr (!AXES) {
+                P1 = wx * g[0] + wy * g[1];
+                P2 = wz * g[0] + ww * g[1];
+                Q11 = wx * wx * g[2] + 2.0 * wx * wy * g[4] + wy * wy * g[3];
+                Q22 = wz * wz * g[2] + 2.0 * wz * ww * g[4] + ww * ww * g[3];
+                Q12 = wx * wz * g[2] + (wx * ww + wy * wz) * g[4] + wy * ww * g[3];
+            }
             const double P[2] = {P1 + cr.x * S, P2 + cr.y * S};
             const double Q[3] = {Q11 + 2.0 * cr.x * P1 + cr.x * cr.x * S,
                                  Q12 + cr.x * P2 + cr.y * P1 + cr.x * cr.y * S,
