@@ -96,6 +96,7 @@ struct hgs_ctx {
     int nblocks_cap = 0, nv_cap = 0;
     uint64_t *masks = nullptr;
     uint32_t *word_off = nullptr;  // per view and mask word: cut position of its first selected node
+    uint32_t *chunk_order = nullptr;
     uint32_t *blk_counts = nullptr, *blk_offsets = nullptr, *cut_base = nullptr;
     int32_t *cut_ids = nullptr;
     double *cut_t = nullptr;
@@ -444,6 +445,7 @@ hgs_status ensure_cut_cap(hgs_ctx *ctx, uint32_t cap)
     if ((s = realloc_buf(ctx, ctx->trec, cap))) return s;
     if ((s = realloc_buf(ctx, ctx->vis_mask, (size_t)cap / 64 + 8))) return s;
     if ((s = realloc_buf(ctx, ctx->vis_counts, (size_t)cap / 256 + 2))) return s;
+    if ((s = realloc_buf(ctx, ctx->chunk_order, (size_t)cap / 256 + 2))) return s;
     if ((s = realloc_buf(ctx, ctx->vis_offsets, (size_t)cap / 256 + 2))) return s;
     if ((s = realloc_buf(ctx, ctx->skeys, cap))) return s;
     if ((s = realloc_buf(ctx, ctx->svals, cap))) return s;
@@ -508,14 +510,16 @@ void enqueue_forward(hgs_ctx *ctx, int nv, uint32_t n_tiles, hipStream_t st, hip
                 st);
     launch_cut_emit(h, ctx->views_dev, nv, ctx->masks, ctx->blk_offsets, nb, ctx->word_off, ctx->cut_ids, nullptr,
                     ctx->cut_t, ctx->cut_cap, ctx->cut_base, &ctx->ctr->cut_total, st);
+    if (nv > 1)
+        launch_chunk_order(ctx->blk_offsets, nb, nv, &ctx->ctr->cut_total, ctx->chunk_order, ctx->cut_cap, st);
     if (ctx->streaming)  // the cut's nodes and parents made resident in the cache
         launch_stream_frame(ctx->sd, ctx->pinfo, ctx->cut_ids, &ctx->ctr->cut_total, ctx->cut_cap,
                             ctx->host_params_dev, ctx->cache_params, st);
     mark(1);
     launch_preprocess(h, ctx->views_dev, nv, ctx->cut_base, ctx->cut_ids, ctx->cut_t, &ctx->ctr->cut_total,
                       ctx->cut_cap, ctx->recs, ctx->axes, ctx->depth_key, ctx->trec, ctx->ntiles, ctx->cjac,
-                      ctx->vis_mask,
-                      ctx->vis_counts, ctx->tile_w, ctx->tile_h, st);
+                      ctx->vis_mask, ctx->vis_counts, nv > 1 ? ctx->chunk_order : nullptr, ctx->tile_w, ctx->tile_h,
+                      st);
     mark(2);
     const uint32_t vblocks = (ctx->cut_cap + 255) / 256;
     launch_scan(ctx->vis_counts, vblocks, nullptr, ctx->vis_offsets, &ctx->ctr->vis_total, ctx->partial, st);

@@ -231,12 +231,19 @@ void launch_plan_whole(uint32_t cap, const uint32_t *n_dev, int bits, const Sort
 bool launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t cap, int nseg, int bits, const SortScratch &s,
                        hipStream_t st);
 
-// preprocess: interpolation, EWA projection, SH colour, footprint, per cut entry
+// The order of the chunks of 256 cut entries for several views: order[i] = the
+// i-th chunk, all views' chunks of one run of nodes together.  order holds
+// (cap + 255) / 256 entries and is complete when *cut_total <= cap.
+void launch_chunk_order(const uint32_t *block_offsets, int nblocks, int nv, const uint32_t *cut_total,
+                        uint32_t *order, uint32_t cap, hipStream_t st);
+
+// preprocess: interpolation, EWA projection, SH colour, footprint, per cut
+// entry (order: as above, or NULL: list order)
 void launch_preprocess(const DevHier &h, const DevView *views, int nv, const uint32_t *cut_base,
                        const int32_t *cut_ids, const double *cut_t, const uint32_t *cut_total, uint32_t cap,
                        SplatRec *recs, double4 *axes, uint32_t *depth_key, uint4 *trec, uint32_t *ntiles,
-                       float *cjac, uint64_t *vis_mask, uint32_t *vis_block_counts, int tile_w, int tile_h,
-                       hipStream_t st);
+                       float *cjac, uint64_t *vis_mask, uint32_t *vis_block_counts, const uint32_t *order,
+                       int tile_w, int tile_h, hipStream_t st);
 // Also writes vis_rank[k] = compaction position of visible cut entry k (the
 // row of its screen-space gradient).
 void launch_compact_visible(const uint64_t *vis_mask, const uint32_t *vis_block_offsets, const uint32_t *cut_total,

@@ -20,6 +20,31 @@ constexpr double kAlphaMinD = 1.0 / 255.0;
 constexpr int kPG = kPGradFloats;
 static_assert(kPG == 20, "row layout");
 
+// Stores of what only later kernels read: past the L2's reuse, which the
+// parameter records need (3.62 -> 3.54 ms at 30 M visible splats of 32 views,
+// 0.70 -> 0.63 ms at 8 views of a 3 M node hierarchy).
+typedef float nt_f4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_past(float4 *p, float x, float y, float z, float w)
+{
+    __builtin_nontemporal_store((nt_f4{x, y, z, w}), reinterpret_cast<nt_f4 *>(p));
+}
+__device__ __forceinline__ void store_past(double4 *p, const double4 &v)
+{
+    typedef double nt_d2 __attribute__((ext_vector_type(2)));
+    nt_d2 *q = reinterpret_cast<nt_d2 *>(p);
+    __builtin_nontemporal_store((nt_d2{v.x, v.y}), q);
+    __builtin_nontemporal_store((nt_d2{v.z, v.w}), q + 1);
+}
+__device__ __forceinline__ void store_past(SplatRec *p, const SplatRec &r)
+{
+    static_assert(sizeof(SplatRec) == 3 * sizeof(nt_f4), "three quads");
+    nt_f4 q[3];
+    __builtin_memcpy(q, &r, sizeof r);
+    nt_f4 *o = reinterpret_cast<nt_f4 *>(p);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) __builtin_nontemporal_store(q[k], o + k);
+}
+
 __device__ __forceinline__ int view_of(const uint32_t *cut_base, int nv, uint32_t k)
 {
     int lo = 0, hi = nv - 1;
@@ -43,7 +68,78 @@ __device__ __forceinline__ int view_of_wave(const uint32_t *cut_base, int nv, ui
     return k >= b0 && k < b1 ? vf : view_of(cut_base, nv, k);
 }
 
-__global__ __launch_bounds__(kT, 5) void k_preprocess(DevHier h, const DevView *__restrict__ views, int nv,
+// The order in which the chunks of kT cut entries are worked on when there are
+// several views.  The list is view-major, but the views' cuts hold mostly the
+// same nodes (2.3 to 5 views per selected node at 8 to 32 views), 192 B of SH
+// and 48 B of geometry each: chunk after chunk of one view, every view reads
+// them from memory again (17 GB at 30 M visible splats).  Here all views'
+// chunks that begin in a run of kOrderBlocks cut blocks (4096 nodes) follow
+// each other, so that the first one's reads serve the others from the L2: at
+// 30 M visible splats of 32 views 17.0 -> 11.9 GB read and 4.49 -> 4.06 ms, at
+// 8 views of a 3 M node hierarchy 873 -> 775 us.  Runs of 2048 to 16384 nodes
+// are alike within the runs' noise (3%).  A single view's list has nothing to
+// share and keeps its order.
+// One wave per run: lane v holds the chunks of view v that begin there,
+// [ceil(a / kT), ceil(b / kT)) with a and b the run's bounds in the view's
+// list, and the chunks before them in the order are, over all views, those
+// that begin between the view's start and the run.
+constexpr int kOrderBlocks = 4;
+
+__global__ __launch_bounds__(kT) void k_chunk_order(const uint32_t *__restrict__ block_offsets, int nblocks, int nv,
+                                                    const uint32_t *__restrict__ cut_total,
+                                                    uint32_t *__restrict__ order, uint32_t cap_chunks)
+{
+    const int lane = threadIdx.x & 63;
+    const int b0 = (int)(blockIdx.x * (kT / 64) + (threadIdx.x >> 6)) * kOrderBlocks;
+    if (b0 >= nblocks) return;
+    const int b1 = min(b0 + kOrderBlocks, nblocks);
+    const int64_t end = (int64_t)nv * nblocks;
+    auto first = [&](int64_t i) -> uint32_t {  // the first chunk that begins at or behind offset i
+        const uint32_t o = i < end ? block_offsets[i] : *cut_total;
+        return o / kT + (o % kT != 0);
+    };
+    uint32_t before = 0;
+    for (int v = lane; v < nv; v += 64) before += first((int64_t)v * nblocks + b0) - first((int64_t)v * nblocks);
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) before += (uint32_t)__shfl_xor((int)before, d, 64);
+    for (int v0 = 0; v0 < nv; v0 += 64) {
+        const int v = v0 + lane;
+        uint32_t c = 0, n = 0;
+        if (v < nv) {
+            c = first((int64_t)v * nblocks + b0);
+            n = first((int64_t)v * nblocks + b1) - c;
+        }
+        uint32_t inc = n;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t u = (uint32_t)__shfl_up((int)inc, d, 64);
+            if (lane >= d) inc += u;
+        }
+        const uint32_t pos = before + inc - n;
+        for (uint32_t i = 0; i < n; ++i)
+            if (pos + i < cap_chunks) order[pos + i] = c + i;
+        before += (uint32_t)__shfl((int)inc, 63, 64);
+    }
+}
+
+// The chunk of workgroup g of n (at most chunk_grid(n) workgroups), ~0u: none.
+// Workgroups go round robin over the 8 XCDs, each with an L2 of its own: an
+// XCD takes runs of kXcdRun consecutive places of the order (3.53 ms with 64
+// or 128, 3.66 with 256, 3.73 with 1024).
+constexpr uint32_t kXcdRun = 64;
+
+__host__ __device__ __forceinline__ uint32_t chunk_grid(uint32_t n)
+{
+    return (n + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
+}
+
+__device__ __forceinline__ uint32_t chunk_of(const uint32_t *order, uint32_t g, uint32_t n)
+{
+    const uint32_t j = g >> 3, at = ((j / kXcdRun) * 8 + (g & 7u)) * kXcdRun + j % kXcdRun;
+    return at < n ? order[at] : ~0u;
+}
+
+__global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *__restrict__ views, int nv,
                                                    const uint32_t *__restrict__ cut_base,
                                                    const int32_t *__restrict__ cut_ids,
                                                    const double *__restrict__ cut_t,
@@ -52,15 +148,33 @@ __global__ __launch_bounds__(kT, 5) void k_preprocess(DevHier h, const DevView *
                                                    uint32_t *__restrict__ depth_key,
                                                    uint4 *__restrict__ trec, uint32_t *__restrict__ ntiles,
                                                    float *__restrict__ cjac, uint64_t *__restrict__ vis_mask,
-                                                   uint32_t *__restrict__ vis_block_counts, int tile_w, int tile_h)
+                                                   uint32_t *__restrict__ vis_block_counts,
+                                                   const uint32_t *__restrict__ order, int tile_w, int tile_h)
 {
+    __shared__ __align__(16) char s_sh[kT / 64][kShStage];
+    __shared__ uint2 s_src[kT / 64][64];
     __shared__ uint32_t s_cnt;
     if (threadIdx.x == 0) s_cnt = 0;
     __syncthreads();
-    const uint32_t total = min(*cut_total, cap);
-    const uint32_t k = blockIdx.x * kT + threadIdx.x;
+    const uint32_t cut = *cut_total, total = min(cut, cap);
+    const uint32_t nchunks = (total + kT - 1) / kT, cap_chunks = (cap + kT - 1) / kT;
+    uint32_t chunk = blockIdx.x;
+    if (order && cut <= cap) {  // (a cut beyond the capacity is rendered again: any order)
+        // chunks behind the cut stay with the workgroup of their number
+        if (blockIdx.x >= nchunks && blockIdx.x < cap_chunks) {
+            if (threadIdx.x < kT / 64 && blockIdx.x * kT + 64 * threadIdx.x < cap)
+                vis_mask[blockIdx.x * (kT / 64) + threadIdx.x] = 0ull;
+            if (threadIdx.x == 0) vis_block_counts[blockIdx.x] = 0u;
+        }
+        chunk = chunk_of(order, blockIdx.x, nchunks);
+    }
+    if (chunk >= cap_chunks) return;
+    const uint32_t k = chunk * kT + threadIdx.x;
     bool vis = false;
     uint32_t nt = 0;
+    SplatRec r;
+    size_t pn = 0, pp = 0;  // parameter records of the node and, with t > 0, its parent
+    float dir[3] = {0.0f, 0.0f, 0.0f}, t = 0.0f;
     if (k < total) {
         const int vi = view_of_wave(cut_base, nv, k);
         const DevView &V = views[vi];
@@ -85,7 +199,6 @@ __global__ __launch_bounds__(kT, 5) void k_preprocess(DevHier h, const DevView *
                     const uint32_t ty0 = (uint32_t)y0 / tile_h, ty1 = (uint32_t)y1 / tile_h;
                     nt = (tx1 - tx0 + 1) * (ty1 - ty0 + 1);
                     trec[k] = make_uint4(tx0 | (tx1 << 16), ty0 | (ty1 << 16), nt, 0u);
-                    SplatRec r;
                     const double fu = floor(P.u), fv = floor(P.v);
                     r.ax = (int32_t)fu;
                     r.ay = (int32_t)fv;
@@ -112,40 +225,46 @@ __global__ __launch_bounds__(kT, 5) void k_preprocess(DevHier h, const DevView *
                     const double l2 = ca * sn * sn - 2.0 * cb * sn * cs + cc * cs * cs;
                     const double s1 = sqrt(fmax(l1, 0.0) * kHalfLog2e), s2 = sqrt(fmax(l2, 0.0) * kHalfLog2e);
                     const double4 ax4 = make_double4(s1 * cs, s1 * sn, -s2 * sn, s2 * cs);
-                    axes[k] = ax4;
+                    store_past(axes + k, ax4);
                     r.An = (float)(P.kappa * P.o_n);
                     r.Ap = (float)(P.kappa * P.o_p);
                     r.t = (float)P.t;
                     r.invK = (float)(1.0 / (double)P.K);
-                    float raw[3], dcol[3][3], dpn[3];
-                    splat_colour(h, P, raw, dcol, dpn);  // visible splats only
-                    r.r = fmaxf(raw[0], 0.0f);
-                    r.g = fmaxf(raw[1], 0.0f);
-                    r.b = fmaxf(raw[2], 0.0f);
-                    r.unused = 0.0f;
-                    recs[k] = r;
                     depth_key[k] = __float_as_uint((float)P.pc[2]);
-                    float *cj = cjac + (size_t)k * 12;
+                    pn = P.pn;
+                    pp = P.use_par ? P.pp : P.pn;
+                    t = (float)P.t;
 #pragma unroll
-                    for (int ch = 0; ch < 3; ++ch) {
-                        cj[3 * ch] = dcol[ch][0];
-                        cj[3 * ch + 1] = dcol[ch][1];
-                        cj[3 * ch + 2] = dcol[ch][2];
-                        cj[9 + ch] = dpn[ch];
-                    }
+                    for (int c = 0; c < 3; ++c) dir[c] = (float)P.dir[c];
                 }
             }
         }
         ntiles[k] = nt;
     }
     const uint64_t m = __ballot(vis);
-    const uint32_t k0 = blockIdx.x * kT + (threadIdx.x & ~63u);
+    if (m) {
+        float raw[3], dcol[3][3], dpn[3];
+        const int w = threadIdx.x >> 6;
+        splat_colour(h.sh, vis, pn, pp, t, dir, s_sh[w], s_src[w], raw, dcol, dpn);
+        if (vis) {
+            r.r = fmaxf(raw[0], 0.0f);
+            r.g = fmaxf(raw[1], 0.0f);
+            r.b = fmaxf(raw[2], 0.0f);
+            r.unused = 0.0f;
+            store_past(recs + k, r);
+            float4 *cj = reinterpret_cast<float4 *>(cjac + (size_t)k * 12);
+            store_past(cj, dcol[0][0], dcol[0][1], dcol[0][2], dcol[1][0]);
+            store_past(cj + 1, dcol[1][1], dcol[1][2], dcol[2][0], dcol[2][1]);
+            store_past(cj + 2, dcol[2][2], dpn[0], dpn[1], dpn[2]);
+        }
+    }
+    const uint32_t k0 = chunk * kT + (threadIdx.x & ~63u);
     if ((threadIdx.x & 63) == 0) {
         if (k0 < cap) vis_mask[k0 >> 6] = m;
         if (m) atomicAdd(&s_cnt, (uint32_t)__popcll(m));
     }
     __syncthreads();
-    if (threadIdx.x == 0) vis_block_counts[blockIdx.x] = s_cnt;
+    if (threadIdx.x == 0) vis_block_counts[chunk] = s_cnt;
 }
 
 __global__ __launch_bounds__(kT) void k_compact_visible(const uint64_t *__restrict__ vis_mask,
@@ -997,16 +1116,25 @@ __global__ __launch_bounds__(kT, 4) void k_grad_gather(DevHier h, int nv, const 
 
 }  // namespace
 
+void launch_chunk_order(const uint32_t *block_offsets, int nblocks, int nv, const uint32_t *cut_total,
+                        uint32_t *order, uint32_t cap, hipStream_t st)
+{
+    const int runs = (nblocks + kOrderBlocks - 1) / kOrderBlocks, per = kT / 64;
+    hipLaunchKernelGGL(k_chunk_order, dim3((uint32_t)((runs + per - 1) / per)), dim3(kT), 0, st, block_offsets,
+                       nblocks, nv, cut_total, order, (cap + kT - 1) / kT);
+}
+
 void launch_preprocess(const DevHier &h, const DevView *views, int nv, const uint32_t *cut_base,
                        const int32_t *cut_ids, const double *cut_t, const uint32_t *cut_total, uint32_t cap,
                        SplatRec *recs, double4 *axes, uint32_t *depth_key, uint4 *trec, uint32_t *ntiles,
-                       float *cjac, uint64_t *vis_mask, uint32_t *vis_block_counts, int tile_w, int tile_h,
-                       hipStream_t st)
+                       float *cjac, uint64_t *vis_mask, uint32_t *vis_block_counts, const uint32_t *order,
+                       int tile_w, int tile_h, hipStream_t st)
 {
-    const uint32_t blocks = (cap + kT - 1) / kT;
+    uint32_t blocks = (cap + kT - 1) / kT;
     if (!blocks) return;
+    if (order) blocks = chunk_grid(blocks);
     hipLaunchKernelGGL(k_preprocess, dim3(blocks), dim3(kT), 0, st, h, views, nv, cut_base, cut_ids, cut_t, cut_total,
-                       cap, recs, axes, depth_key, trec, ntiles, cjac, vis_mask, vis_block_counts, tile_w, tile_h);
+                       cap, recs, axes, depth_key, trec, ntiles, cjac, vis_mask, vis_block_counts, order, tile_w, tile_h);
 }
 
 void launch_compact_visible(const uint64_t *vis_mask, const uint32_t *vis_block_offsets, const uint32_t *cut_total,
