@@ -21,28 +21,26 @@ constexpr int kPG = kPGradFloats;
 static_assert(kPG == 20, "row layout");
 
 // Stores of what only later kernels read: past the L2's reuse, which the
-// parameter records need (3.62 -> 3.54 ms at 30 M visible splats of 32 views,
-// 0.70 -> 0.63 ms at 8 views of a 3 M node hierarchy).
+// parameter records need.
 typedef float nt_f4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void store_past(float4 *p, float x, float y, float z, float w)
+__device__ __forceinline__ void store_past(float4 *p, const float4 &v)
 {
-    __builtin_nontemporal_store((nt_f4{x, y, z, w}), reinterpret_cast<nt_f4 *>(p));
+    __builtin_nontemporal_store((nt_f4{v.x, v.y, v.z, v.w}), reinterpret_cast<nt_f4 *>(p));
 }
-__device__ __forceinline__ void store_past(double4 *p, const double4 &v)
+
+// Writes the rows of Q quads (16 bytes) that lie one behind the other in
+// `rows` for the 64 lanes of a wave to out, rows of the lanes in m only: in
+// consecutive quads, so that a cache line leaves the wave once and whole
+// instead of in Q parts (with the stores past the L2 the forward preprocess
+// went from 3.62 to 3.35 ms at 30 M visible splats of 32 views).
+template <int Q>
+__device__ __forceinline__ void store_rows(const float4 *rows, float4 *out, uint64_t m, int lane)
 {
-    typedef double nt_d2 __attribute__((ext_vector_type(2)));
-    nt_d2 *q = reinterpret_cast<nt_d2 *>(p);
-    __builtin_nontemporal_store((nt_d2{v.x, v.y}), q);
-    __builtin_nontemporal_store((nt_d2{v.z, v.w}), q + 1);
-}
-__device__ __forceinline__ void store_past(SplatRec *p, const SplatRec &r)
-{
-    static_assert(sizeof(SplatRec) == 3 * sizeof(nt_f4), "three quads");
-    nt_f4 q[3];
-    __builtin_memcpy(q, &r, sizeof r);
-    nt_f4 *o = reinterpret_cast<nt_f4 *>(p);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) __builtin_nontemporal_store(q[k], o + k);
+    for (int i = 0; i < Q; ++i) {
+        const uint32_t e = 64u * i + (uint32_t)lane;
+        if ((m >> (e / Q)) & 1ull) store_past(out + e, rows[e]);
+    }
 }
 
 __device__ __forceinline__ int view_of(const uint32_t *cut_base, int nv, uint32_t k)
@@ -122,7 +120,6 @@ __global__ __launch_bounds__(kT) void k_chunk_order(const uint32_t *__restrict__
     }
 }
 
-// The chunk of workgroup g of n (at most chunk_grid(n) workgroups), ~0u: none.
 // Workgroups go round robin over the 8 XCDs, each with an L2 of its own: an
 // XCD takes runs of kXcdRun consecutive places of the order (3.53 ms with 64
 // or 128, 3.66 with 256, 3.73 with 1024).
@@ -133,10 +130,11 @@ __host__ __device__ __forceinline__ uint32_t chunk_grid(uint32_t n)
     return (n + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
 }
 
-__device__ __forceinline__ uint32_t chunk_of(const uint32_t *order, uint32_t g, uint32_t n)
+// The place in the order of workgroup g's chunk (chunk_grid(n) workgroups).
+__device__ __forceinline__ uint32_t chunk_place(uint32_t g)
 {
-    const uint32_t j = g >> 3, at = ((j / kXcdRun) * 8 + (g & 7u)) * kXcdRun + j % kXcdRun;
-    return at < n ? order[at] : ~0u;
+    const uint32_t j = g >> 3;
+    return ((j / kXcdRun) * 8 + (g & 7u)) * kXcdRun + j % kXcdRun;
 }
 
 __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *__restrict__ views, int nv,
@@ -148,6 +146,7 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
                                                    uint32_t *__restrict__ depth_key,
                                                    uint4 *__restrict__ trec, uint32_t *__restrict__ ntiles,
                                                    float *__restrict__ cjac, uint64_t *__restrict__ vis_mask,
+                                                   uint64_t *__restrict__ pos_mask,
                                                    uint32_t *__restrict__ vis_block_counts,
                                                    const uint32_t *__restrict__ order, int tile_w, int tile_h)
 {
@@ -166,13 +165,16 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
                 vis_mask[blockIdx.x * (kT / 64) + threadIdx.x] = 0ull;
             if (threadIdx.x == 0) vis_block_counts[blockIdx.x] = 0u;
         }
-        chunk = chunk_of(order, blockIdx.x, nchunks);
+        const uint32_t at = chunk_place(blockIdx.x);
+        if (at >= nchunks) return;
+        chunk = order[at];
     }
     if (chunk >= cap_chunks) return;
     const uint32_t k = chunk * kT + threadIdx.x;
     bool vis = false;
     uint32_t nt = 0;
     SplatRec r;
+    double4 ax4 = make_double4(0.0, 0.0, 0.0, 0.0);
     size_t pn = 0, pp = 0;  // parameter records of the node and, with t > 0, its parent
     float dir[3] = {0.0f, 0.0f, 0.0f}, t = 0.0f;
     if (k < total) {
@@ -224,8 +226,7 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
                     const double l1 = ca * cs * cs + 2.0 * cb * sn * cs + cc * sn * sn;
                     const double l2 = ca * sn * sn - 2.0 * cb * sn * cs + cc * cs * cs;
                     const double s1 = sqrt(fmax(l1, 0.0) * kHalfLog2e), s2 = sqrt(fmax(l2, 0.0) * kHalfLog2e);
-                    const double4 ax4 = make_double4(s1 * cs, s1 * sn, -s2 * sn, s2 * cs);
-                    store_past(axes + k, ax4);
+                    ax4 = make_double4(s1 * cs, s1 * sn, -s2 * sn, s2 * cs);
                     r.An = (float)(P.kappa * P.o_n);
                     r.Ap = (float)(P.kappa * P.o_p);
                     r.t = (float)P.t;
@@ -243,20 +244,36 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
     }
     const uint64_t m = __ballot(vis);
     if (m) {
-        float raw[3], dcol[3][3], dpn[3];
-        const int w = threadIdx.x >> 6;
+        float raw[3] = {0.0f, 0.0f, 0.0f}, dcol[3][3], dpn[3];
+        const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
         splat_colour(h.sh, vis, pn, pp, t, dir, s_sh[w], s_src[w], raw, dcol, dpn);
+        // the channels above the colour's clamp at zero
+        const uint64_t p0 = __ballot(vis && raw[0] > 0.0f), p1 = __ballot(vis && raw[1] > 0.0f),
+                       p2 = __ballot(vis && raw[2] > 0.0f);
+        if (lane < 3) pos_mask[(size_t)(k >> 6) * 3 + lane] = lane == 0 ? p0 : (lane == 1 ? p1 : p2);
         if (vis) {
             r.r = fmaxf(raw[0], 0.0f);
             r.g = fmaxf(raw[1], 0.0f);
             r.b = fmaxf(raw[2], 0.0f);
             r.unused = 0.0f;
-            store_past(recs + k, r);
-            float4 *cj = reinterpret_cast<float4 *>(cjac + (size_t)k * 12);
-            store_past(cj, dcol[0][0], dcol[0][1], dcol[0][2], dcol[1][0]);
-            store_past(cj + 1, dcol[1][1], dcol[1][2], dcol[2][0], dcol[2][1]);
-            store_past(cj + 2, dcol[2][2], dpn[0], dpn[1], dpn[2]);
         }
+        // record, colour Jacobian and axes, row by row through the LDS
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+        float4 *o = reinterpret_cast<float4 *>(s_sh[w]);
+        static_assert(sizeof(SplatRec) == 48 && kShStage >= 64 * (48 + 48 + 32), "rows of 3, 3 and 2 quads");
+        if (vis) {
+            __builtin_memcpy(o + 3 * lane, &r, sizeof r);
+            o[192 + 3 * lane] = make_float4(dcol[0][0], dcol[0][1], dcol[0][2], dcol[1][0]);
+            o[193 + 3 * lane] = make_float4(dcol[1][1], dcol[1][2], dcol[2][0], dcol[2][1]);
+            o[194 + 3 * lane] = make_float4(dcol[2][2], dpn[0], dpn[1], dpn[2]);
+            __builtin_memcpy(o + 384 + 2 * lane, &ax4, sizeof ax4);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const size_t kw = k & ~63u;
+        store_rows<3>(o, reinterpret_cast<float4 *>(recs + kw), m, lane);
+        store_rows<3>(o + 192, reinterpret_cast<float4 *>(cjac + 12 * kw), m, lane);
+        store_rows<2>(o + 384, reinterpret_cast<float4 *>(axes + kw), m, lane);
     }
     const uint32_t k0 = chunk * kT + (threadIdx.x & ~63u);
     if ((threadIdx.x & 63) == 0) {
@@ -272,8 +289,7 @@ __global__ __launch_bounds__(kT) void k_compact_visible(const uint64_t *__restri
                                                         const uint32_t *__restrict__ cut_total, uint32_t cap,
                                                         const uint32_t *__restrict__ depth_key,
                                                         uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
-                                                        uint32_t *__restrict__ vis_rank,
-                                                        uint32_t *__restrict__ vis_entry)
+                                                        uint32_t *__restrict__ vis_rank)
 {
     const uint32_t total = min(*cut_total, cap);
     const uint32_t k = blockIdx.x * kT + threadIdx.x;
@@ -297,7 +313,6 @@ __global__ __launch_bounds__(kT) void k_compact_visible(const uint64_t *__restri
         keys[pos] = depth_key[k];
         vals[pos] = k;
         vis_rank[k] = pos;
-        vis_entry[pos] = k;
     }
 }
 
@@ -638,58 +653,30 @@ __global__ void k_fill_u32(uint32_t *__restrict__ p, uint32_t value, size_t n)
 }
 
 // ------------------------------------------------------------------ backward
-// Thread v takes the v-th visible cut entry (vis_entry lists them in cut
-// order, so that every wave holds visible entries only) and writes its
-// attribute-gradient row at the entry's cut position; rows of entries that
-// are not visible are never read.  With g_dt, thread k also clears dL/dt of
-// cut entry k when it is not visible.
-__global__ __launch_bounds__(kT, 3) void k_preprocess_bwd(DevHier h, const DevView *__restrict__ views, int nv,
-                                                       const uint32_t *__restrict__ cut_base,
-                                                       const int32_t *__restrict__ cut_ids,
-                                                       const double *__restrict__ cut_t,
-                                                       const uint32_t *__restrict__ cut_total, uint32_t cap,
-                                                       const uint32_t *__restrict__ ntiles,
-                                                       const SplatRec *__restrict__ recs,
-                                                       const float *__restrict__ cjac,
-                                                       const uint32_t *__restrict__ vis_entry,
-                                                       const uint32_t *__restrict__ vis_total,
-                                                       const double *__restrict__ sgrad, float *__restrict__ pg,
-                                                       float *__restrict__ g_dt)
+// The attribute-gradient row of cut entry k of view V (zero when it does not
+// project), and its dL/dt, from its screen-gradient row sg, its colour Jacobian
+// cj (both in LDS) and the words pos of its colour channels above the clamp.
+__device__ __forceinline__ void entry_bwd(const DevHier &h, const DevView &V, uint32_t k, uint32_t node_id,
+                                          double t_in, const uint64_t *__restrict__ pos, const double *sg,
+                                          const float *cj, float (&row)[kPG], float &dt_out)
 {
-    const uint32_t total = min(*cut_total, cap);
-    const uint32_t vis = min(*vis_total, total);
-    const uint32_t tid = blockIdx.x * kT + threadIdx.x;
-    if (g_dt && tid < total && ntiles[tid] == 0) g_dt[tid] = 0.0f;
-    if (tid >= vis) return;
-    const uint32_t k = vis_entry[tid];
-    float *out = pg + (size_t)k * kPG;
-    float row[kPG];  // the entry's attribute gradient, stored as five float4
-    const double *sg = sgrad + (size_t)tid * 12;  // screen-gradient rows by visible rank
+    Proj P;
+    project_splat(h, V, node_id, t_in, P);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the LDS rows have arrived
+    if (!P.ok) return;
     const double du = sg[0], dv = sg[1], dAn = sg[5], dAp = sg[6];
     const double drgb[3] = {sg[7], sg[8], sg[9]};
     double dt = sg[10];
-    const int vi = view_of_wave(cut_base, nv, k);
-    const DevView &V = views[vi];
-    Proj P;
-    project_splat(h, V, (uint32_t)cut_ids[k], cut_t[k], P);
-    if (!P.ok) {
-        out[kPG - 1] = 0.0f;
-        if (g_dt) g_dt[k] = 0.0f;
-        return;
-    }
     const uint32_t node = P.node, par = P.par;
-    const bool node_leaf = (h.pinfo[node] & kLeafBit) != 0;
     const bool use_par = P.has_par && P.t > 0.0;
     const double t = P.t, w0 = 1.0 - t;
 
-    // colour: rgb = max(0, raw); the forward kept rgb, d raw / d dir and
+    // colour: rgb = max(0, raw); the forward kept raw > 0, d raw / d dir and
     // (SH_p - SH_n) . Y per channel
-    const SplatRec rec = recs[k];
-    const float *cj = cjac + (size_t)k * 12;
     double gr[3];
-    gr[0] = rec.r > 0.0f ? drgb[0] : 0.0;
-    gr[1] = rec.g > 0.0f ? drgb[1] : 0.0;
-    gr[2] = rec.b > 0.0f ? drgb[2] : 0.0;
+    gr[0] = (pos[0] >> (k & 63u)) & 1ull ? drgb[0] : 0.0;
+    gr[1] = (pos[1] >> (k & 63u)) & 1ull ? drgb[1] : 0.0;
+    gr[2] = (pos[2] >> (k & 63u)) & 1ull ? drgb[2] : 0.0;
     double ddir[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -830,11 +817,93 @@ __global__ __launch_bounds__(kT, 3) void k_preprocess_bwd(DevHier h, const DevVi
     row[10] = (float)((P.on_raw > 0.0 ? 1.0 : (P.on_raw < 0.0 ? -1.0 : 0.0)) * don);
     row[11] = (float)((P.op_raw > 0.0 ? 1.0 : (P.op_raw < 0.0 ? -1.0 : 0.0)) * dop);
     row[kPG - 1] = 1.0f;
-    float4 *out4 = reinterpret_cast<float4 *>(out);
+    dt_out = use_par ? (float)dt : 0.0f;
+}
+
+// Takes the chunks of cut entries in the forward's order and writes, for the
+// visible ones, the attribute-gradient rows at their cut positions; rows of
+// entries that are not visible are never read.  With g_dt, dL/dt of those is
+// cleared.  A wave's screen-gradient rows lie one behind the other (visible
+// entries rank in cut order), and so do its colour Jacobians and the rows it
+// writes: all three pass through the wave's LDS in whole lines, the loads
+// under way while the entries are projected.  2.63 -> 2.11 ms at 30 M visible
+// splats of 32 views, 572 -> 444 us at 8 views of a 3 M node hierarchy (of it
+// 0.13 ms and 46 us are the order's); what bounds it now is half memory (a
+// 96-byte row, a 48-byte Jacobian and the parameters read, 80 bytes written)
+// and half FP64 arithmetic at 4 waves per SIMD.  Listing the entries whose row
+// is not all zero first (64% of them) was slower: 3.2 ms, the list is a longer
+// chain than the work saved.
+__global__ __launch_bounds__(kT, 4) void k_preprocess_bwd(DevHier h, const DevView *__restrict__ views, int nv,
+                                                       const uint32_t *__restrict__ cut_base,
+                                                       const int32_t *__restrict__ cut_ids,
+                                                       const double *__restrict__ cut_t,
+                                                       const uint32_t *__restrict__ cut_total, uint32_t cap,
+                                                       const uint64_t *__restrict__ vis_mask,
+                                                       const uint64_t *__restrict__ pos_mask,
+                                                       const float *__restrict__ cjac,
+                                                       const uint32_t *__restrict__ vis_offsets,
+                                                       const uint32_t *__restrict__ order,
+                                                       const double *__restrict__ sgrad, float *__restrict__ pg,
+                                                       float *__restrict__ g_dt)
+{
+    // per wave: 64 rows of 96 B (screen gradients) and 64 of 48 B (Jacobians);
+    // the 64 rows of 80 B written take the place of the former
+    constexpr int kRows = 64 * 96, kStage = kRows + 64 * 48;
+    static_assert(64 * kPG * 4 <= kRows, "the written rows fit");
+    __shared__ __align__(16) char s_stage[kT / 64][kStage];
+    const uint32_t total = min(*cut_total, cap), nchunks = (total + kT - 1) / kT;
+    const uint32_t at = order ? chunk_place(blockIdx.x) : blockIdx.x;
+    if (at >= nchunks) return;
+    const uint32_t chunk = order ? order[at] : at;
+    const uint32_t k = chunk * kT + threadIdx.x;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    uint32_t rank = vis_offsets[chunk];  // of the wave's first visible entry
+    uint64_t m = 0ull;                   // its visible entries
 #pragma unroll
-    for (int q = 0; q < kPG / 4; ++q)
-        out4[q] = make_float4(row[4 * q], row[4 * q + 1], row[4 * q + 2], row[4 * q + 3]);
-    if (g_dt) g_dt[k] = use_par ? (float)dt : 0.0f;
+    for (int q = 0; q < kT / 64; ++q) {
+        const uint64_t mq = vis_mask[chunk * (kT / 64) + q];
+        if (q < w) rank += (uint32_t)__popcll(mq);
+        if (q == w) m = mq;
+    }
+    m = (uint64_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)m) & 0xFFFFFFFFull |
+        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(m >> 32)) << 32;
+    const bool seen = (m >> lane) & 1ull;
+    if (g_dt && !seen && k < total) g_dt[k] = 0.0f;
+    if (m == 0ull) return;
+    char *stage = s_stage[w];
+    const uint32_t cnt = (uint32_t)__popcll(m), kw = k & ~63u;
+    const float *rows = reinterpret_cast<const float *>(sgrad + (size_t)rank * 12);
+    const float *jac = cjac + (size_t)kw * 12;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        const uint32_t e = 64u * i + (uint32_t)lane;
+        if (e < 6u * cnt) load_lds16(rows + 4 * e, stage + 1024 * i);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const uint32_t e = 64u * i + (uint32_t)lane;
+        if ((m >> (e / 3u)) & 1ull) load_lds16(jac + 4 * e, stage + kRows + 1024 * i);
+    }
+    float row[kPG];
+#pragma unroll
+    for (int q = 0; q < kPG; ++q) row[q] = 0.0f;
+    if (seen) {
+        float dt = 0.0f;
+        const uint32_t r = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        entry_bwd(h, views[view_of_wave(cut_base, nv, k)], k, (uint32_t)cut_ids[k], cut_t[k],
+                  pos_mask + (size_t)(k >> 6) * 3, reinterpret_cast<const double *>(stage + 96 * r),
+                  reinterpret_cast<const float *>(stage + kRows + 48 * lane), row, dt);
+        if (g_dt) g_dt[k] = dt;
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+    float4 *o = reinterpret_cast<float4 *>(stage);
+    if (seen)
+#pragma unroll
+        for (int q = 0; q < kPG / 4; ++q)
+            o[kPG / 4 * lane + q] = make_float4(row[4 * q], row[4 * q + 1], row[4 * q + 2], row[4 * q + 3]);
+    __builtin_amdgcn_wave_barrier();
+    store_rows<kPG / 4>(o, reinterpret_cast<float4 *>(pg + (size_t)kw * kPG), m, lane);
 }
 
 // Gathers each interior node's parameter gradient from the cut entries of
@@ -1127,24 +1196,25 @@ void launch_chunk_order(const uint32_t *block_offsets, int nblocks, int nv, cons
 void launch_preprocess(const DevHier &h, const DevView *views, int nv, const uint32_t *cut_base,
                        const int32_t *cut_ids, const double *cut_t, const uint32_t *cut_total, uint32_t cap,
                        SplatRec *recs, double4 *axes, uint32_t *depth_key, uint4 *trec, uint32_t *ntiles,
-                       float *cjac, uint64_t *vis_mask, uint32_t *vis_block_counts, const uint32_t *order,
-                       int tile_w, int tile_h, hipStream_t st)
+                       float *cjac, uint64_t *vis_mask, uint64_t *pos_mask, uint32_t *vis_block_counts,
+                       const uint32_t *order, int tile_w, int tile_h, hipStream_t st)
 {
     uint32_t blocks = (cap + kT - 1) / kT;
     if (!blocks) return;
     if (order) blocks = chunk_grid(blocks);
     hipLaunchKernelGGL(k_preprocess, dim3(blocks), dim3(kT), 0, st, h, views, nv, cut_base, cut_ids, cut_t, cut_total,
-                       cap, recs, axes, depth_key, trec, ntiles, cjac, vis_mask, vis_block_counts, order, tile_w, tile_h);
+                       cap, recs, axes, depth_key, trec, ntiles, cjac, vis_mask, pos_mask, vis_block_counts, order, tile_w,
+                       tile_h);
 }
 
 void launch_compact_visible(const uint64_t *vis_mask, const uint32_t *vis_block_offsets, const uint32_t *cut_total,
                             uint32_t cap, const uint32_t *depth_key, uint32_t *keys, uint32_t *vals,
-                            uint32_t *vis_rank, uint32_t *vis_entry, hipStream_t st)
+                            uint32_t *vis_rank, hipStream_t st)
 {
     const uint32_t blocks = (cap + kT - 1) / kT;
     if (!blocks) return;
     hipLaunchKernelGGL(k_compact_visible, dim3(blocks), dim3(kT), 0, st, vis_mask, vis_block_offsets, cut_total, cap,
-                       depth_key, keys, vals, vis_rank, vis_entry);
+                       depth_key, keys, vals, vis_rank);
 }
 
 void launch_zero_rows(double *rows, int width, const uint32_t *vis_total, uint32_t vis_cap, hipStream_t st)
@@ -1239,17 +1309,19 @@ void launch_fill_u32(uint32_t *p, uint32_t value, size_t n, hipStream_t st)
 
 void launch_preprocess_backward(const DevHier &h, const DevView *views, int nv, const uint32_t *cut_base,
                                 const int32_t *cut_ids, const double *cut_t, const uint32_t *cut_total, uint32_t cap,
-                                const uint32_t *ntiles, const SplatRec *recs, const float *cjac,
-                                const uint32_t *vis_entry, const uint32_t *vis_total, const double *sgrad, float *pg,
+                                const uint32_t *ntiles, const uint64_t *vis_mask, const uint64_t *pos_mask,
+                                const float *cjac, const uint32_t *vis_offsets,
+                                const uint32_t *order, const double *sgrad, float *pg,
                                 const uint64_t *masks, int64_t words, const uint32_t *word_off,
                                 const int32_t *interior, int64_t n_interior,
                                 float *g_mean, float *g_scale, float *g_rot, float *g_opacity, float *g_sh,
                                 float *g_dt, const AdamRows *fused, hipStream_t st)
 {
-    const uint32_t blocks = (cap + kT - 1) / kT;
+    uint32_t blocks = (cap + kT - 1) / kT;
     if (!blocks) return;
+    if (order) blocks = chunk_grid(blocks);
     hipLaunchKernelGGL(k_preprocess_bwd, dim3(blocks), dim3(kT), 0, st, h, views, nv, cut_base, cut_ids, cut_t,
-                       cut_total, cap, ntiles, recs, cjac, vis_entry, vis_total, sgrad, pg, g_dt);
+                       cut_total, cap, vis_mask, pos_mask, cjac, vis_offsets, order, sgrad, pg, g_dt);
     const int64_t gblocks = (n_interior + kT - 1) / kT;
     if (!gblocks) return;
     if (fused)
