@@ -60,26 +60,29 @@ __device__ __forceinline__ void sh_grad_dot(double x, double y, double z, const 
            c14 * (xx - yy) * B[14];
 }
 
-// FP32 versions for the forward colour (stored in FP32 afterwards).
+// FP32 versions for the forward colour (stored in FP32 afterwards).  The sums
+// are written as the FMAs they are, so that every kernel that evaluates the
+// basis rounds it alike.
 __device__ __forceinline__ void sh_eval_f(float x, float y, float z, float Y[16])
 {
     const float xx = x * x, yy = y * y, zz = z * z;
+    const float x2y2 = fmaf(x, x, -yy), z51 = fmaf(5.0f, zz, -1.0f);
     Y[0] = 0.28209479177387814f;
     Y[1] = 0.4886025119029199f * y;
     Y[2] = 0.4886025119029199f * z;
     Y[3] = 0.4886025119029199f * x;
     Y[4] = 1.0925484305920792f * x * y;
     Y[5] = 1.0925484305920792f * y * z;
-    Y[6] = 0.31539156525252005f * (3.0f * zz - 1.0f);
+    Y[6] = 0.31539156525252005f * fmaf(3.0f, zz, -1.0f);
     Y[7] = 1.0925484305920792f * x * z;
-    Y[8] = 0.5462742152960396f * (xx - yy);
-    Y[9] = 0.5900435899266435f * y * (3.0f * xx - yy);
+    Y[8] = 0.5462742152960396f * x2y2;
+    Y[9] = 0.5900435899266435f * y * fmaf(3.0f, xx, -yy);
     Y[10] = 2.890611442640554f * x * y * z;
-    Y[11] = 0.4570457994644658f * y * (5.0f * zz - 1.0f);
-    Y[12] = 0.3731763325901154f * z * (5.0f * zz - 3.0f);
-    Y[13] = 0.4570457994644658f * x * (5.0f * zz - 1.0f);
-    Y[14] = 1.445305721320277f * z * (xx - yy);
-    Y[15] = 0.5900435899266435f * x * (xx - 3.0f * yy);
+    Y[11] = 0.4570457994644658f * y * z51;
+    Y[12] = 0.3731763325901154f * z * fmaf(5.0f, zz, -3.0f);
+    Y[13] = 0.4570457994644658f * x * z51;
+    Y[14] = 1.445305721320277f * z * x2y2;
+    Y[15] = 0.5900435899266435f * x * fmaf(-3.0f, yy, xx);
 }
 
 __device__ __forceinline__ void sh_grad_dot_f(float x, float y, float z, const float B[16], float g[3])
@@ -311,9 +314,9 @@ __device__ __forceinline__ void splat_colour(const float *__restrict__ sh, bool 
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int q = 4 * (kShQuads * pass + c) + e, k = q / 3, ch = q % 3;  // coefficient 3 k + ch
-                    sht[q] = w0 * cn[e] + t * cp[e];
-                    acc[ch] += sht[q] * Y[k];
-                    dp[ch] += (cp[e] - cn[e]) * Y[k];
+                    sht[q] = fmaf(w0, cn[e], t * cp[e]);
+                    acc[ch] = fmaf(sht[q], Y[k], acc[ch]);
+                    dp[ch] = fmaf(cp[e] - cn[e], Y[k], dp[ch]);
                 }
             }
         }
