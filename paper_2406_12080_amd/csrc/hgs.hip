@@ -128,6 +128,9 @@ struct hgs_ctx {
     double *sgrad = nullptr;     // [visible rank][12] screen-space gradients
     uint32_t *vis_rank = nullptr;  // per cut entry: its visible rank (visible entries only)
     uint64_t *pos_mask = nullptr;  // per 64 cut entries three words: colour channels above the clamp
+    uint64_t *live = nullptr;  // per 64 cut entries a word: those with an attribute-gradient row
+    uint64_t *sel = nullptr;   // the same by node, as many words as masks
+    uint64_t *word_views = nullptr;  // per mask word and 64 views, the views with such a node
     float *pgrad = nullptr;  // per cut entry, kPGradFloats floats
     float *cjac = nullptr;   // per cut entry, 12 floats: d colour / d dir, parent - node colour
 
@@ -400,6 +403,8 @@ hgs_status ensure_fixed(hgs_ctx *ctx, int nv, uint32_t n_tiles, size_t n_pix)
         const int nvc = std::max(nv, ctx->nv_cap), nbc = std::max(nb, ctx->nblocks_cap);
         const size_t words = (size_t)((ctx->n + 63) / 64);
         if ((s = realloc_buf(ctx, ctx->masks, words * nvc + 1))) return s;
+        if ((s = realloc_buf(ctx, ctx->sel, words * nvc + 1))) return s;
+        if ((s = realloc_buf(ctx, ctx->word_views, words * ((nvc + 63) / 64) + 1))) return s;
         if ((s = realloc_buf(ctx, ctx->word_off, words * nvc + 1))) return s;
         if ((s = realloc_buf(ctx, ctx->blk_counts, (size_t)nbc * nvc))) return s;
         if ((s = realloc_buf(ctx, ctx->blk_offsets, (size_t)nbc * nvc))) return s;
@@ -452,6 +457,7 @@ hgs_status ensure_cut_cap(hgs_ctx *ctx, uint32_t cap)
     if ((s = realloc_buf(ctx, ctx->pair_offsets, cap))) return s;
     if ((s = realloc_buf(ctx, ctx->sgrad, (size_t)cap * 12))) return s;
     if ((s = realloc_buf(ctx, ctx->vis_rank, (size_t)cap))) return s;
+    if ((s = realloc_buf(ctx, ctx->live, (size_t)cap / 64 + 8))) return s;
     if ((s = realloc_buf(ctx, ctx->pos_mask, ((size_t)cap / 256 + 2) * 12))) return s;
     if ((s = realloc_buf(ctx, ctx->pgrad, (size_t)cap * kPGradFloats))) return s;
     if ((s = realloc_buf(ctx, ctx->cjac, (size_t)cap * 12))) return s;
@@ -631,9 +637,9 @@ void enqueue_backward(hgs_ctx *ctx, int nv, const hgs_grads *out, const AdamRows
     {
         KernelTimer kt(ctx, 2, st);
         launch_preprocess_backward(h, ctx->views_dev, nv, ctx->cut_base, ctx->cut_ids, ctx->cut_t,
-                                   &ctx->ctr->cut_total, ctx->cut_cap, ctx->ntiles, ctx->vis_mask, ctx->pos_mask,
-                                   ctx->cjac, ctx->vis_offsets, nv > 1 ? ctx->chunk_order : nullptr, ctx->sgrad, ctx->pgrad, ctx->masks,
-                                   (ctx->n + 63) / 64,
+                                   &ctx->ctr->cut_total, ctx->cut_cap, ctx->vis_mask, ctx->pos_mask, ctx->cjac,
+                                   ctx->vis_offsets, nv > 1 ? ctx->chunk_order : nullptr, ctx->sgrad, ctx->pgrad,
+                                   ctx->live, ctx->sel, ctx->word_views, ctx->masks, (ctx->n + 63) / 64,
                                    ctx->word_off, ctx->interior, ctx->n_interior, out ? out->mean : nullptr,
                                    out ? out->scale : nullptr, out ? out->rot : nullptr,
                                    out ? out->opacity : nullptr, out ? out->sh : nullptr, out ? out->dt : nullptr,

@@ -425,13 +425,15 @@ struct AdamRows {
 };
 void launch_zero_rows(double *rows, int width, const uint32_t *vis_total, uint32_t vis_cap, hipStream_t st);
 // pos_mask: three words per 64 cut entries, the colour channels above the
-// clamp.  order: the forward's, or NULL.
+// clamp.  order: the forward's, or NULL.  live: a word per 64 cut entries;
+// sel: as many words as masks; word_views: per mask word of
+// one view a word for every 64 views (all three written here).
 void launch_preprocess_backward(const DevHier &h, const DevView *views, int nv, const uint32_t *cut_base,
                                 const int32_t *cut_ids, const double *cut_t, const uint32_t *cut_total, uint32_t cap,
-                                const uint32_t *ntiles, const uint64_t *vis_mask, const uint64_t *pos_mask,
-                                const float *cjac, const uint32_t *vis_offsets,
-                                const uint32_t *order, const double *sgrad, float *pg,
-                                const uint64_t *masks, int64_t words, const uint32_t *word_off,
+                                const uint64_t *vis_mask, const uint64_t *pos_mask, const float *cjac,
+                                const uint32_t *vis_offsets,
+                                const uint32_t *order, const double *sgrad, float *pg, uint64_t *live,
+                                uint64_t *sel, uint64_t *word_views, const uint64_t *masks, int64_t words, const uint32_t *word_off,
                                 const int32_t *interior, int64_t n_interior, float *g_mean, float *g_scale,
                                 float *g_rot, float *g_opacity, float *g_sh, float *g_dt, const AdamRows *fused,
                                 hipStream_t st);

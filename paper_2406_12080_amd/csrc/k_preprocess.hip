@@ -16,7 +16,7 @@ constexpr double kAlphaMinD = 1.0 / 255.0;
 // per cut entry, gradient w.r.t. the interpolated attributes: mean 0..2,
 // scale 3..5, raw quaternion 6..9, node opacity 10, parent opacity 11,
 // colour cotangent 12..14, view direction 15..17 (the SH basis follows from
-// it in the gather, as the forward evaluated it), 18 unused, live flag 19
+// it in the gather, as the forward evaluated it), t 18, 19 unused
 constexpr int kPG = kPGradFloats;
 static_assert(kPG == 20, "row layout");
 
@@ -653,12 +653,12 @@ __global__ void k_fill_u32(uint32_t *__restrict__ p, uint32_t value, size_t n)
 }
 
 // ------------------------------------------------------------------ backward
-// The attribute-gradient row of cut entry k of view V (zero when it does not
-// project), and its dL/dt, from its screen-gradient row sg, its colour Jacobian
+// The attribute-gradient row of cut entry k of view V and its dL/dt, if it
+// projects and its screen-gradient row is not all zeros (`any`), from its screen-gradient row sg, its colour Jacobian
 // cj (both in LDS) and the words pos of its colour channels above the clamp.
 __device__ __forceinline__ void entry_bwd(const DevHier &h, const DevView &V, uint32_t k, uint32_t node_id,
                                           double t_in, const uint64_t *__restrict__ pos, const double *sg,
-                                          const float *cj, float (&row)[kPG], float &dt_out)
+                                          const float *cj, float (&row)[kPG], bool &any, float &dt_out)
 {
     Proj P;
     project_splat(h, V, node_id, t_in, P);
@@ -667,6 +667,9 @@ __device__ __forceinline__ void entry_bwd(const DevHier &h, const DevView &V, ui
     const double du = sg[0], dv = sg[1], dAn = sg[5], dAp = sg[6];
     const double drgb[3] = {sg[7], sg[8], sg[9]};
     double dt = sg[10];
+    any = !(du == 0.0 && dv == 0.0 && sg[2] == 0.0 && sg[3] == 0.0 && sg[4] == 0.0 && dAn == 0.0 && dAp == 0.0 &&
+            drgb[0] == 0.0 && drgb[1] == 0.0 && drgb[2] == 0.0 && dt == 0.0);
+    if (!any) return;
     const uint32_t node = P.node, par = P.par;
     const bool use_par = P.has_par && P.t > 0.0;
     const double t = P.t, w0 = 1.0 - t;
@@ -688,7 +691,7 @@ __device__ __forceinline__ void entry_bwd(const DevHier &h, const DevView &V, ui
     row[15] = (float)P.dir[0];
     row[16] = (float)P.dir[1];
     row[17] = (float)P.dir[2];
-    row[18] = 0.0f;
+    row[18] = (float)t;
     row[12] = (float)gr[0];
     row[13] = (float)gr[1];
     row[14] = (float)gr[2];
@@ -816,13 +819,15 @@ __device__ __forceinline__ void entry_bwd(const DevHier &h, const DevView &V, ui
     // opacity through |o|
     row[10] = (float)((P.on_raw > 0.0 ? 1.0 : (P.on_raw < 0.0 ? -1.0 : 0.0)) * don);
     row[11] = (float)((P.op_raw > 0.0 ? 1.0 : (P.op_raw < 0.0 ? -1.0 : 0.0)) * dop);
-    row[kPG - 1] = 1.0f;
+    row[kPG - 1] = 0.0f;
     dt_out = use_par ? (float)dt : 0.0f;
 }
 
 // Takes the chunks of cut entries in the forward's order and writes, for the
-// visible ones, the attribute-gradient rows at their cut positions; rows of
-// entries that are not visible are never read.  With g_dt, dL/dt of those is
+// visible ones that reached a pixel (more than a third at 32 views far into a
+// scene did not: their screen-gradient row is all zeros), the attribute-
+// gradient rows at their cut positions; live: one bit per cut entry, the rows
+// that the gather has to read.  With g_dt, dL/dt of all others is
 // cleared.  A wave's screen-gradient rows lie one behind the other (visible
 // entries rank in cut order), and so do its colour Jacobians and the rows it
 // writes: all three pass through the wave's LDS in whole lines, the loads
@@ -833,7 +838,7 @@ __device__ __forceinline__ void entry_bwd(const DevHier &h, const DevView &V, ui
 // and half FP64 arithmetic at 4 waves per SIMD.  Listing the entries whose row
 // is not all zero first (64% of them) was slower: 3.2 ms, the list is a longer
 // chain than the work saved.
-__global__ __launch_bounds__(kT, 4) void k_preprocess_bwd(DevHier h, const DevView *__restrict__ views, int nv,
+__global__ __launch_bounds__(kT, 3) void k_preprocess_bwd(DevHier h, const DevView *__restrict__ views, int nv,
                                                        const uint32_t *__restrict__ cut_base,
                                                        const int32_t *__restrict__ cut_ids,
                                                        const double *__restrict__ cut_t,
@@ -844,7 +849,7 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess_bwd(DevHier h, const DevVi
                                                        const uint32_t *__restrict__ vis_offsets,
                                                        const uint32_t *__restrict__ order,
                                                        const double *__restrict__ sgrad, float *__restrict__ pg,
-                                                       float *__restrict__ g_dt)
+                                                       uint64_t *__restrict__ live, float *__restrict__ g_dt)
 {
     // per wave: 64 rows of 96 B (screen gradients) and 64 of 48 B (Jacobians);
     // the 64 rows of 80 B written take the place of the former
@@ -869,7 +874,10 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess_bwd(DevHier h, const DevVi
         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(m >> 32)) << 32;
     const bool seen = (m >> lane) & 1ull;
     if (g_dt && !seen && k < total) g_dt[k] = 0.0f;
-    if (m == 0ull) return;
+    if (m == 0ull) {
+        if (lane == 0) live[k >> 6] = 0ull;
+        return;
+    }
     char *stage = s_stage[w];
     const uint32_t cnt = (uint32_t)__popcll(m), kw = k & ~63u;
     const float *rows = reinterpret_cast<const float *>(sgrad + (size_t)rank * 12);
@@ -887,12 +895,13 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess_bwd(DevHier h, const DevVi
     float row[kPG];
 #pragma unroll
     for (int q = 0; q < kPG; ++q) row[q] = 0.0f;
+    bool any = false;
     if (seen) {
         float dt = 0.0f;
         const uint32_t r = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
         entry_bwd(h, views[view_of_wave(cut_base, nv, k)], k, (uint32_t)cut_ids[k], cut_t[k],
                   pos_mask + (size_t)(k >> 6) * 3, reinterpret_cast<const double *>(stage + 96 * r),
-                  reinterpret_cast<const float *>(stage + kRows + 48 * lane), row, dt);
+                  reinterpret_cast<const float *>(stage + kRows + 48 * lane), row, any, dt);
         if (g_dt) g_dt[k] = dt;
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -903,7 +912,56 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess_bwd(DevHier h, const DevVi
         for (int q = 0; q < kPG / 4; ++q)
             o[kPG / 4 * lane + q] = make_float4(row[4 * q], row[4 * q + 1], row[4 * q + 2], row[4 * q + 3]);
     __builtin_amdgcn_wave_barrier();
-    store_rows<kPG / 4>(o, reinterpret_cast<float4 *>(pg + (size_t)kw * kPG), m, lane);
+    const uint64_t lm = __ballot(any);
+    if (lane == 0) live[k >> 6] = lm;
+    store_rows<kPG / 4>(o, reinterpret_cast<float4 *>(pg + (size_t)kw * kPG), lm, lane);
+}
+
+// Per view and mask word, the nodes whose cut entry has an attribute-gradient
+// row (sel): the entries' bits live[...] of the word's run in the cut, spread
+// to the places of the selected nodes.  A workgroup takes 64 words of 8 views,
+// one wave per view, and also notes which of the views have a node in a word:
+// word_views holds, for every 64 views, 64 bits per word.
+constexpr int kLiveViews = 8;
+
+__global__ __launch_bounds__(64 * kLiveViews) void k_live_nodes(
+    const uint64_t *__restrict__ masks, const uint32_t *__restrict__ word_off, int64_t words, int nv,
+    const uint64_t *__restrict__ live, const uint32_t *__restrict__ cut_total, uint32_t cap,
+    uint64_t *__restrict__ sel, uint8_t *__restrict__ word_views)
+{
+    __shared__ uint64_t s_has[kLiveViews];  // per view, its words with a node
+    const int lane = threadIdx.x & 63, u = threadIdx.x >> 6, v = blockIdx.y * kLiveViews + u;
+    const int64_t w = (int64_t)blockIdx.x * 64 + lane;
+    uint64_t r = 0ull;
+    if (w < words && v < nv) {
+        const int64_t i = (int64_t)v * words + w;
+        const uint64_t m = masks[i];
+        if (m) {
+            const uint32_t total = min(*cut_total, cap), p = word_off[i], sh = p & 63u;
+            const uint32_t n = p < total ? min((uint32_t)__popcll(m), total - p) : 0u;
+            uint64_t b = 0ull;  // the run's bits
+            if (n) b = live[p >> 6] >> sh;
+            if (sh + n > 64u) b |= live[(p >> 6) + 1] << (64u - sh);
+            if (n < 64u) b &= (1ull << n) - 1ull;
+            if (n == 64u) r = b;
+            else
+                for (uint64_t k = m; b; b >>= 1, k &= k - 1ull)
+                    if (b & 1ull) r |= k & (~k + 1ull);
+        }
+        sel[i] = r;
+    }
+    const uint64_t h = __ballot(r != 0ull);
+    if (lane == 0) s_has[u] = h;
+    __syncthreads();
+    if (u == 0 && w < words) {
+        uint32_t views = 0;
+#pragma unroll
+        for (int q = 0; q < kLiveViews; ++q) views |= (uint32_t)((s_has[q] >> lane) & 1ull) << q;
+        const int64_t row = w * (8 * ((nv + 63) / 64));
+        word_views[row + blockIdx.y] = (uint8_t)views;
+        if (blockIdx.y + 1 == gridDim.y)  // the last views' workgroup clears the bits behind them
+            for (int g = gridDim.y; g < 8 * ((nv + 63) / 64); ++g) word_views[row + g] = 0;
+    }
 }
 
 // Gathers each interior node's parameter gradient from the cut entries of
@@ -913,16 +971,22 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess_bwd(DevHier h, const DevVi
 // node, views and entries in a fixed order: no atomics, and the result is
 // reproducible bit for bit.  Positions come from the cut's bit masks: node j
 // of view v sits at word_off[v][j / 64] plus the selected nodes below j in
-// its word.  The children of a node are contiguous ids, and those in the
-// cut are consecutive cut entries, so one or two mask words give all of
-// them at once.  The mask words of kGatherViews views are loaded together;
-// positions and entries are read only for the views that hold one.
+// its word.  The children of a node are contiguous ids, so one or two mask
+// words give all of them at once.
+//
+// Bound by the chain of dependent loads (words of a view, then rows) at the 12
+// waves per CU that the 59 sums and two rows leave.  A wave goes through the
+// views together, and only through those that have an entry with a row in one
+// of its words (word_views; 5 of 32 views far into a scene), two rows in
+// flight: 3.45 -> 1.56 ms for 14.5 M interior nodes and 32 views, 495 -> 327 us
+// for 1 M and 8 views.  Each thread through views of its own, reading masks,
+// tile counts and t of every entry, took the former; listing the entries first,
+// or 16 waves per CU with 40 spilled registers, 5.3 ms.
 //
 // FUSED: instead of adding the sum to the gradient arrays, the thread
 // applies the optimiser step to its node right away (every interior node,
 // those with no contribution too, whose gradient is zero): the gradient is
 // never written, re-read or cleared.
-constexpr int kGatherViews = 8;
 
 // The fused optimiser step of one block: thread t holds the gathered
 // gradient of interior node q0 + t (node id `node`; zero past the end).  The
@@ -1020,11 +1084,11 @@ __device__ __forceinline__ void adam_block(const AdamRows &ad, int64_t n_interio
 }
 
 template <bool FUSED>
-__global__ __launch_bounds__(kT, 4) void k_grad_gather(DevHier h, int nv, const uint64_t *__restrict__ masks,
+__global__ __launch_bounds__(kT, 3) void k_grad_gather(DevHier h, int nv, const uint64_t *__restrict__ masks,
                                                     int64_t words, const uint32_t *__restrict__ word_off,
-                                                    const uint32_t *__restrict__ cut_total, uint32_t cap,
-                                                    const double *__restrict__ cut_t,
-                                                    const uint32_t *__restrict__ ntiles, const float *__restrict__ pg,
+                                                    const uint64_t *__restrict__ sel,
+                                                    const uint64_t *__restrict__ word_views,
+                                                    const float *__restrict__ pg,
                                                     const int32_t *__restrict__ interior, int64_t n_interior,
                                                     float *__restrict__ g_mean, float *__restrict__ g_scale,
                                                     float *__restrict__ g_rot, float *__restrict__ g_op,
@@ -1042,13 +1106,13 @@ __global__ __launch_bounds__(kT, 4) void k_grad_gather(DevHier h, int nv, const 
     for (int m = 0; m < 48; ++m) ash[m] = 0.0f;
     bool any = false;
     if (valid) {
-        const uint32_t total = min(*cut_total, cap);
         const int64_t c0 = h.child_begin[i], c1 = c0 + h.child_count[i];  // children [c0, c1)
         // adds the attribute gradient of a contributing entry (row r), weighted
         // 1 - t as the node's own entry (op 10: node opacity term) or t as a
         // child's entry (op 11: parent opacity term)
-        auto add = [&](const float4 (&r)[5], float t, int op) {
-            const float w = op == 10 ? 1.0f - t : t;
+        auto add = [&](const float4 (&r)[5], int op) {
+            const float t = r[4].z, w = op == 10 ? 1.0f - t : t;
+            if (op == 11 && !(t > 0.0f)) return;
             const float g[15] = {r[0].x, r[0].y, r[0].z, r[0].w, r[1].x, r[1].y, r[1].z, r[1].w,
                                  r[2].x, r[2].y, r[2].z, r[2].w, r[3].x, r[3].y, r[3].z};
 #pragma unroll
@@ -1064,87 +1128,84 @@ __global__ __launch_bounds__(kT, 4) void k_grad_gather(DevHier h, int nv, const 
             }
             any = true;
         };
-        // the entries at cut positions pa (op oa) and pb (op ob; ~0u: none),
-        // added in that order: their tile counts and t first, then the rows
-        // of those that are visible and contribute (a child's entry only with
-        // t > 0; a row without a live splat adds nothing), the two entries'
-        // loads in flight together
-        auto take2 = [&](uint32_t pa, int oa, uint32_t pb, int ob) {
-            const bool va = pa < total, vb = pb < total;
-            uint32_t nta = 0, ntb = 0;
-            float ta = 0.0f, tb = 0.0f;
-            if (va) {
-                nta = ntiles[pa];
-                ta = (float)cut_t[pa];
-            }
-            if (vb) {
-                ntb = ntiles[pb];
-                tb = (float)cut_t[pb];
-            }
-            const bool ua = nta != 0 && (oa == 10 || ta > 0.0f), ub = ntb != 0 && (ob == 10 || tb > 0.0f);
-            float4 ra[5], rb[5];
-            if (ua) {
-                const float4 *g4 = reinterpret_cast<const float4 *>(pg + (size_t)pa * kPG);
-#pragma unroll
-                for (int q = 0; q < 5; ++q) ra[q] = g4[q];
-            }
-            if (ub) {
-                const float4 *g4 = reinterpret_cast<const float4 *>(pg + (size_t)pb * kPG);
-#pragma unroll
-                for (int q = 0; q < 5; ++q) rb[q] = g4[q];
-            }
-            if (ua && ra[4].w != 0.0f) add(ra, ta, oa);
-            if (ub && rb[4].w != 0.0f) add(rb, tb, ob);
-        };
         const int64_t wi = i >> 6, wa = c0 >> 6, wb = (c1 - 1) >> 6;
         const uint64_t below_i = (1ull << (i & 63)) - 1ull, own_bit = 1ull << (i & 63);
         // the children's bits in their first word (wa) and last word (wb)
         const int lo = (int)(c0 & 63), hi = (int)((c1 - 1) & 63);
         const uint64_t k_lo = ~((1ull << lo) - 1ull), k_hi = hi == 63 ? ~0ull : ((1ull << (hi + 1)) - 1ull);
-        const uint64_t ka = wa == wb ? (k_lo & k_hi) : k_lo, kb = wa == wb ? 0ull : k_hi;
-        const bool wide = wb - wa > 1;  // children over more than two words: every view is looked at
-    #pragma unroll 1
-        for (int v0 = 0; v0 < nv; v0 += kGatherViews) {
-            // the views of this group that hold the node or one of its children
-            // (their mask words loaded together)
-            uint32_t hit = 0;
-            if (wide) {
-                hit = (1u << min(kGatherViews, nv - v0)) - 1u;
-            } else {
-    #pragma unroll
-                for (int u = 0; u < kGatherViews; ++u) {
-                    const int v = v0 + u;
-                    if (v < nv) {
-                        const uint64_t *mv = masks + (int64_t)v * words;
-                        const uint64_t mo = mv[wi], ma = mv[wa], mb = kb ? mv[wb] : 0ull;
-                        hit |= ((mo & own_bit) || (ma & ka) || (mb & kb)) ? 1u << u : 0u;
-                    }
-                }
+        const int groups = (nv + 63) / 64;
+#pragma unroll 1
+        for (int g = 0; g < groups; ++g) {
+            // the views with an entry in a word of the node or its children,
+            // one after the other, the threads of the wave together
+            uint64_t hit = word_views[wi * groups + g];
+            for (int64_t w = wa; w <= wb; ++w) hit |= word_views[w * groups + g];
+            uint32_t h0 = (uint32_t)hit, h1 = (uint32_t)(hit >> 32);
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                h0 |= (uint32_t)__shfl_xor((int)h0, d, 64);
+                h1 |= (uint32_t)__shfl_xor((int)h1, d, 64);
             }
-            while (hit) {
-                const int v = v0 + __ffs(hit) - 1;
-                hit &= hit - 1u;
-                const uint64_t *mv = masks + (int64_t)v * words;
-                const uint32_t *ov = word_off + (int64_t)v * words;
-                // own entry
-                const uint64_t mo = mv[wi];
-                const uint32_t own = (mo & own_bit) ? ov[wi] + (uint32_t)__popcll(mo & below_i) : ~0u;
-                // children: the selected ones among [c0, c1) are consecutive entries from p0
-                uint32_t p0 = ~0u, nsel = 0;
-                for (int64_t w = wa; w <= wb; ++w) {
-                    const uint64_t mw = mv[w];
-                    const uint64_t m = mw & (w == wa ? k_lo : ~0ull) & (w == wb ? k_hi : ~0ull);
-                    if (!m) continue;
-                    if (p0 == ~0u) p0 = ov[w] + (uint32_t)__popcll(mw & ((m & (~m + 1ull)) - 1ull));
-                    nsel += (uint32_t)__popcll(m);
+            uint64_t all = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)h1) << 32 |
+                           (uint32_t)__builtin_amdgcn_readfirstlane((int)h0);
+#pragma unroll 1
+            for (; all; all &= all - 1ull) {
+                const int v = 64 * g + __builtin_ctzll(all);
+                const bool h = (hit >> (v & 63)) & 1ull;
+                const int64_t at = (int64_t)v * words;
+                const uint64_t *sv = sel + at, *mv = masks + at;
+                const uint32_t *ov = word_off + at;
+                bool own = false;
+                uint32_t po = 0;
+                if (h) {
+                    const uint64_t so = sv[wi], mo = mv[wi];
+                    own = (so & own_bit) != 0ull;
+                    po = ov[wi] + (uint32_t)__popcll(mo & below_i);
                 }
-                // the own entry, then the children's, two at a time
-                uint32_t k = 0;
-                if (own != ~0u) {
-                    take2(own, 10, nsel ? p0 : ~0u, 11);
-                    k = 1;
-                }
-                for (; k < nsel; k += 2) take2(p0 + k, 11, k + 1 < nsel ? p0 + k + 1 : ~0u, 11);
+                int64_t w = h ? wa : wb + 1;
+                do {  // two words of children at a time (most nodes: all of them)
+                    uint64_t ca = 0ull, cb = 0ull, ma = 0ull, mb = 0ull;
+                    uint32_t pa = 0, pb = 0;
+                    if (w <= wb) {
+                        ca = sv[w] & (w == wa ? k_lo : ~0ull) & (w == wb ? k_hi : ~0ull);
+                        ma = mv[w];
+                        pa = ov[w];
+                    }
+                    if (w < wb) {
+                        cb = sv[w + 1] & (w + 1 == wb ? k_hi : ~0ull);
+                        mb = mv[w + 1];
+                        pb = ov[w + 1];
+                    }
+                    w += 2;
+                    auto child = [&](uint32_t &pos) -> bool {
+                        const bool first = ca != 0ull;
+                        const uint64_t c = first ? ca : cb, b = c & (~c + 1ull);
+                        pos = (first ? pa : pb) + (uint32_t)__popcll((first ? ma : mb) & (b - 1ull));
+                        ca &= first ? ~b : 0ull;
+                        cb &= first ? ~0ull : ~b;
+                        return c != 0ull;
+                    };
+                    for (;;) {  // two rows in flight: the node's own, then its children's
+                        uint32_t p0 = po, p1;
+                        const bool o0 = own, b0 = own || child(p0);
+                        own = false;
+                        if (!__any(b0)) break;
+                        const bool b1 = child(p1);
+                        float4 r0[5], r1[5];
+                        if (b0) {
+                            const float4 *g4 = reinterpret_cast<const float4 *>(pg + (size_t)p0 * kPG);
+#pragma unroll
+                            for (int q = 0; q < 5; ++q) r0[q] = g4[q];
+                        }
+                        if (b1) {
+                            const float4 *g4 = reinterpret_cast<const float4 *>(pg + (size_t)p1 * kPG);
+#pragma unroll
+                            for (int q = 0; q < 5; ++q) r1[q] = g4[q];
+                        }
+                        if (b0) add(r0, o0 ? 10 : 11);
+                        if (b1) add(r1, 11);
+                    }
+                } while (__any(w <= wb));
             }
         }
     }
@@ -1309,10 +1370,10 @@ void launch_fill_u32(uint32_t *p, uint32_t value, size_t n, hipStream_t st)
 
 void launch_preprocess_backward(const DevHier &h, const DevView *views, int nv, const uint32_t *cut_base,
                                 const int32_t *cut_ids, const double *cut_t, const uint32_t *cut_total, uint32_t cap,
-                                const uint32_t *ntiles, const uint64_t *vis_mask, const uint64_t *pos_mask,
-                                const float *cjac, const uint32_t *vis_offsets,
-                                const uint32_t *order, const double *sgrad, float *pg,
-                                const uint64_t *masks, int64_t words, const uint32_t *word_off,
+                                const uint64_t *vis_mask, const uint64_t *pos_mask, const float *cjac,
+                                const uint32_t *vis_offsets,
+                                const uint32_t *order, const double *sgrad, float *pg, uint64_t *live,
+                                uint64_t *sel, uint64_t *word_views, const uint64_t *masks, int64_t words, const uint32_t *word_off,
                                 const int32_t *interior, int64_t n_interior,
                                 float *g_mean, float *g_scale, float *g_rot, float *g_opacity, float *g_sh,
                                 float *g_dt, const AdamRows *fused, hipStream_t st)
@@ -1321,16 +1382,19 @@ void launch_preprocess_backward(const DevHier &h, const DevView *views, int nv, 
     if (!blocks) return;
     if (order) blocks = chunk_grid(blocks);
     hipLaunchKernelGGL(k_preprocess_bwd, dim3(blocks), dim3(kT), 0, st, h, views, nv, cut_base, cut_ids, cut_t,
-                       cut_total, cap, vis_mask, pos_mask, cjac, vis_offsets, order, sgrad, pg, g_dt);
+                       cut_total, cap, vis_mask, pos_mask, cjac, vis_offsets, order, sgrad, pg, live, g_dt);
     const int64_t gblocks = (n_interior + kT - 1) / kT;
     if (!gblocks) return;
+    hipLaunchKernelGGL(k_live_nodes, dim3((uint32_t)((words + 63) / 64), (nv + kLiveViews - 1) / kLiveViews),
+                       dim3(64 * kLiveViews), 0, st,
+                       masks, word_off, words, nv, live, cut_total, cap, sel, reinterpret_cast<uint8_t *>(word_views));
     if (fused)
         hipLaunchKernelGGL(k_grad_gather<true>, dim3((uint32_t)gblocks), dim3(kT), 0, st, h, nv, masks, words,
-                           word_off, cut_total, cap, cut_t, ntiles, pg, interior, n_interior, nullptr, nullptr,
+                           word_off, sel, word_views, pg, interior, n_interior, nullptr, nullptr,
                            nullptr, nullptr, nullptr, *fused);
     else
         hipLaunchKernelGGL(k_grad_gather<false>, dim3((uint32_t)gblocks), dim3(kT), 0, st, h, nv, masks, words,
-                           word_off, cut_total, cap, cut_t, ntiles, pg, interior, n_interior, g_mean, g_scale, g_rot,
+                           word_off, sel, word_views, pg, interior, n_interior, g_mean, g_scale, g_rot,
                            g_opacity, g_sh, AdamRows{});
 }
 
