@@ -445,26 +445,45 @@ __global__ __launch_bounds__(TW *TH) void k_blend(const DevView *__restrict__ vi
     }
 }
 
-// Pixel of lane l inside its wave's 8x8 block in the backward: column l & 3
-// and row l >> 4 of the 4x4 quarter (l >> 2) & 3, so that the lane swaps of
-// the reduction (l ^ 32, l ^ 16) run over a quarter's rows.
-__device__ __forceinline__ int bwd_quarter(int lane) { return (lane >> 2) & 3; }
-__device__ __forceinline__ int bwd_x(int lane) { return (bwd_quarter(lane) & 1) * 4 + (lane & 3); }
-__device__ __forceinline__ int bwd_y(int lane) { return (bwd_quarter(lane) >> 1) * 4 + (lane >> 4); }
-
 // Sums over each row of 16 lanes (one 4x4 quarter of the wave's block) of 12
 // per-lane values, taken as six pairs: four halvings with DPP inside the row
 // (partners l ^ 8, l ^ 7, l ^ 2 and l ^ 1), each keeping one of the two
 // values of a pair per lane.  A: the pairs after the first halving.  Lane l of
 // the row ends with the row's total of value row_slot(l) (value 2 k + 1 is the
 // second of pair k; -1: a copy of another lane's total).
+//
+// In the second halving the lanes that keep a pair's first value are whole
+// banks of 4 (lanes l with l & 4 clear): two adds under bank masks instead of
+// two selects and an add.  Every lane must be active.  (The leading s_nop
+// covers the two wait states that a DPP operand needs after the VALU wrote
+// it.)
+__device__ __forceinline__ void halve_l7(const float (&A)[6], float (&B)[3])
+{
+#define HGS_HALF(o, f, s)                                                                                  \
+    "v_add_f32_dpp " o ", " f ", " f " row_half_mirror row_mask:0xf bank_mask:0x5\n\t"                    \
+    "v_add_f32_dpp " o ", " s ", " s " row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+    asm("s_nop 1\n\t" HGS_HALF("%0", "%3", "%4") HGS_HALF("%1", "%5", "%6") HGS_HALF("%2", "%7", "%8")
+        : "=&v"(B[0]), "=&v"(B[1]), "=&v"(B[2])
+        : "v"(A[0]), "v"(A[1]), "v"(A[2]), "v"(A[3]), "v"(A[4]), "v"(A[5]));
+#undef HGS_HALF
+}
+// The first halving of a pair without products (banks 0 and 1 keep the first).
+__device__ __forceinline__ float halve_l8(float first, float second)
+{
+    float o;
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        : "=&v"(o)
+        : "v"(first), "v"(second));
+    return o;
+}
+
 __device__ __forceinline__ float row_reduce12(const float (&A)[6], int lane)
 {
-    const bool b2 = (lane & 4) != 0, b1 = (lane & 2) != 0, b0 = (lane & 1) != 0;
+    const bool b1 = (lane & 2) != 0, b0 = (lane & 1) != 0;
     float B[3];
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-        B[m] = (b2 ? A[2 * m + 1] : A[2 * m]) + dpp_move<0x141>(b2 ? A[2 * m] : A[2 * m + 1]);  // half mirror
+    halve_l7(A, B);
     const float C0 = (b1 ? B[1] : B[0]) + dpp_move<0x4E>(b1 ? B[0] : B[1]);
     const float C1 = B[2] + dpp_move<0x4E>(B[2]);
     return (b0 ? C1 : C0) + dpp_move<0xB1>(b0 ? C0 : C1);
@@ -530,40 +549,32 @@ __device__ __forceinline__ double2 centre_offsets(const SplatRec &r, const doubl
     return make_double2(dx * W.x + dy * W.y, dx * W.z + dy * W.w);
 }
 
-// Reduction.  Each step (one splat per quarter, one pixel per lane) leaves
-// six values per lane, h, the three colour terms, dL/dA_n and dL/dA_p, of
-// which h enters weighted by 1, y and y^2 (y the pixel's row in its quarter):
-// eight sums over the four rows of a quarter's columns.  Two steps are taken
-// together: v_permlane32_swap of a value of the first and of the second step,
-// and an add, halve both at once; v_permlane16_swap does the same for the sums
-// 0-3 against 4-7, so that 24 instructions leave, for both steps, four sums
-// per lane (row r of 16 lanes: sums 0-3 or 4-7 by r & 1, of step r >> 1).  The
-// shift to the tile centre, the weights x and x^2 and two quad exchanges
-// finish the sums over the columns, and the totals go to the tile's LDS sums
-// (FP64 atomics).
+// Reduction.  Each step (one splat per quarter, one pixel per lane) leaves 12
+// values per lane: the moments of h about the tile's centre on the splat's
+// axes, dL/dA_n, dL/dA_p, the colours and dL/dt.  They are summed over the
+// quarter's row of 16 lanes by four DPP halvings, and the totals go to the
+// tile's LDS sums (FP64 atomics).
 //
-// The kernel issues VALU instructions near the limit (1.07 of one per 4 cycles
-// and SIMD) with the LDS 0.57 busy, so what counts is their number per step,
-// about 93 (119 with the 12 slots formed per lane and summed by four DPP
-// halvings, 34 instructions and their operands' selects): the walk's order is
-// a list made per batch instead of a bit mask taken apart step by step, the
-// colour behind enters as its product with the cotangent, and a record sits
-// at one LDS address.  v_mfma_f32_16x16x4_f32 for the same sums was slower
-// (six per step; FP32 matrix instructions hold the VALU for their 32 cycles:
-// 11.5 against 9.0 ms), larger batches too (7.6 -> 8.9 ms at 128 entries:
-// fewer tiles resident).  32 views of 1920x1080 over 30M leaves, 16x8 tiles:
-// 9.0 -> 7.6 ms; 16x16 tiles 10.0 -> 7.6, 32x16 19.2 -> 9.7; 8 views of
-// 1280x720 over 2M leaves 4.2 -> 3.4 ms.
+// The order of the operations is written out, every FMA: large splats near the
+// eye cancel almost all of their moments, and any other form or order moves
+// single elements of the scale and rotation gradients (sums over a column
+// first and pixel moments at the flush: by up to 2e-3 of their RMS on 32x16
+// tiles, 5e-4 on smaller ones).  An L1 cotangent of a second step then differs
+// in sign where image and target meet, so that results would change from one
+// version to the next far beyond rounding.  That form took 7.4 ms where this
+// one takes 7.9 (32 views of 1920x1080 over 30M leaves, 16x8 tiles).
 //
-// AXES (32x16 tiles): the colour behind is kept per channel and the moments
-// are formed per lane on the splat's axes and summed by four DPP halvings over
-// the quarter's row of 16 lanes.  Sixteen pixels from the tile's centre the
-// moments of a large splat nearly cancel, and the FP32 rounding of either form
-// moves single elements of the scale and rotation gradients by up to 2e-3 of
-// their RMS; this form, with its operations and order written out, keeps the
-// results of this tile what they have always been (up to 16x16 the two forms
-// stay within 6e-4).  It costs 5 to 7% here: 10.3 against 9.8 ms at 1.5 M
-// splats, 32 views of 1080p (19.2 ms with one entry a step).
+// The kernel issues VALU instructions near the limit, so what counts is their
+// number per step: the walk's order is a list made per batch instead of a bit
+// mask taken apart step by step, two entries are taken at a time, and a record
+// sits at one LDS address.  v_mfma_f32_16x16x4_f32 for the sums was slower
+// (FP32 matrix instructions hold the VALU for their 32 cycles: 11.5 against
+// 9.0 ms), larger batches too (7.6 -> 8.9 ms at 128 entries: fewer tiles
+// resident).  Of the last steps, the halvings under bank masks gave 8.4 ->
+// 8.1 ms and the cotangent's selects kept in registers 8.1 -> 7.9.  From one
+// entry a step found in a bit mask: 9.2 -> 7.9 ms; 16x16 tiles 10.0 -> 7.7,
+// 32x16 19.2 -> 9.7, 8x8 9.7 -> 8.4; 8 views of 1280x720 over 2M leaves
+// 4.2 -> 3.5 ms.
 //
 // DET (the deterministic mode): no floating-point atomics.  Each quarter
 // stores its FP32 partial sums in a slot of its own, the flush adds the
@@ -571,43 +582,6 @@ __device__ __forceinline__ double2 centre_offsets(const SplatRec &r, const doubl
 // with plain stores to det.part at the pair's position in the list
 // k_duplicate emitted (the splat's first pair plus the tile's row-major index
 // in its tile rectangle); launch_det_sum then adds each splat's rows in order.
-// Sums of lanes l and l ^ 32 of a in the lower half of the wave, of b in the upper.
-__device__ __forceinline__ float fold32(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// Sums of lanes l and l ^ 16 of a in the even rows of 16 lanes, of b in the odd rows.
-__device__ __forceinline__ float fold16(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// Over each quad of lanes: the sum of v, and sum_k c[k] v(lane k).
-__device__ __forceinline__ float quad_sum(float v)
-{
-    v += dpp_move<0xB1>(v);
-    return v + dpp_move<0x4E>(v);
-}
-// (FMAs with a lane-exchanged operand written out: the compiler folds an
-// exchange into a multiply or an add, but not into an FMA.  Every lane must
-// be active.  The leading s_nop covers the two wait states that a DPP operand
-// needs after the VALU wrote it.)
-__device__ __forceinline__ float quad_dot(float v, const float (&c)[4])
-{
-#define HGS_DPP_ALL " row_mask:0xf bank_mask:0xf\n\t"
-    float s;
-    asm("s_nop 1\n\t"
-        "v_mul_f32_dpp %0, %1, %2 quad_perm:[0,0,0,0]" HGS_DPP_ALL
-        "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,1,1,1]" HGS_DPP_ALL
-        "v_fmac_f32_dpp %0, %1, %4 quad_perm:[2,2,2,2]" HGS_DPP_ALL
-        "v_fmac_f32_dpp %0, %1, %5 quad_perm:[3,3,3,3]" HGS_DPP_ALL
-        : "=&v"(s)
-        : "v"(v), "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]));
-#undef HGS_DPP_ALL
-    return s;
-}
 
 // A splat staged for one tile by the backward.
 template <int NB>
@@ -640,7 +614,6 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
     constexpr int NW = NT / 64;
     constexpr int SX = TW / 8;
     constexpr int NB = (TW / 8) * (TH / 8);
-    constexpr bool AXES = NT > 256;
     constexpr int PER = 32;  // entries that a wave stages and flushes
     constexpr int BATCH = DET ? PER : PER * NW;
     constexpr int NQW = BATCH / 32;  // 32-entry words of a quarter's mask
@@ -665,33 +638,15 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
     const DevView &V = views[vi];
     const uint32_t lt = tile - V.tile_base;
     const int tx = (int)(lt % (uint32_t)V.tiles_x), ty = (int)(lt / (uint32_t)V.tiles_x);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, q = AXES ? lane >> 4 : bwd_quarter(lane);
-    constexpr int Q1 = AXES ? 16 : 4;  // the first lane of quarter 1
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4;
     const int ox = tx * TW, oy = ty * TH;
-    const int bx = AXES ? quarter_x(lane) : bwd_x(lane), by = AXES ? quarter_y(lane) : bwd_y(lane);
+    const int bx = quarter_x(lane), by = quarter_y(lane);
     const int px = ox + (w % SX) * 8 + bx, py = oy + (w / SX) * 8 + by;
     const bool inside = px < V.W && py < V.H;
     const float lx = (float)bx, ly = (float)by;
     const uint2 rg = ranges[tile];
 
-    const float yl = (float)(lane >> 4) - 1.5f, yl2 = yl * yl;  // the pixel's row about the quarter's centre
-    // the finish: in rows 0 and 2 of 16 lanes (sums 0-3 of a step) lane x of a
-    // quad forms S, S x, S x^2 from the four columns (weights cw; x = 3: the
-    // sum of colour 0), in rows 1 and 3 the plain sums
-    const bool low = (lane & 16) == 0;
-    const int qx = lane & 3;
-    const float yq = low ? (float)((w / SX) * 8 + (q >> 1) * 4) + 1.5f - 0.5f * (TH - 1) : 0.0f;
-    float cw[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float xt = (float)((w % SX) * 8 + (q & 1) * 4 + k) - 0.5f * (TW - 1);  // column k about the tile's centre
-        cw[k] = qx == 0 ? 1.0f : (qx == 1 ? xt : xt * xt);
-    }
-    // (11: nothing to put)
-    const int slot_a = low ? (qx == 0 ? 5 : (qx == 1 ? 0 : (qx == 2 ? 2 : 8))) : (qx == 0 ? 9 : (qx == 3 ? 7 : 11));
-    const int slot_b = low ? (qx == 0 ? 1 : (qx == 1 ? 4 : (qx == 2 ? 3 : 11))) : (qx == 0 ? 10 : (qx == 2 ? 6 : 11));
-    const uint32_t off_a = (uint32_t)offsetof(Rec, g) + 8u * slot_a, off_b = (uint32_t)offsetof(Rec, g) + 8u * slot_b;
-    // AXES: the pixel's offset from the tile centre, this lane's slot, and
+    // the pixel's offset from the tile centre, this lane's slot, and
     // which value of each pair it keeps in the first halving
     const float lxt = (float)(px - ox) - 0.5f * (TW - 1), lyt = (float)(py - oy) - 0.5f * (TH - 1);
     const int slot = row_slot(lane);
@@ -710,19 +665,22 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
     }
     if (threadIdx.x == 0) s_max = 0;
     __syncthreads();
+    // the cotangent as the first halving takes it (pairs (0, 1) and (2, -)),
+    // kept in registers: the compiler would select anew in every step
+    float ga = b3 ? g1 : g0, gb = b3 ? g0 : g1, g2a = b3 ? 0.0f : g2, g2b = b3 ? g2 : 0.0f;
+    asm volatile("" : "+v"(ga), "+v"(gb), "+v"(g2a), "+v"(g2b));
     // the quarter's last contributor, then the tile's
     uint32_t qm = last;
     qm = max(qm, (uint32_t)__shfl_xor((int)qm, 1, 64));
     qm = max(qm, (uint32_t)__shfl_xor((int)qm, 2, 64));
-    qm = max(qm, (uint32_t)__shfl_xor((int)qm, AXES ? 4 : 16, 64));
-    qm = max(qm, (uint32_t)__shfl_xor((int)qm, AXES ? 8 : 32, 64));
-    uint32_t wm = max(qm, (uint32_t)__shfl_xor((int)qm, AXES ? 16 : 4, 64));
-    wm = max(wm, (uint32_t)__shfl_xor((int)wm, AXES ? 32 : 8, 64));
+    qm = max(qm, (uint32_t)__shfl_xor((int)qm, 4, 64));
+    qm = max(qm, (uint32_t)__shfl_xor((int)qm, 8, 64));
+    uint32_t wm = max(qm, (uint32_t)__shfl_xor((int)qm, 16, 64));
+    wm = max(wm, (uint32_t)__shfl_xor((int)wm, 32, 64));
     if (lane == 0) atomicMax(&s_max, wm);
     __syncthreads();
     const uint32_t end = rg.x + s_max;
-    float Rg = 0.0f;  // cotangent . colour composited behind the current splat
-    float R0 = 0.0f, R1 = 0.0f, R2 = 0.0f;  // AXES: that colour instead
+    float R0 = 0.0f, R1 = 0.0f, R2 = 0.0f;  // colour composited behind the current splat
     uint32_t n_eval = 0, n_eval_t = 0, n_con = 0;  // wave totals (scalar)
 
     if (threadIdx.x == 0) {  // (ordered before its first read by the barrier after the staging)
@@ -794,8 +752,8 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int qa = 2 * h + (lane >> 5), i = lane & 31;
-            const uint32_t qma = (uint32_t)__builtin_amdgcn_readlane((int)qm, 2 * h * Q1),
-                           qmb = (uint32_t)__builtin_amdgcn_readlane((int)qm, (2 * h + 1) * Q1);
+            const uint32_t qma = (uint32_t)__builtin_amdgcn_readlane((int)qm, 32 * h),
+                           qmb = (uint32_t)__builtin_amdgcn_readlane((int)qm, 32 * h + 16);
             const uint32_t lastq = lane < 32 ? qma : qmb;
             const int limq = lastq > base ? (int)min(lastq - base, (uint32_t)cnt) : 0;
             int n = 0;
@@ -820,7 +778,7 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
             const uint32_t off[2] = {two & 0xFFFFu, two >> 16};
             two = walk[(p >> 1) + 1];
             float4 Ov[2], Wv[2], Cv[2];
-            float G[2], al[2], anr[2], apr[2], omt[2], omap[2], qp[2], cg[2];
+            float G[2], al[2], anr[2], apr[2], omt[2], omap[2], qp[2];
             bool con[2];
             uint64_t tm[2];
 #pragma unroll
@@ -830,7 +788,6 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
                 Wv[s] = r.w;
                 Ov[s] = r.o;
                 omt[s] = Cv[s].w;
-                cg[s] = fmaf(Cv[s].z, g2, fmaf(Cv[s].y, g1, Cv[s].x * g0));
                 tm[s] = __builtin_amdgcn_ballot_w64(Ov[s].z > 0.0f);
                 G[s] = eval_gauss(Wv[s], r.u[w], lx, ly);
                 anr[s] = Ov[s].x * G[s];
@@ -863,17 +820,11 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
                 const float a = con[s] ? al[s] : 0.0f;
                 T = T * __builtin_amdgcn_rcpf(1.0f - a);
                 aT[s] = a * T;
-                if constexpr (AXES) {
-                    const float d0 = Cv[s].x - R0, d1 = Cv[s].y - R1, d2 = Cv[s].z - R2;
-                    dal[s] = T * fmaf(d2, g2, fmaf(d0, g0, d1 * g1));
-                    R0 = fmaf(a, d0, R0);
-                    R1 = fmaf(a, d1, R1);
-                    R2 = fmaf(a, d2, R2);
-                } else {
-                    const float df = cg[s] - Rg;
-                    dal[s] = T * df;
-                    Rg = fmaf(a, df, Rg);
-                }
+                const float d0 = Cv[s].x - R0, d1 = Cv[s].y - R1, d2 = Cv[s].z - R2;
+                dal[s] = T * fmaf(d2, g2, fmaf(d0, g0, d1 * g1));
+                R0 = fmaf(a, d0, R0);
+                R1 = fmaf(a, d1, R1);
+                R2 = fmaf(a, d2, R2);
             }
             // dL/da_n, dL/da_p (zero through the clamps)
             if (any_t) {
@@ -896,74 +847,36 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
                     dt[s] = con[s] && Ov[s].z > 0.0f ? ((1.0f - qp[s]) - fminf(anr[s], kAlphaMax)) * dal[s] : 0.0f;
-            if constexpr (AXES) {
 #pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    const float4 W = Wv[s];
-                    const float h = G[s] * fmaf(dap[s], Ov[s].y, dan[s] * Ov[s].x);  // G dL/dG
-                    const float v1 = fmaf(lyt, W.y, lxt * W.x), v2 = fmaf(lyt, W.w, lxt * W.z);
-                    // the six pairs and their first halving (row_ror:8): a lane
-                    // keeps the second value of a pair where bit 3 is set
-                    const float pa = b3 ? v2 : v1, pb = b3 ? v1 : v2;
-                    const float ha = h * pa, hb = h * pb, hab = ha * pb;
-                    float A[6];
-                    A[0] = fmaf(h, pa, dpp_move<0x128>(hb));                            // P'_1, P'_2
-                    A[1] = fmaf(ha, pa, dpp_move<0x128>(hb * pb));                      // Q'_11, Q'_22
-                    A[2] = (b3 ? h : hab) + dpp_move<0x128>(b3 ? hab : h);              // Q'_12, S
-                    A[3] = fmaf(G[s], b3 ? dap[s] : dan[s], dpp_move<0x128>(G[s] * (b3 ? dan[s] : dap[s])));
-                    A[4] = fmaf(aT[s], b3 ? g1 : g0, dpp_move<0x128>(aT[s] * (b3 ? g0 : g1)));  // colour 0, 1
-                    if constexpr (DT) {  // colour 2, dL/dt
-                        const float c2 = aT[s] * g2;
-                        A[5] = (b3 ? dt[s] : c2) + dpp_move<0x128>(b3 ? c2 : dt[s]);
+            for (int s = 0; s < 2; ++s) {
+                const float4 W = Wv[s];
+                const float h = G[s] * fmaf(dap[s], Ov[s].y, dan[s] * Ov[s].x);  // G dL/dG
+                const float v1 = fmaf(lyt, W.y, lxt * W.x), v2 = fmaf(lyt, W.w, lxt * W.z);
+                // the six pairs and their first halving (row_ror:8): a lane
+                // keeps the second value of a pair where bit 3 is set
+                const float pa = b3 ? v2 : v1, pb = b3 ? v1 : v2;
+                const float ha = h * pa, hb = h * pb, hab = ha * pb;
+                const float da = b3 ? dap[s] : dan[s], db = b3 ? dan[s] : dap[s];
+                float A[6];
+                A[0] = fmaf(h, pa, dpp_move<0x128>(hb));                            // P'_1, P'_2
+                A[1] = fmaf(ha, pa, dpp_move<0x128>(hb * pb));                      // Q'_11, Q'_22
+                A[2] = halve_l8(hab, h);                                            // Q'_12, S
+                A[3] = fmaf(G[s], da, dpp_move<0x128>(G[s] * db));                  // dL/dA_n, dL/dA_p
+                A[4] = fmaf(aT[s], ga, dpp_move<0x128>(aT[s] * gb));                // colour 0, 1
+                if constexpr (DT) {  // colour 2, dL/dt
+                    A[5] = halve_l8(aT[s] * g2, dt[s]);
+                } else {
+                    A[5] = fmaf(aT[s], g2a, dpp_move<0x128>(aT[s] * g2b));
+                }
+                float tot = row_reduce12(A, lane);
+                // formed by every lane here, where the lane exchange folds into
+                // the add, not under the mask of the lanes that hold a slot
+                asm volatile("" : "+v"(tot));
+                if (slot >= 0) {
+                    if constexpr (DET) {
+                        if (off[s] != kDead) s_gr[4 * w + q][off[s] / kRec][slot] = tot;
                     } else {
-                        A[5] = fmaf(aT[s], b3 ? 0.0f : g2, dpp_move<0x128>(aT[s] * (b3 ? g2 : 0.0f)));
-                    }
-                    const float tot = row_reduce12(A, lane);
-                    if (slot >= 0) {
-                        if constexpr (DET) {
-                            if (off[s] != kDead) s_gr[4 * w + q][off[s] / kRec][slot] = tot;
-                        } else {
-                            if (tot != 0.0f) unsafeAtomicAdd(&rec_at(off[s]).g[slot], (double)tot);
-                        }
-                    }
-                }
-            } else {
-                const float van0 = G[0] * dan[0], van1 = G[1] * dan[1], vap0 = G[0] * dap[0], vap1 = G[1] * dap[1];
-                const float vh0 = fmaf(van0, Ov[0].x, vap0 * Ov[0].y);  // G dL/dG
-                const float vh1 = fmaf(van1, Ov[1].x, vap1 * Ov[1].y);
-                // rows 0 / 1 of 16 lanes: S, S y, S y^2, colour 0 / colour 1, colour 2,
-                // dL/dA_n, dL/dA_p of the first step; rows 2 / 3 of the second
-                const float D0 = fold16(fold32(vh0, vh1), fold32(aT[0] * g1, aT[1] * g1));
-                const float D1 = fold16(fold32(vh0 * yl, vh1 * yl), fold32(aT[0] * g2, aT[1] * g2));
-                const float D2 = fold16(fold32(vh0 * yl2, vh1 * yl2), fold32(van0, van1));
-                const float D3 = fold16(fold32(aT[0] * g0, aT[1] * g0), fold32(vap0, vap1));
-                const float Sy = fmaf(yq, D0, D1);
-                const float Syy = fmaf(yq, Sy + D1, D2);
-                const float f0 = quad_dot(D0, cw), f1 = quad_dot(Sy, cw), f2 = quad_sum(Syy), f3 = quad_sum(D3);
-                float va = qx == 3 ? f3 : f0, vb = qx == 2 ? f2 : f1;
-                // formed by every lane here, where the lane exchanges fold into the
-                // arithmetic, not under the masks of the adds below
-                asm volatile("" : "+v"(va), "+v"(vb));
-                const uint32_t os = lane & 32 ? off[1] : off[0];
-                if constexpr (DET) {
-                    if (os != kDead) {
-                        float *o = s_gr[4 * w + q][os / kRec];
-                        if (slot_a != 11) o[slot_a] = va;
-                        if (slot_b != 11) o[slot_b] = vb;
-                    }
-                } else {  // past a list's end: zeros, to the dead record
-                    if (slot_a != 11) unsafeAtomicAdd(reinterpret_cast<double *>(s_rec + os + off_a), (double)va);
-                    if (slot_b != 11) unsafeAtomicAdd(reinterpret_cast<double *>(s_rec + os + off_b), (double)vb);
-                }
-                if constexpr (DT) {
-                    float f = fold32(dt[0], dt[1]);
-                    f = quad_sum(fold16(f, f));
-                    if (qx == 0 && low) {
-                        if constexpr (DET) {
-                            if (os != kDead) s_gr[4 * w + q][os / kRec][11] = f;
-                        } else {
-                            unsafeAtomicAdd(&rec_at(os).g[11], (double)f);
-                        }
+                        if (tot != 0.0f) unsafeAtomicAdd(&rec_at(off[s]).g[slot], (double)tot);
                     }
                 }
             }
@@ -987,17 +900,9 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
             }
             // moments on the splat's axes about the tile's centre, then about the splat's
             const float4 W = sr.w;
-            const double wx = W.x, wy = W.y, wz = W.z, ww = W.w;
             const double2 cr = s_ref[j];
             const double S = g[5];
-            double P1 = g[0], P2 = g[1], Q11 = g[2], Q22 = g[3], Q12 = g[4];
-            if constexpr (!AXES) {
-                P1 = wx * g[0] + wy * g[1];
-                P2 = wz * g[0] + ww * g[1];
-                Q11 = wx * wx * g[2] + 2.0 * wx * wy * g[4] + wy * wy * g[3];
-                Q22 = wz * wz * g[2] + 2.0 * wz * ww * g[4] + ww * ww * g[3];
-                Q12 = wx * wz * g[2] + (wx * ww + wy * wz) * g[4] + wy * ww * g[3];
-            }
+            const double P1 = g[0], P2 = g[1], Q11 = g[2], Q22 = g[3], Q12 = g[4];
             const double P[2] = {P1 + cr.x * S, P2 + cr.y * S};
             const double Q[3] = {Q11 + 2.0 * cr.x * P1 + cr.x * cr.x * S,
                                  Q12 + cr.x * P2 + cr.y * P1 + cr.x * cr.y * S,
