@@ -142,16 +142,46 @@ def make_view(v) -> View:
     """hgs_view from any object with R, eye, fx, fy, cx, cy, width, height,
     z_near, tau (e.g. ``synth.View``)."""
     out = View()
-    R = np.asarray(v.R, np.float32).reshape(9)
-    for k in range(9):
-        out.R[k] = float(R[k])
-    e = np.asarray(v.eye, np.float32).reshape(3)
-    for k in range(3):
-        out.eye[k] = float(e[k])
+    _fill_view(out, v)
+    return out
+
+
+def _fill_view(out: View, v) -> None:
+    out.R[:] = np.asarray(v.R, np.float32).reshape(9).tolist()
+    out.eye[:] = np.asarray(v.eye, np.float32).reshape(3).tolist()
     out.fx, out.fy, out.cx, out.cy = float(v.fx), float(v.fy), float(v.cx), float(v.cy)
     out.width, out.height = int(v.width), int(v.height)
     out.z_near, out.tau = float(v.z_near), float(v.tau)
-    return out
+
+
+# the fields of View by kind, for several records at once
+_VIEWS = np.dtype([("R", np.float32, 9), ("eye", np.float32, 3), ("f", np.float32, 4), ("wh", np.int32, 2),
+                   ("zt", np.float32, 2)])
+assert _VIEWS.itemsize == ctypes.sizeof(View)
+
+
+def make_views(views) -> ctypes.Array:
+    """The array of ``make_view`` of each.  From 8 on it is filled column by
+    column (256 views: 0.2 ms, where a record at a time takes 0.57 and, filled
+    in place, 0.49; below 8 the columns' fixed cost is the larger)."""
+    n = len(views)
+    if n >= 8:
+        a = np.empty(n, _VIEWS)
+        try:
+            a["R"] = np.concatenate([v.R for v in views]).reshape(n, 9)
+            a["eye"] = np.concatenate([v.eye for v in views]).reshape(n, 3)
+        except ValueError:
+            pass  # not all of one shape: one by one
+        else:
+            with np.errstate(over="ignore"):
+                f = np.array([(v.fx, v.fy, v.cx, v.cy, v.z_near, v.tau) for v in views], np.float64)
+                a["f"], a["zt"] = f[:, :4], f[:, 4:]
+            a["wh"] = np.array([(int(v.width), int(v.height)) for v in views])
+            return (View * n).from_buffer(a)
+    arr = (View * n)()
+    for out, v in zip(arr, views):
+        _fill_view(out, v)
+    return arr
 
 
 _hip = None
@@ -333,11 +363,11 @@ class Renderer:
         views = list(views)
         if tau_max is None:
             tau_max = 0.5 * max(max(v.width, v.height) for v in views)
-        arr = (View * len(views))(*[make_view(v) for v in views])
+        arr = make_views(views)
         keep = torch.empty(max(self.n_nodes, 1), dtype=torch.uint8, device=self.device)
         self._check(self.L.hgs_compact_mark(self.h, arr, len(views), float(tau_min), float(tau_max),
                                             ctypes.c_void_p(keep.data_ptr())))
-        return keep[:self.n_nodes].bool()
+        return keep[:self.n_nodes].view(torch.bool)  # 0 and 1
 
     # -- render ----------------------------------------------------------------
     def render(self, views, out=None, timed: bool = False):
@@ -346,7 +376,7 @@ class Renderer:
         torch = self.torch
         views = list(views)
         nv = len(views)
-        arr = (View * nv)(*[make_view(v) for v in views])
+        arr = make_views(views)
         if out is None:
             out = [torch.empty((v.height, v.width, 3), dtype=torch.float32, device=self.device) for v in views]
         ptrs = (ctypes.c_void_p * nv)(*[o.data_ptr() for o in out])
