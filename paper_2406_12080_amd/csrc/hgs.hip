@@ -1162,7 +1162,8 @@ hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *L, int src_on_device, 
     const BuildOut o{ctx->own[0], ctx->own[1], ctx->own[2], ctx->own[3], ctx->own[4], bmin, bmax};
     build_axis_maps_upload(st);
     for (int d = 0; d < nlev; ++d)
-        launch_match_level(t, w, (int32_t)base[d], (int32_t)(base[d + 1] - base[d]), o, leaf_src, in[4], st);
+        launch_match_level(t, w, (int32_t)base[d], (int32_t)(base[d + 1] - base[d]), o, st);
+    launch_out_sh(t, w, N, o, leaf_src, in[4], st);
     for (int d = nlev - 1; d >= 0; --d)
         launch_box_level(t, (int32_t)base[d], (int32_t)(base[d + 1] - base[d]), bmin, bmax, st);
     if ((s = dalloc(ctx, (void **)&ctx->pinfo, 4 * (size_t)N))) return s;

@@ -367,7 +367,10 @@ void launch_interior_list(const int32_t *child_count, const uint32_t *irank, int
 void launch_merge_level(const BuildTree &t, const int32_t *leaf_src, const BuildLeaves &in, const BuildWork &w,
                         int32_t base, int32_t count, hipStream_t st);
 void launch_match_level(const BuildTree &t, const BuildWork &w, int32_t base, int32_t count, const BuildOut &o,
-                        const int32_t *leaf_src, const float *in_sh, hipStream_t st);
+                        hipStream_t st);
+// the SH records of all N nodes, after every level is merged
+void launch_out_sh(const BuildTree &t, const BuildWork &w, int64_t N, const BuildOut &o, const int32_t *leaf_src,
+                   const float *in_sh, hipStream_t st);
 void launch_box_level(const BuildTree &t, int32_t base, int32_t count, float *bmin, float *bmax, hipStream_t st);
 // pinfo (parent | leaf bit) and the component-major boxes [6][N] of a built tree
 void launch_build_finish(const BuildTree &t, int64_t N, const float *bmin, const float *bmax, uint32_t *pinfo,

@@ -321,12 +321,49 @@ struct LeafIn {
     const float *pos, *scale, *rot, *opacity, *sh;  // node-major inputs
 };
 
-// Nodes of one level, bottom up: a leaf takes its input Gaussian; an
-// interior node merges its children (Eq. merge, w'_i = o_i S_i).
-__global__ __launch_bounds__(kT) void k_merge_level(Tree t, const int32_t *__restrict__ leaf_src, LeafIn in, Work w,
-                                                    int32_t base, int32_t count)
+// The SH record of interior node id of a level, by 16 lanes: lane l takes
+// coefficients l, l + 16 and l + 32.
+constexpr int kShLanes = 16;
+
+__device__ __forceinline__ void merge_sh(const Tree &t, const int32_t *__restrict__ leaf_src, const LeafIn &in,
+                                         const Work &w, int32_t id, int l)
 {
 #pragma clang fp contract(off)
+    const int32_t c0 = t.child_begin[id], cc = t.child_count[id];
+    if (cc == 0) return;
+    double W = 0.0;
+    for (int32_t c = c0; c < c0 + cc; ++c) W += w.op[c] * w.surf[c];
+    double sh[3] = {0.0, 0.0, 0.0};
+    for (int32_t c = c0; c < c0 + cc; ++c) {
+        const double wc = w.op[c] * w.surf[c] / W;
+        if (t.child_count[c] == 0) {
+            const float *src = in.sh + 48 * (int64_t)leaf_src[c] + l;
+            for (int j = 0; j < 3; ++j) sh[j] += wc * (double)src[kShLanes * j];
+        } else {
+            const double *src = w.sh + 48 * (int64_t)w.irank[c] + l;
+            for (int j = 0; j < 3; ++j) sh[j] += wc * src[kShLanes * j];
+        }
+    }
+    double *o = w.sh + 48 * (int64_t)w.irank[id] + l;
+    for (int j = 0; j < 3; ++j) o[kShLanes * j] = sh[j];
+}
+
+// Nodes of one level, bottom up: a leaf takes its input Gaussian; an
+// interior node merges its children (Eq. merge, w'_i = o_i S_i).  The first
+// geo workgroups do that with a thread per node, all but the SH; the others
+// merge the SH records, 16 lanes per node, which read and write them in whole
+// lines (a thread that walked its children's 192 and 384 bytes coefficient by
+// coefficient took half of the kernel: 1.50 ms over the 15 levels of 1M
+// leaves, 0.82 so).
+__global__ __launch_bounds__(kT) void k_merge_level(Tree t, const int32_t *__restrict__ leaf_src, LeafIn in, Work w,
+                                                    int32_t base, int32_t count, uint32_t geo)
+{
+#pragma clang fp contract(off)
+    if (blockIdx.x >= geo) {
+        const int64_t e = (int64_t)(blockIdx.x - geo) * kT + threadIdx.x;
+        if (e < (int64_t)count * kShLanes) merge_sh(t, leaf_src, in, w, base + (int32_t)(e / kShLanes), (int)(e % kShLanes));
+        return;
+    }
     const int32_t k = (int32_t)(blockIdx.x * kT + threadIdx.x);
     if (k >= count) return;
     const int32_t id = base + k;
@@ -369,8 +406,6 @@ __global__ __launch_bounds__(kT) void k_merge_level(Tree t, const int32_t *__res
         for (int j = 0; j < 3; ++j) mu[j] += wc * w.mean[3 * (int64_t)c + j];
     }
     double C[6] = {0, 0, 0, 0, 0, 0};
-    double *sh = w.sh + 48 * (int64_t)w.irank[id];
-    for (int j = 0; j < 48; ++j) sh[j] = 0.0;
     for (int32_t c = c0; c < c0 + cc; ++c) {
         const double wc = w.op[c] * w.surf[c] / W;
         double d[3];
@@ -379,13 +414,6 @@ __global__ __launch_bounds__(kT) void k_merge_level(Tree t, const int32_t *__res
         int e = 0;
         for (int a = 0; a < 3; ++a)
             for (int b = a; b < 3; ++b, ++e) C[e] += wc * (Cc[e] + d[a] * d[b]);
-        if (t.child_count[c] == 0) {
-            const float *src = in.sh + 48 * (int64_t)leaf_src[c];
-            for (int j = 0; j < 48; ++j) sh[j] += wc * (double)src[j];
-        } else {
-            const double *src = w.sh + 48 * (int64_t)w.irank[c];
-            for (int j = 0; j < 48; ++j) sh[j] += wc * src[j];
-        }
     }
     double ev[3], V[9], s[3];
     jacobi3(C, ev, V);
@@ -410,6 +438,25 @@ struct AxisMaps {
 
 __constant__ AxisMaps c_maps;
 
+// The SH records of all nodes, 12 threads each (a thread per node inside the
+// matching took over half of its 0.53 ms for 1M leaves; here 0.15, 5.4 TB/s).
+__global__ __launch_bounds__(kT) void k_out_sh(Tree t, Work w, int64_t N, const int32_t *__restrict__ leaf_src,
+                                               const float *__restrict__ in_sh, float *__restrict__ out_sh)
+{
+    const int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x, id = e / 12;
+    const int q = 4 * (int)(e % 12);
+    if (id >= N) return;
+    float v[4];
+    if (t.child_count[id] > 0) {
+        const double *src = w.sh + 48 * (int64_t)w.irank[id] + q;
+        for (int j = 0; j < 4; ++j) v[j] = (float)src[j];
+    } else {
+        const float *src = in_sh + 48 * (int64_t)leaf_src[id] + q;
+        for (int j = 0; j < 4; ++j) v[j] = src[j];
+    }
+    *reinterpret_cast<float4 *>(out_sh + 4 * e) = make_float4(v[0], v[1], v[2], v[3]);
+}
+
 // Matching of one level, top down: each node's axes re-assigned to be
 // closest to its parent's (the world axes at the root), scales following,
 // the quaternion taken with a non-negative dot product with the parent's
@@ -417,9 +464,7 @@ __constant__ AxisMaps c_maps;
 __global__ __launch_bounds__(kT) void k_match_level(Tree t, Work w, int32_t base, int32_t count,
                                                     float *__restrict__ out_mean, float *__restrict__ out_scale,
                                                     float *__restrict__ out_rot, float *__restrict__ out_op,
-                                                    float *__restrict__ out_sh, const int32_t *__restrict__ leaf_src,
-                                                    const float *__restrict__ in_sh, float *__restrict__ bmin,
-                                                    float *__restrict__ bmax)
+                                                    float *__restrict__ bmin, float *__restrict__ bmax)
 {
 #pragma clang fp contract(off)
     const int32_t k = (int32_t)(blockIdx.x * kT + threadIdx.x);
@@ -492,13 +537,7 @@ __global__ __launch_bounds__(kT) void k_match_level(Tree t, Work w, int32_t base
         out_mean[3 * (int64_t)id + j] = (float)w.mean[3 * (int64_t)id + j];
     }
     out_op[id] = (float)w.op[id];
-    if (t.child_count[id] > 0) {
-        const double *src = w.sh + 48 * (int64_t)w.irank[id];
-        for (int j = 0; j < 48; ++j) out_sh[48 * (int64_t)id + j] = (float)src[j];
-        return;
-    }
-    const float *src = in_sh + 48 * (int64_t)leaf_src[id];
-    for (int j = 0; j < 48; ++j) out_sh[48 * (int64_t)id + j] = src[j];
+    if (t.child_count[id] > 0) return;
     // the leaf's box from its stored (FP32) scale and normalised quaternion,
     // rounded outward to FP32
     double q32[4], n2 = 0.0, s32[3], R32[9];
@@ -654,17 +693,27 @@ void launch_merge_level(const BuildTree &t, const int32_t *leaf_src, const Build
     const Tree tt{t.start, t.size, t.parent, t.child_begin, t.child_count};
     const LeafIn li{in.pos, in.scale, in.rot, in.opacity, in.sh};
     const Work ww{w.mean, w.cov, w.op, w.surf, w.axes, w.sc, w.sh, w.irank, w.R, w.q};
-    hipLaunchKernelGGL(k_merge_level, dim3(blocks_for((uint64_t)count)), dim3(kT), 0, st, tt, leaf_src, li, ww, base,
-                       count);
+    const uint32_t geo = (uint32_t)blocks_for((uint64_t)count);
+    hipLaunchKernelGGL(k_merge_level, dim3(geo + (uint32_t)blocks_for((uint64_t)count * kShLanes)), dim3(kT), 0, st, tt,
+                       leaf_src, li, ww, base, count, geo);
 }
 
 void launch_match_level(const BuildTree &t, const BuildWork &w, int32_t base, int32_t count, const BuildOut &o,
-                        const int32_t *leaf_src, const float *in_sh, hipStream_t st)
+                        hipStream_t st)
 {
     const Tree tt{t.start, t.size, t.parent, t.child_begin, t.child_count};
     const Work ww{w.mean, w.cov, w.op, w.surf, w.axes, w.sc, w.sh, w.irank, w.R, w.q};
     hipLaunchKernelGGL(k_match_level, dim3(blocks_for((uint64_t)count)), dim3(kT), 0, st, tt, ww, base, count, o.mean,
-                       o.scale, o.rot, o.opacity, o.sh, leaf_src, in_sh, o.bmin, o.bmax);
+                       o.scale, o.rot, o.opacity, o.bmin, o.bmax);
+}
+
+void launch_out_sh(const BuildTree &t, const BuildWork &w, int64_t N, const BuildOut &o, const int32_t *leaf_src,
+                   const float *in_sh, hipStream_t st)
+{
+    const Tree tt{t.start, t.size, t.parent, t.child_begin, t.child_count};
+    const Work ww{w.mean, w.cov, w.op, w.surf, w.axes, w.sc, w.sh, w.irank, w.R, w.q};
+    hipLaunchKernelGGL(k_out_sh, dim3(blocks_for((uint64_t)N * 12)), dim3(kT), 0, st, tt, ww, N, leaf_src, in_sh,
+                       o.sh);
 }
 
 void launch_box_level(const BuildTree &t, int32_t base, int32_t count, float *bmin, float *bmax, hipStream_t st)
