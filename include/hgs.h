@@ -127,7 +127,9 @@ typedef struct {
  * stored in FP32.  `src_on_device`: 0 = host pointers, 1 = device pointers.
  * *n_nodes (host) receives the node count.  n_leaves in [1, 2^29];
  * non-finite means: HGS_ERR_INVALID_ARG.  Synchronises the ctx stream;
- * allocates its working memory (FP64, about 0.5 kB per node) for the call. */
+ * allocates its working memory (FP64, about 0.5 kB per node); ctx keeps up
+ * to 2 GiB of it for the next build, gives that back when an allocation of
+ * its own would fail, and frees the rest before the call returns. */
 hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *leaves, int src_on_device, int64_t *n_nodes);
 
 /* Copies ctx's hierarchy out in the layouts of hgs_hierarchy_desc
