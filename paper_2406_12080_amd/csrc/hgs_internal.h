@@ -137,7 +137,8 @@ void launch_word_bounds(const DevHier &h, float4 *bounds, hipStream_t st);
 // Also writes word_off[v][w]: the cut position of the first selected node of
 // mask word w of view v (words holding a selected node only), and, when
 // cut_base is given, cut_base[v] = the cut position of view v's first
-// selected node (cut_base[nv] = *cut_total).
+// selected node (cut_base[nv] = *cut_total).  Without cut_base nothing is
+// written if *cut_total exceeds cap; with it, what fits is.
 void launch_cut_emit(const DevHier &h, const DevView *views, int nv, const uint64_t *masks,
                      const uint32_t *block_offsets, int nblocks, uint32_t *word_off, int32_t *out_ids, float *out_t,
                      double *out_t64, uint32_t cap, uint32_t *cut_base, const uint32_t *cut_total, hipStream_t st);

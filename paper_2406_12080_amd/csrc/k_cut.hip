@@ -293,6 +293,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut_emit(DevHier h, const DevVi
     const int64_t words = (n + 63) >> 6;
     const int v0 = blockIdx.y * VB, nvb = min(VB, nv - v0);
     const int64_t w0 = (int64_t)blockIdx.x * W;
+    if (!cut_base && *cut_total > cap) return;  // a caller's buffers: all or nothing
     if (blockIdx.x == 0 && cut_base) {
         if (threadIdx.x < (uint32_t)nvb)
             cut_base[v0 + threadIdx.x] = block_offsets[(int64_t)(v0 + threadIdx.x) * nblocks];
