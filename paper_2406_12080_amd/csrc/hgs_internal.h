@@ -228,7 +228,7 @@ __device__ __forceinline__ void sort_plan_block(uint32_t lo, uint32_t hi, uint32
 // make theirs with launch_plan_depth and launch_plan_pairs.
 void launch_plan_whole(uint32_t cap, const uint32_t *n_dev, int bits, const SortScratch &s, hipStream_t st);
 // Sorts by the plan in s.  Returns true when the sorted result is in
-// (s.k2, s.v2) (odd pass count).
+// (s.k2, s.v2).
 bool launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t cap, int nseg, int bits, const SortScratch &s,
                        hipStream_t st);
 

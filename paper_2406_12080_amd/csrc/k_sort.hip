@@ -40,6 +40,8 @@ constexpr int kWaves = kT / 64;
 constexpr int kTile = (int)kSortTile;
 constexpr int kItems = kTile / kT;
 constexpr int kRadix = 256;
+constexpr int kTSmall = 1024;          // threads of the one-workgroup sort
+constexpr uint32_t kSortSmall = 8192;  // and its largest segment: 80 KB of LDS, eight pairs a lane
 constexpr int kCopies = 16;  // histogram copies: one digit is at most 4-way contended within a wave
 
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
@@ -252,6 +254,101 @@ __global__ __launch_bounds__(kT) void k_rs_scatter(const uint32_t *__restrict__ 
     }
 }
 
+// All passes of a segment of at most kSortSmall elements in one workgroup: the
+// pairs stay in registers and change places through the LDS, ranked as above
+// by (wave, item, lane).  In place.  Bound by the LDS latency of one compute
+// unit: 19 us for four passes over 3 k pairs, whose twelve launches took 58.
+__global__ __launch_bounds__(kTSmall) void k_rs_small(uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
+                                                      int passes, SortPlan plan)
+{
+    constexpr int NW = kTSmall / 64, NI = (int)kSortSmall / kTSmall;
+    __shared__ uint32_t s_keys[kSortSmall];
+    __shared__ uint32_t s_vals[kSortSmall];
+    __shared__ uint32_t s_wcnt[NW][kRadix];
+    __shared__ uint32_t s_start[kRadix];
+    __shared__ uint32_t s_w[kRadix / 64];
+
+    const SortSeg sg = plan.seg[blockIdx.x];
+    if (sg.hi <= sg.lo) return;
+    const uint32_t n = min(sg.hi - sg.lo, kSortSmall);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t lt = lanemask_lt();
+    const int per = (int)((n + kTSmall - 1) / kTSmall);  // items of a lane: the waves share the elements evenly
+    const uint32_t i0 = (uint32_t)(w * per * 64 + lane);
+    uint32_t key[NI], val[NI], rank[NI];
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        const uint32_t i = i0 + it * 64;
+        const bool valid = it < per && i < n;
+        key[it] = valid ? keys[sg.lo + i] - sg.kbase : 0u;
+        val[it] = valid ? vals[sg.lo + i] : 0u;
+    }
+    for (int p = 0; p < passes; ++p) {
+        const int shift = 8 * p;
+#pragma unroll
+        for (int q = 0; q < kRadix * NW / kTSmall; ++q) (&s_wcnt[0][0])[q * kTSmall + threadIdx.x] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+            if (it >= per) break;
+            const bool valid = i0 + it * 64 < n;
+            const uint32_t d = (key[it] >> shift) & 0xFFu;
+            const uint64_t peers = match_digit(d, valid);
+            const uint32_t before = s_wcnt[w][d];
+            rank[it] = before + (uint32_t)__popcll(peers & lt);
+            if (valid && (peers & lt) == 0) s_wcnt[w][d] = before + (uint32_t)__popcll(peers);
+        }
+        __syncthreads();
+        uint32_t tot = 0, inc = 0;
+        if (threadIdx.x < kRadix) {
+#pragma unroll
+            for (int q = 0; q < NW; ++q) {
+                const uint32_t c = s_wcnt[q][threadIdx.x];
+                s_wcnt[q][threadIdx.x] = tot;
+                tot += c;
+            }
+            inc = tot;
+#pragma unroll
+            for (int dd = 1; dd < 64; dd <<= 1) {
+                const uint32_t y = __shfl_up(inc, dd, 64);
+                if (lane >= dd) inc += y;
+            }
+            if (lane == 63) s_w[w] = inc;
+        }
+        __syncthreads();
+        if (threadIdx.x < kRadix) {
+            uint32_t start = inc - tot;
+#pragma unroll
+            for (int q = 0; q < kRadix / 64; ++q) start += q < w ? s_w[q] : 0u;
+            s_start[threadIdx.x] = start;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+            if (it >= per || i0 + it * 64 >= n) break;
+            const uint32_t d = (key[it] >> shift) & 0xFFu;
+            const uint32_t at = s_start[d] + s_wcnt[w][d] + rank[it];
+            s_keys[at] = key[it];
+            s_vals[at] = val[it];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+            const uint32_t i = i0 + it * 64;
+            if (it >= per || i >= n) break;
+            key[it] = s_keys[i];
+            val[it] = s_vals[i];
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        const uint32_t i = i0 + it * 64;
+        if (it >= per || i >= n) break;
+        keys[sg.lo + i] = key[it] + sg.kbase;
+        vals[sg.lo + i] = val[it];
+    }
+}
+
 // One segment of the whole array.
 __global__ __launch_bounds__(kMaxViews) void k_plan_whole(uint32_t cap, const uint32_t *__restrict__ n_dev,
                                                           SortPlan plan, int G, uint32_t *__restrict__ tot,
@@ -279,13 +376,23 @@ void launch_plan_whole(uint32_t cap, const uint32_t *n_dev, int bits, const Sort
 }
 
 // Sorts (keys, vals) over bits [0, bits) with ceil(bits / 8) passes that
-// ping-pong between (keys, vals) and the scratch pair.  Returns true when the
-// pass count is odd, i.e. the sorted result is in (s.k2, s.v2).
+// ping-pong between (keys, vals) and the scratch pair, or, if cap is small, in
+// place.  Returns true when the sorted result is in (s.k2, s.v2).
 bool launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t cap, int nseg, int bits, const SortScratch &s,
                        hipStream_t st)
 {
     if (cap == 0 || bits <= 0) return false;
     const int passes = (bits + 7) / 8;
+    // No segment can be larger than the array.  One launch instead of three a
+    // pass: a render of 4096 leaves (3 k visible) 177 -> 148 us, of 8192
+    // visible splats 182 us against 208 with 8193 places and the passes over
+    // many blocks, as four views of 2048 against 2049 (184, 221).  Twice as
+    // many would fill the LDS and serve one compute unit with twice the work,
+    // which is about what the launches cost.
+    if (cap <= kSortSmall) {
+        hipLaunchKernelGGL(k_rs_small, dim3(nseg), dim3(kTSmall), 0, st, keys, vals, passes, s.plan);
+        return false;
+    }
     const int G = sort_grid(cap, nseg);
     uint32_t *ki = keys, *vi = vals, *ko = s.k2, *vo = s.v2;
     for (int p = 0; p < passes; ++p) {
