@@ -563,7 +563,7 @@ void enqueue_forward(hgs_ctx *ctx, int nv, uint32_t n_tiles, hipStream_t st, hip
     launch_preprocess(h, ctx->views_dev, nv, ctx->cut_base, ctx->cut_ids, ctx->cut_t, &ctx->ctr->cut_total,
                       ctx->cut_cap, ctx->recs, ctx->axes, ctx->depth_key, ctx->trec, ctx->ntiles, ctx->cjac,
                       ctx->vis_mask, ctx->pos_mask, ctx->vis_counts, nv > 1 ? ctx->chunk_order : nullptr,
-                      ctx->tile_w, ctx->tile_h, st);
+                      ctx->tile_w, ctx->tile_h, &ctx->ctr->inf_colour, st);
     mark(2);
     const uint32_t vblocks = (ctx->cut_cap + 255) / 256;
     launch_scan(ctx->vis_counts, vblocks, nullptr, ctx->vis_offsets, &ctx->ctr->vis_total, ctx->partial, st);

@@ -88,7 +88,7 @@ struct __align__(16) SplatRec {
     float fx, fy;          // mean - anchor
     float An, Ap;          // kappa |o_n|, kappa |o_p|
     float t, invK;
-    float r, g, b;
+    float r, g, b;         // -0: infinite (k_blend_end)
     float unused;
 };
 // The axes w = (w1x, w1y, w2x, w2y) are kept beside the record in FP64
@@ -106,6 +106,8 @@ struct Counters {
     uint32_t vis_total;
     uint32_t pair_total;
     uint32_t overflow;
+    uint32_t inf_colour;  // not 0: a visible splat has an infinite colour
+    uint32_t pad;
     unsigned long long evaluated;
     unsigned long long blended;
     unsigned long long evaluated_t;      // evaluated pairs of interpolated splats (t > 0)
@@ -244,7 +246,7 @@ void launch_preprocess(const DevHier &h, const DevView *views, int nv, const uin
                        const int32_t *cut_ids, const double *cut_t, const uint32_t *cut_total, uint32_t cap,
                        SplatRec *recs, double4 *axes, uint32_t *depth_key, uint4 *trec, uint32_t *ntiles,
                        float *cjac, uint64_t *vis_mask, uint64_t *pos_mask, uint32_t *vis_block_counts,
-                       const uint32_t *order, int tile_w, int tile_h, hipStream_t st);
+                       const uint32_t *order, int tile_w, int tile_h, uint32_t *inf_colour, hipStream_t st);
 // Also writes vis_rank[k] = compaction position of visible cut entry k (the
 // row of its screen-space gradient).
 void launch_compact_visible(const uint64_t *vis_mask, const uint32_t *vis_block_offsets, const uint32_t *cut_total,

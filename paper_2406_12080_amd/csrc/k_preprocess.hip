@@ -148,7 +148,8 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
                                                    float *__restrict__ cjac, uint64_t *__restrict__ vis_mask,
                                                    uint64_t *__restrict__ pos_mask,
                                                    uint32_t *__restrict__ vis_block_counts,
-                                                   const uint32_t *__restrict__ order, int tile_w, int tile_h)
+                                                   const uint32_t *__restrict__ order, int tile_w, int tile_h,
+                                                   uint32_t *__restrict__ inf_colour)
 {
     __shared__ __align__(16) char s_sh[kT / 64][kShStage];
     __shared__ uint2 s_src[kT / 64][64];
@@ -252,9 +253,16 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
                        p2 = __ballot(vis && raw[2] > 0.0f);
         if (lane < 3) pos_mask[(size_t)(k >> 6) * 3 + lane] = lane == 0 ? p0 : (lane == 1 ? p1 : p2);
         if (vis) {
-            r.r = fmaxf(raw[0], 0.0f);
-            r.g = fmaxf(raw[1], 0.0f);
-            r.b = fmaxf(raw[2], 0.0f);
+            auto clamp = [&](float c) -> float {  // at 0 (NaN too); an infinite colour as -0, and noted
+                if (c == __builtin_inff()) {
+                    *inf_colour = 1u;
+                    return -0.0f;
+                }
+                return fabsf(fmaxf(c, 0.0f));
+            };
+            r.r = clamp(raw[0]);
+            r.g = clamp(raw[1]);
+            r.b = clamp(raw[2]);
             r.unused = 0.0f;
         }
         // record, colour Jacobian and axes, row by row through the LDS
@@ -1258,14 +1266,14 @@ void launch_preprocess(const DevHier &h, const DevView *views, int nv, const uin
                        const int32_t *cut_ids, const double *cut_t, const uint32_t *cut_total, uint32_t cap,
                        SplatRec *recs, double4 *axes, uint32_t *depth_key, uint4 *trec, uint32_t *ntiles,
                        float *cjac, uint64_t *vis_mask, uint64_t *pos_mask, uint32_t *vis_block_counts,
-                       const uint32_t *order, int tile_w, int tile_h, hipStream_t st)
+                       const uint32_t *order, int tile_w, int tile_h, uint32_t *inf_colour, hipStream_t st)
 {
     uint32_t blocks = (cap + kT - 1) / kT;
     if (!blocks) return;
     if (order) blocks = chunk_grid(blocks);
     hipLaunchKernelGGL(k_preprocess, dim3(blocks), dim3(kT), 0, st, h, views, nv, cut_base, cut_ids, cut_t, cut_total,
                        cap, recs, axes, depth_key, trec, ntiles, cjac, vis_mask, pos_mask, vis_block_counts, order, tile_w,
-                       tile_h);
+                       tile_h, inf_colour);
 }
 
 void launch_compact_visible(const uint64_t *vis_mask, const uint32_t *vis_block_offsets, const uint32_t *cut_total,
