@@ -817,15 +817,19 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
             float dan[2], dap[2], aT[2], dal[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                // every lane runs the update; with a = 0 it leaves T and R as they are
-                const float a = con[s] ? al[s] : 0.0f;
-                T = T * __builtin_amdgcn_rcpf(1.0f - a);
-                aT[s] = a * T;
-                const float d0 = Cv[s].x - R0, d1 = Cv[s].y - R1, d2 = Cv[s].z - R2;
-                dal[s] = T * fmaf(d2, g2, fmaf(d0, g0, d1 * g1));
-                R0 = fmaf(a, d0, R0);
-                R1 = fmaf(a, d1, R1);
-                R2 = fmaf(a, d2, R2);
+                // under the lane mask: with a = 0 for the others an infinite colour
+                // would make NaN of their R
+                dal[s] = aT[s] = 0.0f;
+                if (con[s]) {
+                    const float a = al[s];
+                    T = T * __builtin_amdgcn_rcpf(1.0f - a);
+                    aT[s] = a * T;
+                    const float d0 = Cv[s].x - R0, d1 = Cv[s].y - R1, d2 = Cv[s].z - R2;
+                    dal[s] = T * fmaf(d2, g2, fmaf(d0, g0, d1 * g1));
+                    R0 = fmaf(a, d0, R0);
+                    R1 = fmaf(a, d1, R1);
+                    R2 = fmaf(a, d2, R2);
+                }
             }
             // dL/da_n, dL/da_p (zero through the clamps)
             if (any_t) {

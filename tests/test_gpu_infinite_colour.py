@@ -67,3 +67,38 @@ def test_image(tile):
     assert np.isposinf(inf[..., 0][touched]).all()
     assert np.array_equal(inf[~touched], one[~touched])
     assert np.array_equal(inf[..., 1:][touched], one[..., 1:][touched])
+
+
+@pytest.mark.parametrize("det", [False, True])
+@pytest.mark.parametrize("tile", TILES)
+def test_gradient(tile, det):
+    """Pixel (16, 16) ends at the infinite splat, which no pixel of its quarter
+    blends; splats on the quarter's far pixel, before and behind it, keep
+    their gradients."""
+    if det:
+        tile = tile[:3] + (0,)
+    from paper_2406_12080_amd import hgs
+    got = []
+    for red in (1.0, HUGE):
+        h = _scene([(16, 16, 1.0, 2.0, 0.1), (16, 16, 1.1, 1.0 - 0.0108, 0.1), (19, 19, 2.0, 0.6, 0.7),
+                    (15.2, 15.2, 3.0, 0.9, red), (19, 19, 4.0, 0.7, 0.3), (18, 18, 5.0, 0.7, 0.3)])
+        r, img = _render(h, tile)
+        try:
+            r.set_deterministic(det)
+            r.render([scenes.axis_view(W, H, F, tau=4.0)], out=[img])
+            nb = r.buffer(hgs.BUF_N_BLEND, torch.int32).view(H, W)
+            assert nb[16, 16] == 2 and nb[19, 19] >= 2
+            assert bool(torch.isfinite(img[16:20, 16:20]).all())
+            assert bool(torch.isfinite(img[15, 15]).all()) == (red < HUGE)
+            g = {k: torch.zeros_like(t) for k, t in hgs.params_to_device(h).items()}
+            dL = torch.ones_like(img)
+            r.backward([dL], g)
+            got.append({k: t.cpu().numpy() for k, t in g.items()})
+        finally:
+            r.close()
+    for k in got[0]:
+        for node in (3, 5, 6):
+            a, b = got[0][k][node], got[1][k][node]
+            assert np.isfinite(b).all(), (k, node)
+            assert np.abs(a).max() > 0 or k == "rot", (k, node)
+            assert np.allclose(a, b, rtol=1e-6, atol=1e-7 * np.abs(a).max()), (k, node)
