@@ -137,6 +137,7 @@ __device__ __forceinline__ uint32_t chunk_place(uint32_t g)
     return ((j / kXcdRun) * 8 + (g & 7u)) * kXcdRun + j % kXcdRun;
 }
 
+template <bool SH_ALIGNED>
 __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *__restrict__ views, int nv,
                                                    const uint32_t *__restrict__ cut_base,
                                                    const int32_t *__restrict__ cut_ids,
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
     if (m) {
         float raw[3] = {0.0f, 0.0f, 0.0f}, dcol[3][3], dpn[3];
         const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        splat_colour(h.sh, vis, pn, pp, t, dir, s_sh[w], s_src[w], raw, dcol, dpn);
+        splat_colour<SH_ALIGNED>(h.sh, vis, pn, pp, t, dir, s_sh[w], s_src[w], raw, dcol, dpn);
         // the channels above the colour's clamp at zero
         const uint64_t p0 = __ballot(vis && raw[0] > 0.0f), p1 = __ballot(vis && raw[1] > 0.0f),
                        p2 = __ballot(vis && raw[2] > 0.0f);
@@ -1271,7 +1272,8 @@ void launch_preprocess(const DevHier &h, const DevView *views, int nv, const uin
     uint32_t blocks = (cap + kT - 1) / kT;
     if (!blocks) return;
     if (order) blocks = chunk_grid(blocks);
-    hipLaunchKernelGGL(k_preprocess, dim3(blocks), dim3(kT), 0, st, h, views, nv, cut_base, cut_ids, cut_t, cut_total,
+    auto k = (uintptr_t)h.sh % 16 == 0 ? k_preprocess<true> : k_preprocess<false>;
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kT), 0, st, h, views, nv, cut_base, cut_ids, cut_t, cut_total,
                        cap, recs, axes, depth_key, trec, ntiles, cjac, vis_mask, pos_mask, vis_block_counts, order, tile_w,
                        tile_h, inf_colour);
 }

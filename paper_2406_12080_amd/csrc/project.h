@@ -260,7 +260,10 @@ __device__ __forceinline__ void project_splat(const DevHier &h, const DevView &V
 // bytes of every visible lane's two records at a time, straight into its 8 KB
 // of LDS (`stage`), four lanes per record and each line once; a lane then
 // reads its own rows.  Quad c of row r lies at place (c + r / 2) % 4 of the
-// row, so that 8 lanes' reads fall into 8 different 16-byte units.
+// row, so that 8 lanes' reads fall into 8 different 16-byte units.  Bound
+// coefficients may begin at any float (a group inside one flat buffer): where
+// that is not a multiple of 16 bytes, they go to the LDS through registers (a
+// kernel of its own, so that the aligned one stays as it is).
 constexpr int kShQuads = 4;                          // 16-byte quads of a record per pass
 constexpr int kShStage = 2 * 64 * kShQuads * 16;     // bytes of LDS per wave
 
@@ -270,6 +273,7 @@ __device__ __forceinline__ void load_lds16(const float *src, char *dst)
                                      (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
 }
 
+template <bool ALIGNED>
 __device__ __forceinline__ void splat_colour(const float *__restrict__ sh, bool vis, size_t pn, size_t pp, float t,
                                              const float (&dir)[3], char *stage, uint2 *src, float raw[3],
                                              float dcol[3][3], float dpn[3])
@@ -298,11 +302,20 @@ __device__ __forceinline__ void splat_colour(const float *__restrict__ sh, bool 
                 const int row = 16 * i + lr;
                 if (row < rows) {
                     const uint2 s = src[row];
-                    load_lds16(sh + (size_t)48 * s.x + 16 * pass + 4 * lc, stage + 1024 * i);
-                    load_lds16(sh + (size_t)48 * s.y + 16 * pass + 4 * lc, stage + 4096 + 1024 * i);
+                    const float *an = sh + (size_t)48 * s.x + 16 * pass + 4 * lc;
+                    const float *ap = sh + (size_t)48 * s.y + 16 * pass + 4 * lc;
+                    if constexpr (ALIGNED) {
+                        load_lds16(an, stage + 1024 * i);
+                        load_lds16(ap, stage + 4096 + 1024 * i);
+                    } else {
+                        float4 *o = reinterpret_cast<float4 *>(stage + 1024 * i) + lane;
+                        o[0] = make_float4(an[0], an[1], an[2], an[3]);
+                        o[256] = make_float4(ap[0], ap[1], ap[2], ap[3]);
+                    }
                 }
             }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if constexpr (!ALIGNED) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_wave_barrier();
         if (vis) {
 #pragma unroll
