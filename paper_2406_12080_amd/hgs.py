@@ -174,7 +174,8 @@ def make_views(views) -> ctypes.Array:
             pass  # not all of one shape: one by one
         else:
             with np.errstate(over="ignore"):
-                f = np.array([(v.fx, v.fy, v.cx, v.cy, v.z_near, v.tau) for v in views], np.float64)
+                f = np.array([(float(v.fx), float(v.fy), float(v.cx), float(v.cy), float(v.z_near), float(v.tau))
+                              for v in views])
                 a["f"], a["zt"] = f[:, :4], f[:, 4:]
             a["wh"] = np.array([(int(v.width), int(v.height)) for v in views])
             return (View * n).from_buffer(a)
