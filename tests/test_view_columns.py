@@ -1,5 +1,6 @@
 """Many view records at once take what one at a time takes and refuse what it
-refuses, whatever the number: anything that float() accepts as an intrinsic."""
+refuses, whatever the number: anything that float() accepts as an intrinsic,
+and rotations and eyes of their own size only."""
 from __future__ import annotations
 
 import numpy as np
@@ -25,7 +26,7 @@ SCALARS = {
 }
 
 
-@pytest.mark.parametrize("n", [7, 8])
+@pytest.mark.parametrize("n", [7, 8, 23, 24])
 @pytest.mark.parametrize("every", [1, 3])
 @pytest.mark.parametrize("kind", SCALARS)
 @pytest.mark.filterwarnings("ignore::DeprecationWarning")
@@ -35,5 +36,43 @@ def test_scalars(kind, every, n):
     for i in range(0, n, every):
         f = SCALARS[kind]
         vs[i] = vs[i].replace(fx=f(vs[i].fx), cy=f(vs[i].cy), tau=f(vs[i].tau))
+    one = (hgs.View * n)(*[hgs.make_view(v) for v in vs])
+    assert bytes(hgs.make_views(vs)) == bytes(one)
+
+
+def _refused(vs, n):
+    with pytest.raises(ValueError):
+        [hgs.make_view(v) for v in vs]
+    with pytest.raises(ValueError):
+        hgs.make_views(vs)
+
+
+@pytest.mark.parametrize("n", [7, 8, 23, 24])
+@pytest.mark.parametrize("field", ["R", "eye"])
+def test_sizes_that_add_up(field, n):
+    """Records of the wrong size, n of the right size in all."""
+    vs = _views(n)
+    size = 9 if field == "R" else 3
+    all_of = np.arange(n * size, dtype=np.float32)
+    cut = size + 1  # the first a value too long, the second a value too short
+    vs[0] = vs[0].replace(**{field: all_of[:cut]})
+    vs[1] = vs[1].replace(**{field: all_of[cut:2 * size]})
+    vs[2:] = [v.replace(**{field: all_of[:size]}) for v in vs[2:]]
+    _refused(vs, n)
+
+
+@pytest.mark.parametrize("n", [8, 24])
+def test_blocks_that_add_up(n):
+    """The same with rotations of 2 and 4 rows."""
+    vs = _views(n)
+    vs[0] = vs[0].replace(R=np.ones((2, 3), np.float32))
+    vs[1] = vs[1].replace(R=np.ones((4, 3), np.float32))
+    _refused(vs, n)
+
+
+@pytest.mark.parametrize("n", [7, 8, 23, 24])
+def test_whole_numbers_beyond_64_bits(n):
+    vs = _views(n)
+    vs[3] = vs[3].replace(width=2 ** 70 + 5)
     one = (hgs.View * n)(*[hgs.make_view(v) for v in vs])
     assert bytes(hgs.make_views(vs)) == bytes(one)
