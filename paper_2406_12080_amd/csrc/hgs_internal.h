@@ -77,6 +77,18 @@ void launch_stream_frame(const StreamDev &s, const uint32_t *pinfo, const int32_
                          const StreamParams &cache, hipStream_t st);
 void launch_stream_cleanup(const StreamDev &s, uint32_t max_age, hipStream_t st);
 
+// Between what lanes of a wave write to the LDS and what others of the same
+// wave read there.  The LDS serves a wave in order, so this costs nothing; it
+// keeps the compiler from moving either across.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// 32 bits that also hold two 16-bit values written as such.
+typedef uint32_t __attribute__((may_alias)) two_u16;
+
 // Blend record of one splat (48 bytes).  The mean is kept as an integer pixel
 // anchor plus an FP32 fraction.  The conic (inverse dilated 2D covariance)
 // is used through its eigen-axes scaled so that, for a pixel offset d from

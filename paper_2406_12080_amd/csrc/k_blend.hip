@@ -286,7 +286,7 @@ __device__ __forceinline__ void blend_tile(const DevView *__restrict__ views, in
             const int n_ch = min(cnt - c0, CH);
             if (lane < 4 * (CH / 32)) (&s_hit[w][0][0])[lane] = 0u;
             for (int k = 0; k < n_ch + 4; k += 32)
-                if (k + 2 * ql < LIST) reinterpret_cast<uint32_t *>(&s_list[w][q][0])[k / 2 + ql] = kDead * 0x10001u;
+                if (k + 2 * ql < LIST) reinterpret_cast<two_u16 *>(&s_list[w][q][0])[k / 2 + ql] = kDead * 0x10001u;
             int steps = 0;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -304,9 +304,9 @@ __device__ __forceinline__ void blend_tile(const DevView *__restrict__ views, in
                 steps = max(steps, max(__builtin_amdgcn_readlane(n, 0), __builtin_amdgcn_readlane(n, 32)));
             }
             steps = __builtin_amdgcn_readfirstlane(steps);
-            __builtin_amdgcn_wave_barrier();  // the lists are this wave's own
+            wave_lds_sync();  // the lists are this wave's own
             const uint16_t *list = &s_list[w][q][0];
-            const uint32_t *walk = reinterpret_cast<const uint32_t *>(list);
+            const two_u16 *walk = reinterpret_cast<const two_u16 *>(list);
             // history: the pixel blended (or stopped at) the entry, the latest
             // entry in bit 0; alive0: alive when it was last emptied
             uint32_t hist = 0u;
@@ -383,7 +383,7 @@ __device__ __forceinline__ void blend_tile(const DevView *__restrict__ views, in
                 if ((p & 31) == 0) flush(p - 32, 32);
             }
             if (p & 31) flush(p & ~31, p & 31);
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
             // the backward takes, per quarter, only the entries it blended here
             // (entries after the last chunk walked lie after every pixel's last
             // contributor, where the backward never looks): the byte of every
@@ -395,7 +395,7 @@ __device__ __forceinline__ void blend_tile(const DevView *__restrict__ views, in
                 for (int qq = 0; qq < 4; ++qq) byte |= ((s_hit[w][qq][e >> 5] >> (e & 31)) & 1u) << qq;
                 if (e < n_ch) qbits[(size_t)w * qstride + b0 + (uint32_t)(c0 + e)] = (uint8_t)byte;
             }
-            __builtin_amdgcn_wave_barrier();  // read before the next chunk clears it
+            wave_lds_sync();  // read before the next chunk clears it
         }
     }
     if (inside) {
@@ -749,7 +749,7 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
 #pragma unroll
         for (int k = 0; k < 4 * LIST / 2; k += 64)
             if (k + 64 <= 4 * LIST / 2 || k + lane < 4 * LIST / 2)
-                reinterpret_cast<uint32_t *>(&s_list[w][0][0])[k + lane] = kDead * 0x10001u;
+                reinterpret_cast<two_u16 *>(&s_list[w][0][0])[k + lane] = kDead * 0x10001u;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int qa = 2 * h + (lane >> 5), i = lane & 31;
@@ -769,10 +769,10 @@ __device__ __forceinline__ void blend_bwd_tile(const DevView *__restrict__ views
             steps = max(steps, max(__builtin_amdgcn_readlane(n, 0), __builtin_amdgcn_readlane(n, 32)));
         }
         steps = __builtin_amdgcn_readfirstlane(steps);
-        __builtin_amdgcn_wave_barrier();  // the lists are this wave's own
+        wave_lds_sync();  // the lists are this wave's own
         // each quarter walks its list, the four quarters of the wave together,
         // two entries at a time
-        const uint32_t *walk = reinterpret_cast<const uint32_t *>(&s_list[w][q][0]);
+        const two_u16 *walk = reinterpret_cast<const two_u16 *>(&s_list[w][q][0]);
         const uint32_t lim = (uint32_t)min((int)(last - min(last, base)), cnt) * kRec;  // the pixel's last contributor
         uint32_t two = walk[0];
         for (int p = 0; p < steps; p += 2) {

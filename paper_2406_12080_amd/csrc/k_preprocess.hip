@@ -268,7 +268,7 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
         }
         // record, colour Jacobian and axes, row by row through the LDS
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         float4 *o = reinterpret_cast<float4 *>(s_sh[w]);
         static_assert(sizeof(SplatRec) == 48 && kShStage >= 64 * (48 + 48 + 32), "rows of 3, 3 and 2 quads");
         if (vis) {
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
             o[194 + 3 * lane] = make_float4(dcol[2][2], dpn[0], dpn[1], dpn[2]);
             __builtin_memcpy(o + 384 + 2 * lane, &ax4, sizeof ax4);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         const size_t kw = k & ~63u;
         store_rows<3>(o, reinterpret_cast<float4 *>(recs + kw), m, lane);
         store_rows<3>(o + 192, reinterpret_cast<float4 *>(cjac + 12 * kw), m, lane);
@@ -914,13 +914,13 @@ __global__ __launch_bounds__(kT, 3) void k_preprocess_bwd(DevHier h, const DevVi
         if (g_dt) g_dt[k] = dt;
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     float4 *o = reinterpret_cast<float4 *>(stage);
     if (seen)
 #pragma unroll
         for (int q = 0; q < kPG / 4; ++q)
             o[kPG / 4 * lane + q] = make_float4(row[4 * q], row[4 * q + 1], row[4 * q + 2], row[4 * q + 3]);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     const uint64_t lm = __ballot(any);
     if (lane == 0) live[k >> 6] = lm;
     store_rows<kPG / 4>(o, reinterpret_cast<float4 *>(pg + (size_t)kw * kPG), lm, lane);

@@ -284,7 +284,7 @@ __device__ __forceinline__ void splat_colour(const float *__restrict__ sh, bool 
     const int r = __popcll(m & ((1ull << lane) - 1ull));
     const float x = dir[0], y = dir[1], z = dir[2], w0 = 1.0f - t;
     if (vis) src[r] = make_uint2((uint32_t)pn, (uint32_t)pp);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     float Y[16];
     sh_eval_f(x, y, z, Y);
     float sht[48];
@@ -316,7 +316,7 @@ __device__ __forceinline__ void splat_colour(const float *__restrict__ sh, bool 
             }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if constexpr (!ALIGNED) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         if (vis) {
 #pragma unroll
             for (int c = 0; c < kShQuads; ++c) {
