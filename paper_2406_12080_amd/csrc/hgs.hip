@@ -13,6 +13,7 @@
 
 #include "hgs.h"
 #include "hgs_internal.h"
+#include "kept_blocks.h"
 
 using namespace hgs;
 
@@ -82,11 +83,14 @@ struct hgs_ctx {
     DevView *views_dev = nullptr;
     double *cmp_emax = nullptr;  // compaction: per-node maximum granularity over the views
     int64_t cmp_emax_n = 0;
-    // temporaries of the build's two phases, kept for the next one up to
-    // kBuildKeep bytes each; given back when memory runs short (dalloc)
-    char *build_ws[2] = {nullptr, nullptr};
-    size_t build_ws_bytes[2] = {0, 0};
-    bool building = false;  // they are in use
+    // device memory comes from here; keeps the temporaries of the build's two
+    // phases for the next one, up to kBuildKeep bytes each
+    hgs::KeptBlocks mem{[](void **p, size_t n) -> int {
+                            const hipError_t e = hipMalloc(p, n);
+                            if (e != hipSuccess) (void)hipGetLastError();
+                            return (int)e;
+                        },
+                        [](void *p) { (void)hipFree(p); }};
     DevView *views_host = nullptr;  // host records of the current views (pageable, changed freely)
     // pinned staging slots of the asynchronous view copies: a slot is reused
     // only after the copy that reads it has run (its event)
@@ -241,29 +245,19 @@ hgs_status finish_cut(hgs_ctx *ctx, Counters *ctr, int64_t capacity, int64_t *ou
     return HGS_OK;
 }
 
+// What a ctx keeps of each of a build's two blocks: up to 1.6M leaves both
+// stay (a build over the same leaves 3.3 ms, with 54 allocations 16.2).  Beyond,
+// the second is allocated and freed by every build, one allocation in place of
+// about 20, which is still the faster: 2M leaves 4.2 ms against 15.4, 8M 13.2
+// against 26.5, 16M 24.4 against 41 (the calls that the allocator does not
+// stall; on either side it stalls some by 0.1 to 3 s from 3M leaves on).
 constexpr size_t kBuildKeep = (size_t)1 << 30;
-
-void drop_build_ws(hgs_ctx *ctx, int k)
-{
-    if (ctx->build_ws[k]) (void)hipFree(ctx->build_ws[k]);
-    ctx->build_ws[k] = nullptr;
-    ctx->build_ws_bytes[k] = 0;
-}
 
 hgs_status dalloc(hgs_ctx *ctx, void **p, size_t bytes)
 {
-    *p = nullptr;
     if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess && !ctx->building && (ctx->build_ws[0] || ctx->build_ws[1])) {
-        (void)hipGetLastError();
-        for (int k = 0; k < 2; ++k) drop_build_ws(ctx, k);
-        e = hipMalloc(p, bytes);
-    }
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(ctx, HGS_ERR_OOM, "hipMalloc(" + std::to_string(bytes) + "): " + hipGetErrorString(e));
-    }
+    if (const int e = ctx->mem.alloc(p, bytes))
+        return fail(ctx, HGS_ERR_OOM, "hipMalloc(" + std::to_string(bytes) + "): " + hipGetErrorString((hipError_t)e));
     ctx->allocs.push_back(*p);
     return HGS_OK;
 }
@@ -807,7 +801,6 @@ void hgs_destroy(hgs_ctx *ctx)
     for (hipEvent_t e : ctx->event_pool) (void)hipEventDestroy(e);
     for (void *p : ctx->allocs) (void)hipFree(p);
     ctx->allocs.clear();
-    for (int k = 0; k < 2; ++k) drop_build_ws(ctx, k);
     delete[] ctx->views_host;
     for (int k = 0; k < kStageRing; ++k) {
         if (ctx->stage[k]) (void)hipHostFree(ctx->stage[k]);
@@ -1033,8 +1026,6 @@ hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *L, int src_on_device, 
     // build (up to kBuildKeep bytes; what does not fit is freed on every exit).
     // A build of 1M leaves made 54 allocations and frees, each free a
     // device-wide wait (0.24 ms on one machine, 1.6 on another): 12.9 -> 2.5 ms.
-    // One block allocated and freed per build was no faster: mapping it costs
-    // by its size.
     std::vector<void *> tmp;
     char *block = nullptr;
     size_t left = 0;
@@ -1046,33 +1037,14 @@ hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *L, int src_on_device, 
             left -= bytes;
             return HGS_OK;
         }
-        *p = nullptr;
-        const hipError_t e = hipMalloc(p, bytes);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
+        if (ctx->mem.alloc(p, bytes))
             return fail(ctx, HGS_ERR_OOM, "hipMalloc(" + std::to_string(bytes) + ") in the hierarchy build");
-        }
         tmp.push_back(*p);
         return HGS_OK;
     };
     // the block of phase k for its next `count` temporaries of `bytes` in all
     // (where memory has no room for one, they are allocated one by one)
-    auto reserve = [&](int k, size_t bytes, size_t count) {
-        bytes += 256 * count;
-        if (ctx->build_ws_bytes[k] < bytes) {
-            drop_build_ws(ctx, k);
-            void *p = nullptr;
-            if (hipMalloc(&p, bytes) != hipSuccess) {
-                (void)hipGetLastError();
-                left = 0;
-                return;
-            }
-            ctx->build_ws[k] = (char *)p;
-            ctx->build_ws_bytes[k] = bytes;
-        }
-        block = ctx->build_ws[k];
-        left = ctx->build_ws_bytes[k];
-    };
+    auto reserve = [&](int k, size_t bytes, size_t count) { block = ctx->mem.reserve(k, bytes + 256 * count, left); };
     struct Cleanup {
         hgs_ctx *ctx;
         std::vector<void *> &v;
@@ -1082,12 +1054,9 @@ hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *L, int src_on_device, 
             // may leave some queued on the blocks that stay
             (void)hipStreamSynchronize(ctx->stream);
             for (void *p : v) (void)hipFree(p);
-            for (int k = 0; k < 2; ++k)
-                if (ctx->build_ws_bytes[k] > kBuildKeep) drop_build_ws(ctx, k);
-            ctx->building = false;
+            ctx->mem.release(kBuildKeep);
         }
     } cleanup{ctx, tmp};
-    ctx->building = true;
     hgs_status s;
     const size_t comp[5] = {3, 3, 4, 1, 48};
     int64_t cap = 2 * n + 64;  // nodes the level arrays have room for
@@ -1317,10 +1286,7 @@ hgs_status hgs_download(hgs_ctx *ctx, const hgs_hierarchy_out *o, int dst_on_dev
             bmx = o->bmax;
         } else {
             for (void **p : {(void **)&par, (void **)&bmn, (void **)&bmx}) {
-                if (hipMalloc(p, 12 * (size_t)N) != hipSuccess) {
-                    (void)hipGetLastError();
-                    return fail(ctx, HGS_ERR_OOM, "hipMalloc in hgs_download");
-                }
+                if (ctx->mem.alloc(p, 12 * (size_t)N)) return fail(ctx, HGS_ERR_OOM, "hipMalloc in hgs_download");
                 tmp.push_back(*p);
             }
         }
