@@ -117,6 +117,7 @@ struct hgs_ctx {
     uint32_t *jrank = nullptr;  // per cut entry: its slot in the depth order of the visible splats
     double *part = nullptr;     // deterministic backward: 11 doubles per emitted pair
     uint32_t part_cap = 0;
+    size_t sel_cap = 0, word_views_cap = 0;  // of sel and word_views (only the backward's)
     bool deterministic = false;
     uint64_t *vis_mask = nullptr;
     uint32_t *vis_counts = nullptr, *vis_offsets = nullptr;
@@ -435,8 +436,6 @@ hgs_status ensure_fixed(hgs_ctx *ctx, int nv, uint32_t n_tiles, size_t n_pix)
         const int nvc = std::max(nv, ctx->nv_cap), nbc = std::max(nb, ctx->nblocks_cap);
         const size_t words = (size_t)((ctx->n + 63) / 64);
         if ((s = realloc_buf(ctx, ctx->masks, words * nvc + 1))) return s;
-        if ((s = realloc_buf(ctx, ctx->sel, words * nvc + 1))) return s;
-        if ((s = realloc_buf(ctx, ctx->word_views, words * ((nvc + 63) / 64) + 1))) return s;
         if ((s = realloc_buf(ctx, ctx->word_off, words * nvc + 1))) return s;
         if ((s = realloc_buf(ctx, ctx->blk_counts, (size_t)nbc * nvc))) return s;
         if ((s = realloc_buf(ctx, ctx->blk_offsets, (size_t)nbc * nvc))) return s;
@@ -1007,6 +1006,7 @@ hgs_status hgs_upload(hgs_ctx *ctx, const hgs_hierarchy_desc *d, int src_on_devi
     // cut workspace sized for the hierarchy (the grid of the cut sweep depends on N)
     ctx->nblocks_cap = 0;
     ctx->nv_cap = 0;
+    ctx->sel_cap = ctx->word_views_cap = 0;
     return HGS_OK;
 }
 
@@ -1253,6 +1253,7 @@ hgs_status hgs_build(hgs_ctx *ctx, const hgs_leaves_desc *L, int src_on_device, 
     ctx->layout_gen++;
     ctx->nblocks_cap = 0;
     ctx->nv_cap = 0;
+    ctx->sel_cap = ctx->word_views_cap = 0;
     *n_nodes = N;
     return HGS_OK;
 }
@@ -1604,6 +1605,17 @@ static hgs_status run_backward(hgs_ctx *ctx, const hgs_grads *out, const AdamRow
         if (hgs_status s = realloc_buf(ctx, ctx->part, (size_t)ctx->pair_cap * 11)) return s;
         ctx->part_cap = ctx->pair_cap;
         ctx->bgraph_valid = false;
+    }
+    // by the mask words and views of the render: as large as its masks, which a
+    // program that only renders does not need twice
+    const size_t words = (size_t)((ctx->n + 63) / 64), sel = words * nv + 1, wv = words * ((nv + 63) / 64) + 1;
+    if (ctx->sel_cap < sel || ctx->word_views_cap < wv) {
+        ctx->sel_cap = ctx->word_views_cap = 0;
+        ctx->bgraph_valid = false;
+        if (hgs_status s = realloc_buf(ctx, ctx->sel, sel)) return s;
+        if (hgs_status s = realloc_buf(ctx, ctx->word_views, wv)) return s;
+        ctx->sel_cap = sel;
+        ctx->word_views_cap = wv;
     }
     const void *outs[21] = {};
     if (fused) {
