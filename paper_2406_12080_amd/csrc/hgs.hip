@@ -111,7 +111,7 @@ struct hgs_ctx {
     double *cut_t = nullptr;
     SplatRec *recs = nullptr;
     double4 *axes = nullptr;
-    uint32_t *depth_key = nullptr, *ntiles = nullptr;
+    uint32_t *depth_key = nullptr;
     uint4 *trec = nullptr;  // per cut entry: tile rectangle and count (visible entries)
     uint2 *rect = nullptr;  // tile rectangles of the visible splats in depth order
     uint32_t *jrank = nullptr;  // per cut entry: its slot in the depth order of the visible splats
@@ -475,7 +475,6 @@ hgs_status ensure_cut_cap(hgs_ctx *ctx, uint32_t cap)
     if ((s = realloc_buf(ctx, ctx->recs, cap))) return s;
     if ((s = realloc_buf(ctx, ctx->axes, cap))) return s;
     if ((s = realloc_buf(ctx, ctx->depth_key, cap))) return s;
-    if ((s = realloc_buf(ctx, ctx->ntiles, cap))) return s;
     if ((s = realloc_buf(ctx, ctx->rect, cap))) return s;
     if ((s = realloc_buf(ctx, ctx->jrank, cap))) return s;
     if ((s = realloc_buf(ctx, ctx->trec, cap))) return s;
@@ -554,7 +553,7 @@ void enqueue_forward(hgs_ctx *ctx, int nv, uint32_t n_tiles, hipStream_t st, hip
                             ctx->host_params_dev, ctx->cache_params, st);
     mark(1);
     launch_preprocess(h, ctx->views_dev, nv, ctx->cut_base, ctx->cut_ids, ctx->cut_t, &ctx->ctr->cut_total,
-                      ctx->cut_cap, ctx->recs, ctx->axes, ctx->depth_key, ctx->trec, ctx->ntiles, ctx->cjac,
+                      ctx->cut_cap, ctx->recs, ctx->axes, ctx->depth_key, ctx->trec, ctx->cjac,
                       ctx->vis_mask, ctx->pos_mask, ctx->vis_counts, nv > 1 ? ctx->chunk_order : nullptr,
                       ctx->tile_w, ctx->tile_h, &ctx->ctr->inf_colour, st);
     mark(2);

@@ -256,7 +256,7 @@ void launch_chunk_order(const uint32_t *block_offsets, int nblocks, int nv, cons
 // entry (order: as above, or NULL: list order)
 void launch_preprocess(const DevHier &h, const DevView *views, int nv, const uint32_t *cut_base,
                        const int32_t *cut_ids, const double *cut_t, const uint32_t *cut_total, uint32_t cap,
-                       SplatRec *recs, double4 *axes, uint32_t *depth_key, uint4 *trec, uint32_t *ntiles,
+                       SplatRec *recs, double4 *axes, uint32_t *depth_key, uint4 *trec,
                        float *cjac, uint64_t *vis_mask, uint64_t *pos_mask, uint32_t *vis_block_counts,
                        const uint32_t *order, int tile_w, int tile_h, uint32_t *inf_colour, hipStream_t st);
 // Also writes vis_rank[k] = compaction position of visible cut entry k (the

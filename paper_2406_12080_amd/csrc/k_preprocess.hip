@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
                                                    const uint32_t *__restrict__ cut_total, uint32_t cap,
                                                    SplatRec *__restrict__ recs, double4 *__restrict__ axes,
                                                    uint32_t *__restrict__ depth_key,
-                                                   uint4 *__restrict__ trec, uint32_t *__restrict__ ntiles,
+                                                   uint4 *__restrict__ trec,
                                                    float *__restrict__ cjac, uint64_t *__restrict__ vis_mask,
                                                    uint64_t *__restrict__ pos_mask,
                                                    uint32_t *__restrict__ vis_block_counts,
@@ -174,7 +174,6 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
     if (chunk >= cap_chunks) return;
     const uint32_t k = chunk * kT + threadIdx.x;
     bool vis = false;
-    uint32_t nt = 0;
     SplatRec r;
     double4 ax4 = make_double4(0.0, 0.0, 0.0, 0.0);
     size_t pn = 0, pp = 0;  // parameter records of the node and, with t > 0, its parent
@@ -201,7 +200,7 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
                     vis = true;
                     const uint32_t tx0 = (uint32_t)x0 / tile_w, tx1 = (uint32_t)x1 / tile_w;
                     const uint32_t ty0 = (uint32_t)y0 / tile_h, ty1 = (uint32_t)y1 / tile_h;
-                    nt = (tx1 - tx0 + 1) * (ty1 - ty0 + 1);
+                    const uint32_t nt = (tx1 - tx0 + 1) * (ty1 - ty0 + 1);
                     trec[k] = make_uint4(tx0 | (tx1 << 16), ty0 | (ty1 << 16), nt, 0u);
                     const double fu = floor(P.u), fv = floor(P.v);
                     r.ax = (int32_t)fu;
@@ -242,7 +241,6 @@ __global__ __launch_bounds__(kT, 4) void k_preprocess(DevHier h, const DevView *
                 }
             }
         }
-        ntiles[k] = nt;
     }
     const uint64_t m = __ballot(vis);
     if (m) {
@@ -1265,7 +1263,7 @@ void launch_chunk_order(const uint32_t *block_offsets, int nblocks, int nv, cons
 
 void launch_preprocess(const DevHier &h, const DevView *views, int nv, const uint32_t *cut_base,
                        const int32_t *cut_ids, const double *cut_t, const uint32_t *cut_total, uint32_t cap,
-                       SplatRec *recs, double4 *axes, uint32_t *depth_key, uint4 *trec, uint32_t *ntiles,
+                       SplatRec *recs, double4 *axes, uint32_t *depth_key, uint4 *trec,
                        float *cjac, uint64_t *vis_mask, uint64_t *pos_mask, uint32_t *vis_block_counts,
                        const uint32_t *order, int tile_w, int tile_h, uint32_t *inf_colour, hipStream_t st)
 {
@@ -1274,7 +1272,7 @@ void launch_preprocess(const DevHier &h, const DevView *views, int nv, const uin
     if (order) blocks = chunk_grid(blocks);
     auto k = (uintptr_t)h.sh % 16 == 0 ? k_preprocess<true> : k_preprocess<false>;
     hipLaunchKernelGGL(k, dim3(blocks), dim3(kT), 0, st, h, views, nv, cut_base, cut_ids, cut_t, cut_total,
-                       cap, recs, axes, depth_key, trec, ntiles, cjac, vis_mask, pos_mask, vis_block_counts, order, tile_w,
+                       cap, recs, axes, depth_key, trec, cjac, vis_mask, pos_mask, vis_block_counts, order, tile_w,
                        tile_h, inf_colour);
 }
 
