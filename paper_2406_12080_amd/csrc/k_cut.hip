@@ -384,7 +384,6 @@ __global__ __launch_bounds__(kCutThreads) void k_cut_emit(DevHier h, const DevVi
 // 0.218 ms for 11.9 M nodes and 256 views along a corridor (2.89 ms with
 // every view at every node).
 constexpr float kEmaxBand = 2e-5f;
-constexpr int kEmaxWords = 1;  // words (64 nodes) per wave
 
 // (f / d)^2 of a box from V = (eye, f^2)
 __device__ __forceinline__ float view_ratio(const float b[6], const float4 &V, float &d2)

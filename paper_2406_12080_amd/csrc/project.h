@@ -19,50 +19,9 @@
 
 namespace hgs {
 
-// Real orthonormal SH basis, degree <= 3, index l*l + l + m, at a unit vector.
-__device__ __forceinline__ void sh_eval(double x, double y, double z, double Y[16])
-{
-    const double xx = x * x, yy = y * y, zz = z * z;
-    Y[0] = 0.28209479177387814;
-    Y[1] = 0.4886025119029199 * y;
-    Y[2] = 0.4886025119029199 * z;
-    Y[3] = 0.4886025119029199 * x;
-    Y[4] = 1.0925484305920792 * x * y;
-    Y[5] = 1.0925484305920792 * y * z;
-    Y[6] = 0.31539156525252005 * (3.0 * zz - 1.0);
-    Y[7] = 1.0925484305920792 * x * z;
-    Y[8] = 0.5462742152960396 * (xx - yy);
-    Y[9] = 0.5900435899266435 * y * (3.0 * xx - yy);
-    Y[10] = 2.890611442640554 * x * y * z;
-    Y[11] = 0.4570457994644658 * y * (5.0 * zz - 1.0);
-    Y[12] = 0.3731763325901154 * z * (5.0 * zz - 3.0);
-    Y[13] = 0.4570457994644658 * x * (5.0 * zz - 1.0);
-    Y[14] = 1.445305721320277 * z * (xx - yy);
-    Y[15] = 0.5900435899266435 * x * (xx - 3.0 * yy);
-}
-
-// sum_k B[k] * grad Y_k(x, y, z): the gradient of the basis polynomials
-// contracted with per-function weights.
-__device__ __forceinline__ void sh_grad_dot(double x, double y, double z, const double B[16], double g[3])
-{
-    const double xx = x * x, yy = y * y, zz = z * z;
-    const double c1 = 0.4886025119029199, c2 = 1.0925484305920792, c20 = 0.31539156525252005;
-    const double c22 = 0.5462742152960396, c9 = 0.5900435899266435, c10 = 2.890611442640554;
-    const double c11 = 0.4570457994644658, c12 = 0.3731763325901154, c14 = 1.445305721320277;
-    g[0] = c1 * B[3] + c2 * (y * B[4] + z * B[7]) + c22 * 2.0 * x * B[8] + c9 * 6.0 * x * y * B[9] +
-           c10 * y * z * B[10] + c11 * (5.0 * zz - 1.0) * B[13] + c14 * 2.0 * x * z * B[14] +
-           c9 * (3.0 * xx - 3.0 * yy) * B[15];
-    g[1] = c1 * B[1] + c2 * (x * B[4] + z * B[5]) - c22 * 2.0 * y * B[8] + c9 * (3.0 * xx - 3.0 * yy) * B[9] +
-           c10 * x * z * B[10] + c11 * (5.0 * zz - 1.0) * B[11] - c14 * 2.0 * y * z * B[14] -
-           c9 * 6.0 * x * y * B[15];
-    g[2] = c1 * B[2] + c2 * (y * B[5] + x * B[7]) + c20 * 6.0 * z * B[6] + c10 * x * y * B[10] +
-           c11 * 10.0 * y * z * B[11] + c12 * (15.0 * zz - 3.0) * B[12] + c11 * 10.0 * x * z * B[13] +
-           c14 * (xx - yy) * B[14];
-}
-
-// FP32 versions for the forward colour (stored in FP32 afterwards).  The sums
-// are written as the FMAs they are, so that every kernel that evaluates the
-// basis rounds it alike.
+// Real orthonormal SH basis, degree <= 3, index l*l + l + m, at a unit vector,
+// for the forward colour (FP32, as it is stored).  The sums are written as the
+// FMAs they are, so that every kernel that evaluates the basis rounds it alike.
 __device__ __forceinline__ void sh_eval_f(float x, float y, float z, float Y[16])
 {
     const float xx = x * x, yy = y * y, zz = z * z;
@@ -85,6 +44,8 @@ __device__ __forceinline__ void sh_eval_f(float x, float y, float z, float Y[16]
     Y[15] = 0.5900435899266435f * x * fmaf(-3.0f, yy, xx);
 }
 
+// sum_k B[k] * grad Y_k(x, y, z): the gradient of the basis polynomials
+// contracted with per-function weights.
 __device__ __forceinline__ void sh_grad_dot_f(float x, float y, float z, const float B[16], float g[3])
 {
     const float xx = x * x, yy = y * y, zz = z * z;
