@@ -402,7 +402,7 @@ void launch_unpack_nodes(const uint32_t *pinfo, const float *box, int64_t N, int
 // preprocess backward and the gradient gather.
 constexpr int kPGradFloats = 20;
 
-constexpr int kL1Blocks = 4096;  // >= kMaxViews
+constexpr int kL1Blocks = 4096;
 void launch_l1(const DevView *views, int nv, uint32_t n_pix, double *partial, double *loss, hipStream_t st);
 
 // backward
