@@ -409,13 +409,13 @@ hgs_status hgs_set_deterministic(hgs_ctx *ctx, int32_t on);
 hgs_status hgs_interior(hgs_ctx *ctx, int32_t *ids, int64_t cap, int64_t *count);
 
 /* Tuning knobs of the blend stage and its backward (chosen by the
- * autotuner): tile edge tile_w x tile_h in {8x8, 16x8, 16x16, 32x16},
- * splats staged per batch (a multiple of 64 up to 1024; 0 = one per
- * thread; the kernels stage at most one per thread at a time), and the work
- * distribution: persistent = 0 launches one workgroup
- * per tile, 1 a persistent grid of as many workgroups as the device holds
- * at once, which take tiles (longest lists first) from a device-side queue
- * until none is left.  Changing them keeps images bit-identical.
+ * autotuner): tile edge tile_w x tile_h, and the work distribution: persistent
+ * = 0 launches one workgroup per tile, 1 a persistent grid of as many
+ * workgroups as the device holds at once, which take tiles (longest lists
+ * first) from a device-side queue until none is left.  batch is accepted for
+ * compatibility and has no effect (the forward stages one splat per thread,
+ * the backward 32 per wave): 0, or with 8x8 tiles 64, 128 or 256, 16x8 128 or
+ * 256, 16x16 256 or 512, 32x16 512.  Changing them keeps images bit-identical.
  * HGS_ERR_INVALID_ARG for other values. */
 hgs_status hgs_set_tuning(hgs_ctx *ctx, int32_t tile_w, int32_t tile_h, int32_t batch, int32_t persistent);
 

@@ -1,11 +1,12 @@
-"""Autotuner of the blend stage: picks the (tile edge, splats staged per
-batch, work distribution) with the fastest step for a given batch of views.
-Every candidate gives bit-identical images, so the choice only moves time."""
+"""Autotuner of the blend stage: picks the (tile edge, work distribution) with
+the fastest step for a given batch of views.  Every candidate gives
+bit-identical images, so the choice only moves time."""
 from __future__ import annotations
 
 import time
 
-# tile_w, tile_h, batch: every combination the library supports
+# tile_w, tile_h, batch; the batch has no effect (set_tuning accepts it and
+# launches the same kernels)
 SHAPES = ((8, 8, 64), (8, 8, 128), (16, 8, 128), (16, 8, 256), (16, 16, 256), (16, 16, 512), (32, 16, 512))
 # each with one workgroup per tile (0) and with a persistent grid over a
 # device-side tile queue (1)
@@ -14,15 +15,20 @@ CANDIDATES = tuple((tw, th, b, p) for tw, th, b in SHAPES for p in (0, 1))
 
 def autotune(r, views, step=None, reps: int = 1, candidates=CANDIDATES, log=None) -> dict:
     """Time `step` (default: a batched render of `views` on renderer `r`)
-    once to warm up and `reps` times per candidate, keep the fastest as the
-    renderer's tuning and return it."""
+    once to warm up and `reps` times per candidate (the first of those with one
+    tile and work distribution), keep the fastest as the renderer's tuning and
+    return it."""
     import torch
     if step is None:
         def step():
             r.render(views)
     best = None
     times = {}
+    timed = set()
     for tw, th, b, p in candidates:
+        if (tw, th, p) in timed:
+            continue
+        timed.add((tw, th, p))
         r.set_tuning(tw, th, b, p)
         step()
         torch.cuda.synchronize()
