@@ -254,10 +254,11 @@ __global__ __launch_bounds__(kT) void k_rs_scatter(const uint32_t *__restrict__ 
     }
 }
 
-// All passes of a segment of at most kSortSmall elements in one workgroup: the
-// pairs stay in registers and change places through the LDS, ranked as above
-// by (wave, item, lane).  In place.  Bound by the LDS latency of one compute
-// unit: 19 us for four passes over 3 k pairs, whose twelve launches took 58.
+// All passes of a segment of an array of at most kSortSmall places in one
+// workgroup: the pairs stay in registers and change places through the LDS,
+// ranked as above by (wave, item, lane).  In place.  Bound by the LDS latency of
+// one compute unit: 19 us for four passes over 3 k pairs, whose twelve launches
+// took 58.
 __global__ __launch_bounds__(kTSmall) void k_rs_small(uint32_t *__restrict__ keys, uint32_t *__restrict__ vals,
                                                       int passes, SortPlan plan)
 {
@@ -383,8 +384,11 @@ bool launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t cap, int nseg, i
 {
     if (cap == 0 || bits <= 0) return false;
     const int passes = (bits + 7) / 8;
-    // No segment can be larger than the array.  One launch instead of three a
-    // pass: a render of 4096 leaves (3 k visible) 177 -> 148 us, of 8192
+    // By the array's capacity, which the host knows, not by the number of pairs,
+    // which it does not: no segment can be larger.  So it serves the depth sort
+    // while the ctx has rendered nothing larger (its buffers do not shrink) and
+    // the sorts of a build; the pair list always has room for more.  One launch
+    // instead of three a pass: a render of 4096 leaves (3 k visible) 177 -> 148 us, of 8192
     // visible splats 182 us against 208 with 8193 places and the passes over
     // many blocks, as four views of 2048 against 2049 (184, 221).  Twice as
     // many would fill the LDS and serve one compute unit with twice the work,
