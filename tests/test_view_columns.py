@@ -26,7 +26,7 @@ SCALARS = {
 }
 
 
-@pytest.mark.parametrize("n", [7, 8, 23, 24])
+@pytest.mark.parametrize("n", [7, 8, 15, 16, 24])
 @pytest.mark.parametrize("every", [1, 3])
 @pytest.mark.parametrize("kind", SCALARS)
 @pytest.mark.filterwarnings("ignore::DeprecationWarning")
@@ -40,14 +40,14 @@ def test_scalars(kind, every, n):
     assert bytes(hgs.make_views(vs)) == bytes(one)
 
 
-def _refused(vs, n):
-    with pytest.raises(ValueError):
+def _refused(vs, error=ValueError):
+    with pytest.raises(error):
         [hgs.make_view(v) for v in vs]
-    with pytest.raises(ValueError):
+    with pytest.raises(error):
         hgs.make_views(vs)
 
 
-@pytest.mark.parametrize("n", [7, 8, 23, 24])
+@pytest.mark.parametrize("n", [7, 8, 15, 16, 24])
 @pytest.mark.parametrize("field", ["R", "eye"])
 def test_sizes_that_add_up(field, n):
     """Records of the wrong size, n of the right size in all."""
@@ -58,21 +58,29 @@ def test_sizes_that_add_up(field, n):
     vs[0] = vs[0].replace(**{field: all_of[:cut]})
     vs[1] = vs[1].replace(**{field: all_of[cut:2 * size]})
     vs[2:] = [v.replace(**{field: all_of[:size]}) for v in vs[2:]]
-    _refused(vs, n)
+    _refused(vs)
 
 
-@pytest.mark.parametrize("n", [8, 24])
+@pytest.mark.parametrize("n", [8, 16, 24])
 def test_blocks_that_add_up(n):
     """The same with rotations of 2 and 4 rows."""
     vs = _views(n)
     vs[0] = vs[0].replace(R=np.ones((2, 3), np.float32))
     vs[1] = vs[1].replace(R=np.ones((4, 3), np.float32))
-    _refused(vs, n)
+    _refused(vs)
 
 
-@pytest.mark.parametrize("n", [7, 8, 23, 24])
+@pytest.mark.parametrize("n", [7, 8, 15, 16, 24])
 def test_whole_numbers_beyond_64_bits(n):
     vs = _views(n)
     vs[3] = vs[3].replace(width=2 ** 70 + 5)
     one = (hgs.View * n)(*[hgs.make_view(v) for v in vs])
     assert bytes(hgs.make_views(vs)) == bytes(one)
+
+
+@pytest.mark.parametrize("n", [7, 8, 16, 24])
+@pytest.mark.parametrize("bad,error", [(None, TypeError), ([1.0, 2.0], TypeError), (1j, TypeError), ("x", ValueError)])
+def test_no_numbers(n, bad, error):
+    vs = _views(n)
+    vs[2] = vs[2].replace(fy=bad)
+    _refused(vs, error)
