@@ -8,7 +8,7 @@ stream.  Importing this module does not need a GPU; creating a
 from __future__ import annotations
 
 import ctypes
-import math
+import operator
 import os
 
 import numpy as np
@@ -159,33 +159,30 @@ def _fill_view(out: View, v) -> None:
 _VIEWS = np.dtype([("R", np.float32, 9), ("eye", np.float32, 3), ("f", np.float32, 4), ("wh", np.int32, 2),
                    ("zt", np.float32, 2)])
 assert _VIEWS.itemsize == ctypes.sizeof(View)
+_INTRINSICS = operator.attrgetter("fx", "fy", "cx", "cy", "z_near", "tau")
+_SIZE = operator.attrgetter("width", "height")
 
 
 def make_views(views) -> ctypes.Array:
     """The array of ``make_view`` of each.  From 16 on it is filled column by
-    column (256 views: 0.32 ms, one record after the other in place 0.53; 16:
-    0.034 and 0.034)."""
+    column (256 views: 0.29 ms, one record after the other in place 0.53; 16:
+    0.030 and 0.035)."""
     n = len(views)
     if n >= 16:
         a = np.empty(n, _VIEWS)
         try:
-            # every record of its own size: sizes that only add up would mix the views
-            R, eye = [v.R for v in views], [v.eye for v in views]
-            if any(math.prod(s) != 9 for s in {x.shape for x in R}):
+            # (one array of all refuses records of different sizes)
+            R, eye = np.array([v.R for v in views]), np.array([v.eye for v in views])
+            f = np.array(list(map(_INTRINSICS, views)), np.float64)
+            wh = np.array(list(map(_SIZE, views)))
+            if (R.size, eye.size) != (9 * n, 3 * n) or f.shape != (n, 6) or np.isnan(f).any() or wh.dtype != np.int64:
                 raise ValueError
-            if any(math.prod(s) != 3 for s in {x.shape for x in eye}):
-                raise ValueError
-            a["R"] = np.concatenate(R).reshape(n, 9)
-            a["eye"] = np.concatenate(eye).reshape(n, 3)
-            f = np.array([(v.fx, v.fy, v.cx, v.cy, v.z_near, v.tau) for v in views], np.float64)
-            if f.shape != (n, 6) or np.isnan(f).any():
-                raise ValueError
+            a["R"], a["eye"], a["wh"] = R.reshape(n, 9), eye.reshape(n, 3), wh
             with np.errstate(over="ignore"):
                 a["f"], a["zt"] = f[:, :4], f[:, 4:]
-            a["wh"] = np.array([(int(v.width), int(v.height)) for v in views], np.int64)
             return (View * n).from_buffer(a)
-        except (AttributeError, ValueError, TypeError, RuntimeError, OverflowError):
-            pass  # not arrays of one shape, not plain numbers, beyond a column's range: one by one
+        except (ValueError, TypeError, RuntimeError, OverflowError):
+            pass  # not of one shape, not plain numbers, beyond a column's range: one by one
     arr = (View * n)()
     for out, v in zip(arr, views):
         _fill_view(out, v)
