@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import operator
 import os
+from itertools import chain
 
 import numpy as np
 
@@ -165,17 +166,17 @@ _SIZE = operator.attrgetter("width", "height")
 
 def make_views(views) -> ctypes.Array:
     """The array of ``make_view`` of each.  From 16 on it is filled column by
-    column (256 views: 0.29 ms, one record after the other in place 0.53; 16:
-    0.030 and 0.035)."""
+    column (256 views: 0.22 ms, one record after the other in place 0.53; 16:
+    0.026 and 0.035)."""
     n = len(views)
     if n >= 16:
         a = np.empty(n, _VIEWS)
         try:
             # (one array of all refuses records of different sizes)
             R, eye = np.array([v.R for v in views]), np.array([v.eye for v in views])
-            f = np.array(list(map(_INTRINSICS, views)), np.float64)
-            wh = np.array(list(map(_SIZE, views)))
-            if (R.size, eye.size) != (9 * n, 3 * n) or f.shape != (n, 6) or np.isnan(f).any() or wh.dtype != np.int64:
+            f = np.fromiter(chain.from_iterable(map(_INTRINSICS, views)), np.float64, 6 * n).reshape(n, 6)
+            wh = np.fromiter(chain.from_iterable(map(_SIZE, views)), np.int64, 2 * n).reshape(n, 2)
+            if (R.size, eye.size) != (9 * n, 3 * n) or np.isnan(f).any():  # (it takes None for NaN)
                 raise ValueError
             a["R"], a["eye"], a["wh"] = R.reshape(n, 9), eye.reshape(n, 3), wh
             with np.errstate(over="ignore"):

@@ -3,6 +3,8 @@ refuses, whatever the number: anything that float() accepts as an intrinsic,
 and rotations and eyes of their own size only."""
 from __future__ import annotations
 
+from fractions import Fraction
+
 import numpy as np
 import pytest
 
@@ -23,6 +25,8 @@ SCALARS = {
     "tensor with gradient": lambda x: torch.tensor(x, requires_grad=True),
     "text": str,
     "integer": int,
+    "double of numpy": np.float64,
+    "fraction": Fraction,
 }
 
 
@@ -84,3 +88,13 @@ def test_no_numbers(n, bad, error):
     vs = _views(n)
     vs[2] = vs[2].replace(fy=bad)
     _refused(vs, error)
+
+
+@pytest.mark.parametrize("n", [7, 16])
+@pytest.mark.parametrize("size", [64.9, "64", np.int32(64), np.float32(64.5), True, Fraction(129, 2)])
+def test_image_sizes(n, size):
+    """int() of whatever it is."""
+    vs = _views(n)
+    vs[1] = vs[1].replace(width=size)
+    one = (hgs.View * n)(*[hgs.make_view(v) for v in vs])
+    assert bytes(hgs.make_views(vs)) == bytes(one) and one[1].width == int(size)
