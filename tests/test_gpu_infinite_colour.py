@@ -102,3 +102,34 @@ def test_gradient(tile, det):
             assert np.isfinite(b).all(), (k, node)
             assert np.abs(a).max() > 0 or k == "rot", (k, node)
             assert np.allclose(a, b, rtol=1e-6, atol=1e-7 * np.abs(a).max()), (k, node)
+
+
+def test_replayed():
+    """Two views in one captured graph, the colour made infinite and finite again
+    in place between the replays."""
+    from paper_2406_12080_amd import hgs
+    h = _scene([(x, y, 3.0 + 0.01 * x, 0.5, 0.5) for x in range(2, W, 5) for y in range(2, H, 5)])
+    vs = [scenes.axis_view(W, H, F, tau=4.0), scenes.axis_view(W, H, F, tau=4.0, eye=(0.05, 0.0, 0.0))]
+    r = hgs.Renderer(0)
+    try:
+        r.upload(h)
+        P = hgs.params_to_device(h)
+        r.bind(*[P[k] for k in hgs.PARAM_FIELDS])
+        out = [torch.empty((H, W, 3), device="cuda") for _ in vs]
+        sh = P["sh"].clone()
+        pictures = []
+        for huge in (False, True, False, True, True, False):
+            P["sh"].copy_(sh)
+            if huge:
+                P["sh"][7, [0, 6, 18]] = HUGE
+            r.render(vs, out=out)
+            pictures.append([o.clone() for o in out])
+        for k in range(2):
+            a, b = pictures[0][k], pictures[1][k]
+            inf = torch.isposinf(b[..., 0])
+            assert 4 <= int(inf.sum()) <= 16
+            assert torch.equal(a[~inf], b[~inf]) and torch.equal(a[..., 1:], b[..., 1:])
+            for i, p in enumerate(pictures):
+                assert torch.equal(p[k], pictures[1 if i in (1, 3, 4) else 0][k])
+    finally:
+        r.close()
